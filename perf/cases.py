@@ -1,0 +1,381 @@
+"""The work that a user of this package has it do, as cases to time.
+
+Ranges the cases stand for:
+  training     1-40 tables of 1000 rows to 51 GB, rows of 8-256 floats, batches of 64-65536
+               samples, bags of 1-32 lookups, Zipf exponents 1.05-1.2 with popular rows next to
+               each other or scattered, none to all of the hot rows stale, inputs dropped when
+               all or half of their lookups are stale; through the step scheduler
+               (PipelinedStep), through the calls in order (EmbeddingStep, also with its
+               one-launch lookup + grouping), and with the feature normalization fused into
+               the lookup (ss_embbag_forward_ln / ss_embbag_ln_backward)
+  setting up   access counters and the selection of the hot rows; the search for the
+               threshold on a sample of the inputs
+Everything is fp32 with int32 row ids: the package has no other types.  Sizes that are not the
+package's stated workloads (workload.CONFIGS) are generic.
+
+A training pass is a stretch of consecutive batches (one snapshot period in most of the listed
+cases), indices and gradients in device memory, as a data loader and a dense model leave them.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2404_04270_amd import binding as B
+from paper_2404_04270_amd.sampling import SamplingBlock
+from paper_2404_04270_amd.step import EmbeddingStep, PipelinedStep
+
+GRAD_BUFFERS = 4           # gradient tensors in turn, as the dense model's output buffers
+LR, GRAD_SIGMA, INIT_BOUND = 0.01, 0.01, 0.05
+LN_EPS = 1e-5
+
+
+def _train(name, kind, tables, rows, dim, batch, bag, zipf, hot, every, threshold, batches,
+           permute=False, stale_share=0.0, alpha_share=1.0):
+    return {"name": name, "kind": kind, "tables": tables, "rows": rows, "dim": dim,
+            "batch": batch, "bag": bag, "zipf": zipf, "permute": permute, "hot": hot,
+            "every": every, "threshold": threshold, "batches": batches,
+            "stale_share": stale_share, "alpha_share": alpha_share}
+
+
+def listed():
+    return [
+        # the smallest stated workload, call by call: what a first experiment, a test or a small
+        # model costs per iteration (launches and host time)
+        _train("calls_8x10k_d16", "calls", 8, 10_000, 16, 128, 1, 1.05, 100, 10, 1e-3, 10),
+        # sizes that are multiples of nothing: an in-house model with short bags and 36-float rows
+        _train("calls_5x123457_d36_bag3", "calls", 5, 123_457, 36, 777, 3, 1.1, 1234, 25, 5e-4, 25,
+               permute=True),
+        # the headline workload, call by call on one stream (a program that puts its dense model
+        # between lookup and update and uses no scheduler)
+        _train("calls_26x1m_d64", "calls", 26, 1_000_000, 64, 8192, 1, 1.2, 5000, 100, 1e-4, 100),
+        # the stated workload of small rows, through the scheduler
+        _train("pipelined_26x100k_d16", "pipelined", 26, 100_000, 16, 2048, 1, 1.1, 1000, 50, 5e-4,
+               50, permute=True),
+        # the headline workload (Terabyte-like one-hot features)
+        _train("pipelined_26x1m_d64", "pipelined", 26, 1_000_000, 64, 8192, 1, 1.2, 5000, 100, 1e-4,
+               100),
+        # the same late in training: every hot row stale, the skip path busy
+        _train("pipelined_26x1m_d64_frozen", "pipelined", 26, 1_000_000, 64, 8192, 1, 1.2, 5000,
+               100, 1e-4, 100, stale_share=1.0),
+        # large-batch training of medium rows; no power of two anywhere
+        _train("pipelined_26x500k_d32_b40000", "pipelined", 26, 500_000, 32, 40_000, 1, 1.15, 5000,
+               50, 1e-4, 50, permute=True),
+        # the multi-hot workload (41 GB of tables, 20 lookups per bag)
+        _train("pipelined_8x10m_d128_bag20", "pipelined", 8, 10_000_000, 128, 4096, 20, 1.2, 10_000,
+               100, 1e-4, 100),
+        # the single huge table (51 GB)
+        _train("pipelined_1x200m_d64", "pipelined", 1, 200_000_000, 64, 65_536, 1, 1.05, 100_000,
+               200, 1e-4, 200),
+        # training with feature normalization fused into the lookup, headline geometry
+        _train("normalized_26x1m_d64", "normalized", 26, 1_000_000, 64, 8192, 1, 1.2, 5000, 0, 0.0,
+               20),
+        # which rows are hot: access counts over sampled inputs, then the most accessed rows
+        {"name": "hot_set_26x1m", "kind": "hot_set", "tables": 26, "rows": 1_000_000,
+         "batch": 8192, "bag": 1, "zipf": 1.2, "permute": True, "hot": 5000, "batches": 16},
+        # which threshold: drifts of the hot rows, then the search on a sample of the hot inputs
+        {"name": "threshold_26x1m_d64", "kind": "threshold", "tables": 26, "rows": 1_000_000,
+         "dim": 64, "bag": 1, "zipf": 1.2, "permute": False, "hot": 5000, "samples": 65_536},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["pipelined"] * 4 + ["calls"] * 2 + ["grouped", "normalized", "hot_set",
+                                                          "threshold"])
+    tables = _log_int(rng, 1, 40)
+    zipf = round(rng.uniform(1.05, 1.2), 3)
+    permute = rng.random() < 0.5
+    dim = 4 * _log_int(rng, 2, 64)
+    rows = _log_int(rng, 1000, min(20_000_000, (6 << 30) // (tables * dim * 4)))
+    hot = max(1, int(rows * math.exp(rng.uniform(math.log(5e-4), math.log(2e-2)))))
+    bag = 1 if kind == "grouped" or rng.random() < 0.6 else _log_int(rng, 2, 32)
+    if kind == "hot_set":
+        batch = _log_int(rng, 256, max(512, min(65_536, 2_000_000 // (tables * bag))))
+        return {"kind": kind, "tables": tables, "rows": rows, "batch": batch,
+                "bag": bag, "zipf": zipf, "permute": permute, "hot": hot,
+                "batches": rng.randint(4, 24)}
+    if kind == "threshold":
+        return {"kind": kind, "tables": tables, "rows": rows, "dim": dim, "bag": bag,
+                "zipf": zipf, "permute": permute, "hot": hot,
+                "samples": _log_int(rng, 1000, min(200_000, max(1100, 4_000_000 // (tables * bag))))}
+    batch = _log_int(rng, 64, max(128, min(65_536, 1_500_000 // (tables * bag))))
+    # as many batches as stay below the bytes of the largest listed case
+    per_batch = 4 * tables * batch * dim * (bag + 2)
+    batches = max(2, min(rng.randint(10, 60), int(1.5e10 / per_batch)))
+    case = _train("", kind, tables, rows, dim, batch, bag, zipf, hot, max(2, batches // 2),
+                  rng.choice([1e-4, 5e-4, 1e-3]), batches, permute,
+                  rng.choice([0.0, 0.0, 0.5, 1.0]), rng.choice([1.0, 1.0, 0.5]))
+    del case["name"]
+    return case
+
+
+# ---- inputs ---------------------------------------------------------------------------------
+def _zipf_ranks(shape, n, zipf, gen):
+    """Ranks 0 .. n-1 with P(k) ~ (k+1)^-zipf: the power law's continuous inverse, rounded."""
+    a = 1.0 - zipf
+    lo, hi = 0.5 ** a, (n + 0.5) ** a
+    u = torch.rand(shape, dtype=torch.float64, device="cuda", generator=gen)
+    x = u.mul_(hi - lo).add_(lo).pow_(1.0 / a)
+    return x.round_().sub_(1.0).clamp_(0, n - 1).to(torch.int64)
+
+
+def _to_row(ranks, rows, permute, table):
+    """Popular rows next to each other at the start of the table, or scattered over it."""
+    if not permute:
+        return ranks
+    mul = 2_654_435_761
+    while math.gcd(mul, rows) != 1:
+        mul += 2
+    return (ranks * mul + 7919 * table) % rows
+
+
+def _indices(case, n, batch, gen, ranks_below=None):
+    """int32 [n, T, batch, L]"""
+    out = torch.empty(n, case["tables"], batch, case["bag"], dtype=torch.int32, device="cuda")
+    for t in range(case["tables"]):
+        r = _zipf_ranks((n, batch, case["bag"]), ranks_below or case["rows"], case["zipf"], gen)
+        out[:, t] = _to_row(r, case["rows"], case["permute"], t)
+    return out
+
+
+def _hot_ids(case):
+    """The rows of the most popular ranks, ascending, per table."""
+    r = torch.arange(case["hot"], device="cuda")
+    return [_to_row(r, case["rows"], case["permute"], t).sort().values.to(torch.int32)
+            for t in range(case["tables"])]
+
+
+def _stale_bits(case, bits):
+    """The less popular hot rows settle first: the last `stale_share` of the hot ranks."""
+    first = int(round(case["hot"] * (1.0 - case["stale_share"])))
+    r = torch.arange(first, case["hot"], device="cuda")
+    for t, b in enumerate(bits):
+        row = _to_row(r, case["rows"], case["permute"], t)
+        word = torch.zeros(b.numel(), dtype=torch.int64, device="cuda")
+        word.index_add_(0, row >> 5, torch.ones_like(row) << (row & 31))
+        b.copy_(word)
+
+
+def _weights(case, gen):
+    w = torch.empty(case["tables"], case["rows"], case["dim"], device="cuda")
+    return w.uniform_(-INIT_BOUND, INIT_BOUND, generator=gen)
+
+
+def _gradients(case, gen):
+    shape = (case["tables"], case["batch"], case["dim"])
+    return [torch.randn(shape, device="cuda", generator=gen).mul_(GRAD_SIGMA)
+            for _ in range(min(GRAD_BUFFERS, case["batches"]))]
+
+
+def _alpha(case):
+    return max(1, int(case["tables"] * case["bag"] * case["alpha_share"]))
+
+
+class _Normalized:
+    """Buffers of a training loop with the normalization fused into lookup and backward."""
+
+    def __init__(self, case, weights, gen):
+        T, D, n, L = case["tables"], case["dim"], case["batch"], case["bag"]
+        self.tables = B.Tables(weights)
+        self.bits = self.tables.new_bits()
+
+        def new(*shape, dtype=torch.float32):
+            return torch.zeros(*shape, dtype=dtype, device="cuda")
+
+        self.skip_mask, self.kept_ids = new(n, dtype=torch.uint8), new(n, dtype=torch.int32)
+        self.n_kept, self.idx_c = new(1, dtype=torch.int32), new(T, n, L, dtype=torch.int32)
+        self.ws_filter = new(max(256, B.ss_filter_batch_workspace_bytes(T, n, L)),
+                             dtype=torch.uint8)
+        self.ws_backward = new(B.ss_backward_workspace_bytes(T, n, L, D), dtype=torch.uint8)
+        self.ws_ln = new(B.ss_layernorm_backward_workspace_bytes(T, D, n), dtype=torch.uint8)
+        self.y, self.dx = new(T, n, D), new(T, n, D)
+        self.mean, self.rstd = new(T, n), new(T, n)
+        self.gamma = torch.rand(T, D, device="cuda", generator=gen).add_(0.5)
+        self.beta = torch.randn(T, D, device="cuda", generator=gen).mul_(0.1)
+        self.dgamma, self.dbeta = new(T, D), new(T, D)
+        self.alpha = _alpha(case)
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(int(seed))
+    kind, s = case["kind"], {"case": case}
+    if kind == "hot_set":
+        T, R, H = case["tables"], case["rows"], case["hot"]
+        s["idx"] = list(_indices(case, case["batches"], case["batch"], gen).unbind(0))
+        s["flat"] = torch.zeros(T, R, dtype=torch.int32, device="cuda")
+        s["counters"] = B.AccessCounters(T, R, s["flat"].device, list(s["flat"].unbind(0)))
+        s["ids"] = torch.zeros(T, H, dtype=torch.int32, device="cuda")
+        s["bits"] = torch.zeros(T, B.Tables.bitmap_words(R), dtype=torch.int32, device="cuda")
+        s["ws"] = torch.empty(B.ss_select_hot_workspace_bytes(T, R), dtype=torch.uint8,
+                              device="cuda")
+        s["out"] = list(s["ids"].unbind(0)), list(s["bits"].unbind(0))
+        return s
+    s["w"] = _weights(case, gen)
+    weights = list(s["w"].unbind(0))
+    if kind == "threshold":
+        T, S = case["tables"], case["samples"]
+        tables = B.Tables(weights)
+        tables.new_bits()
+        s["hot"] = B.HotState(tables, _hot_ids(case), diagnostics=True)
+        B.ss_detect_stale(tables, s["hot"], 0.0, True)            # the snapshot
+        # then every hot row moves, by amounts over two decades
+        for w, ids in zip(weights, s["hot"].hot_ids):
+            far = torch.rand(len(ids), 1, device="cuda", generator=gen).mul_(2.0).sub_(5.0)
+            step = torch.randn(len(ids), case["dim"], device="cuda", generator=gen)
+            w[ids.long()] += step * (10.0 ** far)
+        # the sample is taken from the inputs that read hot rows only
+        sidx = _indices(case, 1, S, gen, ranks_below=case["hot"])[0].contiguous()
+        s["block"] = SamplingBlock(tables, s["hot"], sidx, alpha=T * case["bag"],
+                                   population=1000 * S)
+        return s
+    s["idx"] = list(_indices(case, case["batches"], case["batch"], gen).unbind(0))
+    s["grads"] = _gradients(case, gen)
+    if kind == "normalized":
+        s["step"] = _Normalized(case, weights, gen)
+    else:
+        more = {} if kind == "pipelined" else {"grouped_forward": kind == "grouped"}
+        s["step"] = (PipelinedStep if kind == "pipelined" else EmbeddingStep)(
+            weights, _hot_ids(case), case["batch"], case["bag"], LR, case["threshold"],
+            case["every"], alpha=_alpha(case), diagnostics=False, **more)
+    if case["stale_share"] > 0:        # resumed late in training
+        _stale_bits(case, s["step"].bits)
+    return s
+
+
+# ---- one pass -------------------------------------------------------------------------------
+def run(s):
+    return {"pipelined": _run_pipelined, "calls": _run_calls, "grouped": _run_calls,
+            "normalized": _run_normalized, "hot_set": _run_hot_set,
+            "threshold": _run_threshold}[s["case"]["kind"]](s)
+
+
+def _tables_out(s):
+    """The updated tables, in pieces of at most 4 GB."""
+    flat = s["w"].view(-1)
+    return flat if flat.numel() <= 1 << 30 else list(flat.split(1 << 30))
+
+
+def _run_pipelined(s):
+    step, idx, grads = s["step"], s["idx"], s["grads"]
+    n, ahead = len(idx), 0
+    for k in range(n):
+        fresh = 0
+        while ahead < n and step.room() > 0 and (fresh < 2 or ahead <= k):
+            step.submit(idx[ahead])
+            ahead += 1
+            fresh += 1
+        pooled = step.forward()
+        step.backward(grads[k % len(grads)])
+    return {"pooled": pooled, "weights": _tables_out(s), "stale": list(step.bits),
+            "skipped": step.skip_mask, "n_kept": step.n_kept}
+
+
+def _run_calls(s):
+    step, idx, grads = s["step"], s["idx"], s["grads"]
+    for k in range(len(idx)):
+        step.filter_forward(idx[k])
+        step.backward(grads[k % len(grads)])
+    return {"pooled": step.pooled, "weights": _tables_out(s), "stale": list(step.bits),
+            "skipped": step.skip_mask, "n_kept": step.n_kept}
+
+
+def _run_normalized(s):
+    m, idx, grads = s["step"], s["idx"], s["grads"]
+    for k in range(len(idx)):
+        B.ss_filter_batch(m.tables, idx[k], m.alpha, m.skip_mask, m.kept_ids, m.n_kept, m.idx_c,
+                          m.ws_filter)
+        B.ss_embbag_forward_ln(m.tables, m.idx_c, m.n_kept, m.gamma, m.beta, LN_EPS, m.y, m.mean,
+                               m.rstd)
+        B.ss_embbag_ln_backward(m.tables, m.idx_c, m.n_kept, grads[k % len(grads)], m.gamma,
+                                m.mean, m.rstd, m.dx, m.dgamma, m.dbeta, m.ws_ln)
+        B.ss_embbag_backward_update(m.tables, m.idx_c, m.n_kept, m.dx, LR, m.ws_backward)
+    return {"y": m.y, "mean": m.mean, "rstd": m.rstd, "dx": m.dx, "dgamma": m.dgamma,
+            "dbeta": m.dbeta, "weights": _tables_out(s), "skipped": m.skip_mask,
+            "n_kept": m.n_kept}
+
+
+def _run_hot_set(s):
+    s["flat"].zero_()
+    for idx in s["idx"]:
+        B.ss_count_accesses(s["counters"], idx)
+    ids, bits = s["out"]
+    B.ss_select_hot_top(s["counters"], s["case"]["hot"], ids, bits, s["ws"])
+    return {"counts": s["flat"], "ids": s["ids"], "bits": s["bits"]}
+
+
+def _run_threshold(s):
+    s["block"].refresh_drift()
+    best, tried = s["block"].find_threshold(0.2, 1e-6, 1e-1)
+    return {"best": 0.0 if best is None else best,
+            "tried": torch.tensor(tried, dtype=torch.float64), "drift": list(s["hot"].drift)}
+
+
+# ---- what a pass cannot do without ----------------------------------------------------------
+def _mass(case, first, last, n=None):
+    """Share of the lookups that hit ranks first .. last-1."""
+    a = 1.0 - case["zipf"]
+    lo, hi = 0.5 ** a, ((n or case["rows"]) + 0.5) ** a
+    return ((last + 0.5) ** a - (first + 0.5) ** a) / (hi - lo)
+
+
+def _distinct(case, lookups, first=0, last=None):
+    """Expected number of distinct rows of ranks first .. last-1 among `lookups` lookups."""
+    edges = np.unique(np.round(np.geomspace(1, case["rows"] + 1, 4000)).astype(np.int64)) - 1
+    edges = np.unique(np.clip(edges, first, case["rows"] if last is None else last))
+    a = 1.0 - case["zipf"]
+    f = (edges + 0.5) ** a
+    ranks = np.diff(edges)
+    p = np.diff(f) / ((case["rows"] + 0.5) ** a - 0.5 ** a) / np.maximum(ranks, 1)
+    return float(np.sum(ranks * -np.expm1(lookups * np.log1p(-np.minimum(p, 1 - 1e-12)))))
+
+
+def _below(n, q, alpha):
+    """P(Binomial(n, q) < alpha)"""
+    if q <= 0:
+        return 1.0
+    if q >= 1:
+        return 1.0 if n < alpha else 0.0
+    log = [math.lgamma(n + 1) - math.lgamma(k + 1) - math.lgamma(n - k + 1) + k * math.log(q)
+           + (n - k) * math.log1p(-q) for k in range(min(alpha, n + 1))]
+    return min(1.0, sum(math.exp(v) for v in log))
+
+
+def work(case):
+    T, L = case["tables"], case["bag"]
+    if case["kind"] == "hot_set":
+        n, R, H = case["batches"] * T * case["batch"] * L, case["rows"], case["hot"]
+        return {"bytes": 4.0 * (n + T * R + T * H + T * R / 32), "flops": float(n)}
+    D, H = case["dim"], case["hot"]
+    if case["kind"] == "threshold":
+        n = T * case["samples"] * L
+        return {"bytes": 4.0 * (n + T * H * (1 + 2 * D + 2)), "flops": 3.0 * T * H * D + n}
+    n, stale = case["batch"] * L, int(round(H * case["stale_share"]))
+    kept = _below(T * L, _mass(case, H - stale, H) if stale else 0.0, _alpha(case))
+    read = T * _distinct(case, n * kept)
+    frozen = T * _distinct(case, n * kept, H - stale, H) if stale else 0.0
+    vectors = T * case["batch"] * D * kept
+    words = T * n * (1 + kept) + 2 * case["batch"]              # indices read, kept ones written
+    words += read * D + vectors                                 # lookup
+    words += vectors + 2 * (read - frozen) * D                  # update
+    if case["kind"] == "normalized":
+        words += read * D + 2 * vectors                         # rows again, dy in, dx out
+    words *= case["batches"]
+    if case["every"]:
+        words += 3 * T * H * D * (case["batches"] // case["every"])
+    return {"bytes": 4.0 * words, "flops": case["batches"] * 3.0 * T * n * D * kept}
+
+
+def tolerance(case):
+    """Four times what a pass differs by from the same pass in 64 bits: 1e-8 (tables) to 1.8e-7
+    (pooled vectors, normalization parameters) in the norm, 2.8e-6 at the worst element (a row
+    that thousands of lookups update); 1e-16 for the drifts, which are sums in 64 bits."""
+    if case["kind"] == "hot_set":
+        return "exact"
+    if case["kind"] == "threshold":
+        return {"rel": 1e-14, "max": 1e-13}
+    return {"rel": 8e-7, "max": 1.2e-5}
