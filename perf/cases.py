@@ -372,10 +372,11 @@ def work(case):
 
 def tolerance(case):
     """Four times what a pass differs by from the same pass in 64 bits: 1e-8 (tables) to 1.8e-7
-    (pooled vectors, normalization parameters) in the norm, 2.8e-6 at the worst element (a row
-    that thousands of lookups update); 1e-16 for the drifts, which are sums in 64 bits."""
+    (pooled vectors, gradients of the normalization parameters) in the norm and 5e-6 at the worst
+    element (a row that thousands of lookups update); 7.6e-7 in the norm for the means of the
+    normalized vectors, whose terms all but cancel; 1e-16 for the drifts, sums in 64 bits."""
     if case["kind"] == "hot_set":
         return "exact"
     if case["kind"] == "threshold":
         return {"rel": 1e-14, "max": 1e-13}
-    return {"rel": 8e-7, "max": 1.2e-5}
+    return {"rel": 3e-6 if case["kind"] == "normalized" else 8e-7, "max": 2e-5}
