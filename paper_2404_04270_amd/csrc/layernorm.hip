@@ -4,7 +4,9 @@
 //
 // Both directions are bound by HBM: the forward pass reads x and writes y, the
 // backward pass reads dy and x and writes dx (12 bytes per element; the
-// statistics and the parameters are noise).  A group of G lanes owns a vector
+// statistics and the parameters are noise).  What keeps them from its rate is the
+// number of independent loads in flight, so a group asks for several vectors at
+// once.  A group of G lanes owns a vector
 // and keeps it in registers (one f4 per lane for dim <= 256, up to four for
 // dim = 1024), so every element is read once; means are reduced with wavefront
 // shuffles, the variance from the centred values (two passes over registers,
@@ -18,14 +20,20 @@
 // fly (the sum of the bag's rows, in bag order, exactly as ss_embbag_forward
 // forms it) instead of reading it from memory: the pooled tensor is then never
 // written nor read, which at 26 x 8192 x 64 takes 109 MB out of the 273 MB the
-// two passes move.
+// two passes move.  One-hot bags have a form of their own (one load of the row
+// number and one of the row per vector, those of 4 or 2 vectors together, where
+// the bag loop asked for four rows of one bag and then waited): 21.1 instead of
+// 28.0 us forward, 25.1 instead of 30.8 backward at 26 x 8192 x 64.  The forward
+// pass streams y past the caches as the plain lookup does.  Multi-hot bags are
+// pooled by the lookup kernel's own code: 29.0 instead of 33.7 us forward, 25.9
+// instead of 49.0 backward at 8 tables x 4096 bags of 20 x 128.
+#include "forward_body.h"
 #include "ss_common.h"
 
 namespace ss {
 namespace {
 
 // P below = f4 per lane: 1 for dim <= 256, up to 4 for dim = 64 lanes * 4 * 4 = 1024
-constexpr int kLnTiles = 8;          // vectors per group and workgroup (backward)
 
 template <int G>
 __device__ __forceinline__ float group_sum(float v)
@@ -36,6 +44,20 @@ __device__ __forceinline__ float group_sum(float v)
 }
 
 __device__ __forceinline__ float hsum(f4 v) { return (v.x + v.y) + (v.z + v.w); }
+
+// Sums of products, and products that later sums use, with their roundings spelled out:
+// which of two products of a sum becomes part of an FMA is otherwise the compiler's choice,
+// and the kernels that read their vectors and those that pool them must agree bit for bit.
+__device__ __forceinline__ float hdot(f4 a, f4 b)
+{
+    return fmaf(a.x, b.x, a.y * b.y) + fmaf(a.z, b.z, a.w * b.w);
+}
+template <typename A, typename B>
+__device__ __forceinline__ A mul_rounded(A a, B b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
 
 // loads the lane's share of a vector; lanes / slots past the row read nothing
 template <int G, int P>
@@ -49,8 +71,9 @@ __device__ __forceinline__ void load_row(const f4 *__restrict__ p, int c, int D4
     }
 }
 
-// Where a vector comes from: memory (x != nullptr), or the bag of rows it is the
-// sum of.
+// Where the vectors come from: memory, the one row a one-hot bag names, or the bag of
+// rows a vector is the sum of (kBagFull: a row fills its group of lanes exactly).
+enum XFrom { kMemory, kOneHot, kBag, kBagFull };
 struct XSource {
     const float *x;                  // [T][Bcap][dim]
     const float *const *weights;     // tables
@@ -95,27 +118,65 @@ __device__ __forceinline__ void pool_row(const XSource &src, int t, int64_t vec,
         if (c + i * G >= D4) v[i] = f4{0.f, 0.f, 0.f, 0.f};
 }
 
-template <int G, int P, bool POOL>
-__device__ __forceinline__ void fetch_x(const XSource &src, int t, int64_t vec, int c, int D4,
-                                        f4 (&v)[P])
+// The V vectors j0 + k * NG of table t (those at n or beyond: vector j0 again, which is
+// always valid), everything that does not depend on another load requested at once.
+template <int G, int P, int V, XFrom FROM>
+__device__ __forceinline__ void fetch_x(const XSource &src, int t, int Bcap, int j0, int NG,
+                                        int n, int c, int D4, f4 (&v)[V][P])
 {
-    if (POOL)
-        pool_row<G, P>(src, t, vec, c, D4, v);
-    else
-        load_row<G, P>(reinterpret_cast<const f4 *>(src.x) + vec * D4, c, D4, v);
+    const int64_t base = (int64_t)t * Bcap;
+    if constexpr (FROM == kOneHot) {
+        const auto W = as_global(reinterpret_cast<const f4 *>(src.weights[t]));
+        const int32_t *__restrict__ ip = src.idx + base;
+        int32_t r[V];
+#pragma unroll
+        for (int k = 0; k < V; ++k) r[k] = ip[j0 + k * NG < n ? j0 + k * NG : j0];
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const int col = c + i * G;
+                v[k][i] = f4{0.f, 0.f, 0.f, 0.f};
+                if (col < D4) v[k][i] = W[(int64_t)r[k] * D4 + col];
+            }
+    } else {
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const int64_t vec = base + (j0 + k * NG < n ? j0 + k * NG : j0);
+            if constexpr (P == 1 && (FROM == kBag || FROM == kBagFull)) {
+                // lanes past the row form the sum of column 0 and hold zeros, as after load_row
+                const auto Wc = as_global(reinterpret_cast<const f4 *>(src.weights[t])) +
+                                (FROM == kBagFull || c < D4 ? c : 0);
+                v[k][0] = pool_bag<G, FROM == kBagFull>(Wc, src.idx + vec * src.L, src.L,
+                                                        FROM == kBagFull ? G : D4);
+                if (FROM == kBag && c >= D4) v[k][0] = f4{0.f, 0.f, 0.f, 0.f};
+            } else if constexpr (FROM == kBag)
+                pool_row<G, P>(src, t, vec, c, D4, v[k]);
+            else
+                load_row<G, P>(reinterpret_cast<const f4 *>(src.x) + vec * D4, c, D4, v[k]);
+        }
+    }
 }
 
-// A group takes V vectors of its tile (V = 4 while a vector is one f4 per lane):
-// all their loads are issued before the first of them is normalised, which is
-// what a pass that only streams needs most.
-template <int G, int P, bool POOL>
+// A group takes V vectors of its tile: all their loads are issued before the first of
+// them is normalised, which is what a pass that only streams needs most.  More than four
+// (two in the backward pass, which reads twice as much per vector) leave too few
+// wavefronts to overlap one's loads with another's stores: 24.5 us with eight and 21.0
+// with four forward, 27.9 with four, 24.8 with two and 26.0 with one backward, at 26 x 8192
+// one-hot vectors of 64 floats.
+template <int P, XFrom FROM> constexpr int ln_fwd_vectors()
+{
+    return P > 1 || FROM == kBag || FROM == kBagFull ? 1 : 4;
+}
+
+template <int G, int P, XFrom FROM>
 __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     XSource src, int Bcap, const int32_t *__restrict__ n_valid,
     const float *__restrict__ gamma, const float *__restrict__ beta, float eps,
     float *y, float *__restrict__ mean, float *__restrict__ rstd, int D4,
     int tiles_per_table)
 {
-    constexpr int NG = kWG / G, V = P == 1 ? 4 : 1;
+    constexpr int NG = kWG / G, V = ln_fwd_vectors<P, FROM>();
     const int t = blockIdx.x / tiles_per_table;
     const int tile = blockIdx.x - t * tiles_per_table;
     const int n = clamp_valid(n_valid, Bcap);
@@ -125,12 +186,7 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     const float inv_d = 1.0f / (float)(D4 * 4);
 
     f4 v[V][P];
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-        // vectors past n_valid fetch vector j0 again (always valid) and store nothing
-        const int j = j0 + k * NG < n ? j0 + k * NG : j0;
-        fetch_x<G, P, POOL>(src, t, (int64_t)t * Bcap + j, c, D4, v[k]);
-    }
+    fetch_x<G, P, V, FROM>(src, t, Bcap, j0, NG, n, c, D4, v);
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const int j = j0 + k * NG;
@@ -140,16 +196,16 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < P; ++i) s += hsum(v[k][i]);
-        const float mu = group_sum<G>(s) * inv_d;
+        const float mu = mul_rounded(group_sum<G>(s), inv_d);
         float q = 0.f;
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             if (c + i * G < D4) {
                 v[k][i] = v[k][i] - mu;
-                q += hsum(v[k][i] * v[k][i]);
+                q += hdot(v[k][i], v[k][i]);
             }
         }
-        const float var = group_sum<G>(q) * inv_d;
+        const float var = mul_rounded(group_sum<G>(q), inv_d);
         const float rs = 1.0f / sqrtf(var + eps);
 #pragma unroll
         for (int i = 0; i < P; ++i) {
@@ -158,7 +214,8 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
                 f4 o = v[k][i] * rs;
                 if (gamma) o = o * reinterpret_cast<const f4 *>(gamma)[(int64_t)t * D4 + col];
                 if (beta) o = o + reinterpret_cast<const f4 *>(beta)[(int64_t)t * D4 + col];
-                yp[col] = o;
+                if (FROM == kMemory) yp[col] = o;
+                else __builtin_nontemporal_store(o, &yp[col]);
             }
         }
         if (c == 0) {
@@ -168,17 +225,22 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     }
 }
 
-// Workgroup b of a table takes vectors [b * NG * kLnTiles, (b+1) * NG * kLnTiles);
-// group g takes every NG-th of them.  Partial parameter gradients: one row of
-// dim floats per workgroup for dgamma and one for dbeta.
-template <int G, int P, bool POOL>
+// Workgroup b of a table takes vectors [b * NG * tiles, (b+1) * NG * tiles); group g
+// takes every NG-th of them, V at a time (tiles is a multiple of V).  Partial parameter gradients: one row
+// of dim floats per workgroup for dgamma and one for dbeta.
+template <int P, XFrom FROM> constexpr int ln_bwd_vectors()
+{
+    return P > 1 || FROM == kBag || FROM == kBagFull ? 1 : 2;
+}
+
+template <int G, int P, XFrom FROM>
 __global__ __launch_bounds__(kWG) void ln_backward_kernel(
     const float *dy, XSource src, int Bcap,
     const int32_t *__restrict__ n_valid, const float *__restrict__ gamma,
     const float *__restrict__ mean, const float *__restrict__ rstd, float *dx, int D4,
-    int wgs_per_table, f4 *__restrict__ part_dgamma, f4 *__restrict__ part_dbeta)
+    int tiles, int wgs_per_table, f4 *__restrict__ part_dgamma, f4 *__restrict__ part_dbeta)
 {
-    constexpr int NG = kWG / G;
+    constexpr int NG = kWG / G, V = ln_bwd_vectors<P, FROM>();
     __shared__ f4 s_red[kWG];
     const int t = blockIdx.x / wgs_per_table;
     const int wg = blockIdx.x - t * wgs_per_table;
@@ -197,33 +259,44 @@ __global__ __launch_bounds__(kWG) void ln_backward_kernel(
         acc_g[i] = acc_b[i] = f4{0.f, 0.f, 0.f, 0.f};
     }
 
-    for (int k = 0; k < kLnTiles; ++k) {
-        const int j = (wg * kLnTiles + k) * NG + g;
-        if (j >= n) break;                    // later vectors of this group are past n too
-        const int64_t vec = (int64_t)t * Bcap + j;
-        f4 xv[P], dv[P];
-        load_row<G, P>(reinterpret_cast<const f4 *>(dy) + vec * D4, c, D4, dv);
-        fetch_x<G, P, POOL>(src, t, vec, c, D4, xv);
-        const float mu = mean[vec], rs = rstd[vec];
-        float s1 = 0.f, s2 = 0.f;
+    for (int k0 = 0; k0 < tiles; k0 += V) {
+        const int j0 = (wg * tiles + k0) * NG + g;         // vectors j0 + k * NG
+        if (j0 >= n) break;                   // later vectors of this group are past n too
+        f4 xv[V][P], dv[V][P];
+        float mu[V], rs[V];
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            if (c + i * G < D4) {
-                xv[i] = (xv[i] - mu) * rs;                 // x-hat
-                const f4 gd = gam[i] * dv[i];
-                s1 += hsum(gd);
-                s2 += hsum(gd * xv[i]);
-                acc_g[i] = acc_g[i] + dv[i] * xv[i];
-                acc_b[i] = acc_b[i] + dv[i];
-            }
+        for (int k = 0; k < V; ++k) {
+            const int64_t vec = (int64_t)t * Bcap + (j0 + k * NG < n ? j0 + k * NG : j0);
+            load_row<G, P>(reinterpret_cast<const f4 *>(dy) + vec * D4, c, D4, dv[k]);
+            mu[k] = mean[vec];
+            rs[k] = rstd[vec];
         }
-        const float m1 = group_sum<G>(s1) * inv_d;
-        const float m2 = group_sum<G>(s2) * inv_d;
-        f4 *op = reinterpret_cast<f4 *>(dx) + vec * D4;      // may be dy's own row
+        fetch_x<G, P, V, FROM>(src, t, Bcap, j0, NG, n, c, D4, xv);
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            const int col = c + i * G;
-            if (col < D4) op[col] = (gam[i] * dv[i] - m1 - xv[i] * m2) * rs;
+        for (int k = 0; k < V; ++k) {
+            if (j0 + k * NG >= n) break;
+            const int64_t vec = (int64_t)t * Bcap + j0 + k * NG;
+            float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                if (c + i * G < D4) {
+                    xv[k][i] = mul_rounded(xv[k][i] - mu[k], rs[k]);             // x-hat
+                    const f4 gd = mul_rounded(gam[i], dv[k][i]);
+                    s1 += hdot(gam[i], dv[k][i]);
+                    s2 += hdot(gd, xv[k][i]);
+                    acc_g[i] = acc_g[i] + dv[k][i] * xv[k][i];
+                    acc_b[i] = acc_b[i] + dv[k][i];
+                }
+            }
+            const float m1 = mul_rounded(group_sum<G>(s1), inv_d);
+            const float m2 = mul_rounded(group_sum<G>(s2), inv_d);
+            f4 *op = reinterpret_cast<f4 *>(dx) + vec * D4;      // may be dy's own row
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const int col = c + i * G;
+                if (col < D4)
+                    op[col] = (mul_rounded(gam[i], dv[k][i]) - m1 - xv[k][i] * m2) * rs[k];
+            }
         }
     }
 
@@ -265,6 +338,7 @@ __global__ __launch_bounds__(kWG) void ln_param_reduce_kernel(
     if (col < D4) {
         const f4 *__restrict__ pg = part_dgamma + (int64_t)t * wgs_per_table * D4 + col;
         const f4 *__restrict__ pb = part_dbeta + (int64_t)t * wgs_per_table * D4 + col;
+#pragma unroll 4
         for (int w = part; w < wgs_per_table; w += kParts) {
             sg = sg + pg[(int64_t)w * D4];
             sb = sb + pb[(int64_t)w * D4];
@@ -283,10 +357,27 @@ __global__ __launch_bounds__(kWG) void ln_param_reduce_kernel(
     }
 }
 
-int backward_wgs(int dim, int Bcap)
+// Backward: vectors per lane group, and workgroups per table.  Eight vectors per group
+// keep the partial rows of the parameter gradients few; fewer where that would leave under
+// two workgroups per compute unit, each a chain of trips to memory (9 tables x 3001 vectors
+// of 36 floats pooled from bags of 5: 12.8 us with two per group, 17.6 with eight; 8 x 1000
+// of 512 floats: 11.8 and 17.4).  With the border at 1024 or 1600 workgroups 8 x 4096 x 128
+// (bags of 20) takes 27.7 or 30.2 us instead of 25.9.
+constexpr int kLnMaxTiles = 8;
+constexpr int kLnMinWgs = 512;
+
+struct BackwardPlan {
+    int tiles, wgs;
+};
+
+BackwardPlan plan_backward(int T, int dim, int Bcap)
 {
-    const int per_wg = (kWG / lanes_per_row(dim)) * kLnTiles;
-    return (Bcap + per_wg - 1) / per_wg;
+    const int ng = kWG / lanes_per_row(dim);
+    BackwardPlan p;
+    p.tiles = kLnMaxTiles;
+    while (p.tiles > 2 && (int64_t)T * Bcap < (int64_t)kLnMinWgs * ng * p.tiles) p.tiles /= 2;
+    p.wgs = (Bcap + ng * p.tiles - 1) / (ng * p.tiles);
+    return p;
 }
 
 }  // namespace
@@ -298,28 +389,30 @@ int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *co
 {
     const XSource src{x, weights, idx, L};
     const int D4 = dim / 4, g = lanes_per_row(dim);
-    const int per_tile = (kWG / g) * (D4 <= g ? 4 : 1);      // as V in the kernel
+    const int per_tile = (kWG / g) * (D4 <= g && (x || L == 1) ? 4 : 1);     // as V in the kernel
     const int tiles = (Bcap + per_tile - 1) / per_tile;
     if ((int64_t)tiles * T > 0x7fffffffLL)
         return fail(SS_ERR_UNSUPPORTED, "ss_layernorm_forward: grid too large");
     ProfScope prof(x ? "ln_forward_kernel" : "ln_forward_pool_kernel", s);
-#define SS_LN_FWD(P_)                                                                   \
-    if (x)                                                                              \
-        launch(ln_forward_kernel<G, P_, false>, dim3((unsigned)(tiles * T)), dim3(kWG), s, \
-               src, Bcap, n_valid, gamma, beta, eps, y, mean, rstd, D4, tiles);         \
-    else                                                                                \
-        launch(ln_forward_kernel<G, P_, true>, dim3((unsigned)(tiles * T)), dim3(kWG), s, \
-               src, Bcap, n_valid, gamma, beta, eps, y, mean, rstd, D4, tiles)
+#define SS_LN_FWD1(P_, F_)                                                                   \
+    launch(ln_forward_kernel<G, P_, F_>, dim3((unsigned)(tiles * T)), dim3(kWG), s, src, Bcap, \
+           n_valid, gamma, beta, eps, y, mean, rstd, D4, tiles)
+#define SS_LN_FWD(P_)                                                                        \
+    if (x) { SS_LN_FWD1(P_, kMemory); }                                                      \
+    else if (L == 1) { SS_LN_FWD1(P_, kOneHot); }                                            \
+    else if (P_ == 1 && D4 == g) { SS_LN_FWD1(P_, (P_ == 1 ? kBagFull : kBag)); }             \
+    else { SS_LN_FWD1(P_, kBag); }
     SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_FWD(1); } else {
         if (D4 <= 64) { SS_LN_FWD(1); } else if (D4 <= 128) { SS_LN_FWD(2); } else { SS_LN_FWD(4); }
     });
 #undef SS_LN_FWD
+#undef SS_LN_FWD1
     return check_launch("ss_layernorm_forward");
 }
 
 size_t layernorm_backward_ws_bytes(int T, int dim, int Bcap)
 {
-    return align_up((size_t)2 * T * backward_wgs(dim, Bcap) * dim * sizeof(float), 256);
+    return align_up((size_t)2 * T * plan_backward(T, dim, Bcap).wgs * dim * sizeof(float), 256);
 }
 
 int32_t launch_layernorm_backward(int T, int dim, const float *dy, const float *x,
@@ -330,7 +423,8 @@ int32_t launch_layernorm_backward(int T, int dim, const float *dy, const float *
 {
     const XSource src{x, weights, idx, L};
     const int D4 = dim / 4, g = lanes_per_row(dim);
-    const int wgs = backward_wgs(dim, Bcap);
+    const BackwardPlan plan = plan_backward(T, dim, Bcap);
+    const int wgs = plan.wgs;
     if ((int64_t)wgs * T > 0x7fffffffLL)
         return fail(SS_ERR_UNSUPPORTED, "ss_layernorm_backward: grid too large");
     const bool params = dgamma || dbeta;
@@ -338,17 +432,19 @@ int32_t launch_layernorm_backward(int T, int dim, const float *dy, const float *
     f4 *pb = params ? pg + (size_t)T * wgs * D4 : nullptr;
     {
         ProfScope prof(x ? "ln_backward_kernel" : "ln_backward_pool_kernel", s);
-#define SS_LN_BWD(P_)                                                                   \
-    if (x)                                                                              \
-        launch(ln_backward_kernel<G, P_, false>, dim3((unsigned)(wgs * T)), dim3(kWG), s, dy, \
-               src, Bcap, n_valid, gamma, mean, rstd, dx, D4, wgs, pg, pb);             \
-    else                                                                                \
-        launch(ln_backward_kernel<G, P_, true>, dim3((unsigned)(wgs * T)), dim3(kWG), s, dy, \
-               src, Bcap, n_valid, gamma, mean, rstd, dx, D4, wgs, pg, pb)
+#define SS_LN_BWD1(P_, F_)                                                                   \
+    launch(ln_backward_kernel<G, P_, F_>, dim3((unsigned)(wgs * T)), dim3(kWG), s, dy, src,   \
+           Bcap, n_valid, gamma, mean, rstd, dx, D4, plan.tiles, wgs, pg, pb)
+#define SS_LN_BWD(P_)                                                                        \
+    if (x) { SS_LN_BWD1(P_, kMemory); }                                                      \
+    else if (L == 1) { SS_LN_BWD1(P_, kOneHot); }                                            \
+    else if (P_ == 1 && D4 == g) { SS_LN_BWD1(P_, (P_ == 1 ? kBagFull : kBag)); }             \
+    else { SS_LN_BWD1(P_, kBag); }
         SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_BWD(1); } else {
             if (D4 <= 64) { SS_LN_BWD(1); } else if (D4 <= 128) { SS_LN_BWD(2); } else { SS_LN_BWD(4); }
         });
 #undef SS_LN_BWD
+#undef SS_LN_BWD1
     }
     if (params)
         launch(ln_param_reduce_kernel, dim3((D4 + kRedCols - 1) / kRedCols, T), dim3(kWG), s,
