@@ -14,44 +14,71 @@
 //
 // Selecting.  Both rules reduce to "count > c, or count == c and fewer than e
 // such rows came before": for the share rule c = (smallest passing count) - 1
-// and e = 0, computed on the host; for top-H, c is the H-th largest count, found
-// by a four-pass radix select over the 8-bit digits of the counters (histogram
-// per pass in LDS, one pick step per pass), and e is what is left of H after the
-// rows above c.  A three-step ordered compaction (block totals, scan, write)
-// then emits the ids in ascending order; 64 consecutive rows per wavefront step
-// make the bitmap words fall out of the same ballots.
+// and e = 0, computed on the host; for top-H, c is the H-th largest count and e
+// what is left of H after the rows above c.  The counters are the only large
+// thing here (104 MB for 26 x 1 M rows), so what counts is how often they are
+// read: twice.  One pass builds a histogram whose bins tell counts below 1024
+// apart, as nearly all are, and larger ones to an eighth of an octave; its last
+// workgroup per table picks the bin that holds the H-th largest count.  Where
+// that bin holds several counts, up to three further passes split it by ten bits
+// each (they are always launched and leave at once where nothing is left to
+// split).  A second pass over the counters writes two bitmaps, "above c" and
+// "equal to c", and their bits per 4096 rows; the last step works on these
+// bitmaps, a sixteenth of the counters: every workgroup adds up what lies
+// before its 32768 rows, ranks its bits, and writes ids in ascending order and
+// the bitmap.  26 x 1 M rows: histogram 32 us (and 3 x 1.5), bitmaps 18, ids 7, instead of
+// four histogram passes of 34 us with 5 us each to pick a digit, 25 to count, 54 to write;
+// one table of 200 M rows 0.39 instead of 3.2 ms.
 #include "ss_common.h"
 
 namespace ss {
 namespace {
 
-constexpr int kCountSlots = 1024;        // LDS counters per workgroup
-constexpr int kCountChunk = 2048;        // lookups per workgroup
-constexpr int kSelSteps = 16;            // 64-row steps per wavefront
-constexpr int kSelRows = kSelSteps * kWG;   // rows per workgroup: 4096
+constexpr int kBlockRows = 4096;         // selection: rows per workgroup of the bitmap pass
+constexpr int kBlockWords = kBlockRows / 32;
+constexpr int kSuper = 64;               // ... blocks whose totals are also summed up,
+constexpr int kManyBlocks = 2048;        // ... in tables of more blocks than this
+constexpr int kWriteBlocks = 8;          // ... blocks per workgroup of the last step
+constexpr int kHistThreads = 512;        // histogram passes: threads per workgroup
+constexpr int kHistStep = kHistThreads * 4;   // ... rows of a step of a workgroup
+constexpr uint32_t kExact = 1024;        // counts below this have a bin each
+constexpr int kExactBits = 10;
+constexpr int kSubBits = 3;              // larger ones: 2^3 bins per octave
+constexpr int kBins = (int)kExact + ((32 - kExactBits) << kSubBits);
+constexpr int kRefine = 3;               // passes that split a bin, kExactBits each
 
-__global__ __launch_bounds__(kWG) void count_kernel(
+// NT threads with ITEMS lookups each, all requested before the first is counted.  What
+// bounds it is the rate of adds to memory (about 30 per nanosecond): fewer, the
+// more lookups share an LDS table; but a small batch wants many short workgroups, each of
+// which is one chain of trips to memory (row ids, LDS slots, counters).
+template <int NT, int ITEMS, int SLOTS>
+__global__ __launch_bounds__(NT) void count_kernel(
     const int32_t *__restrict__ idx, int Bcap, int L, const int32_t *__restrict__ n_valid,
     uint32_t *const *__restrict__ counts, int chunks_per_table)
 {
-    __shared__ uint32_t s_tag[kCountSlots];
-    __shared__ uint32_t s_cnt[kCountSlots];
+    __shared__ uint32_t s_tag[SLOTS];
+    __shared__ uint32_t s_cnt[SLOTS];
     const int t = blockIdx.x / chunks_per_table;
     const int chunk = blockIdx.x - t * chunks_per_table;
+    const int64_t cap = (int64_t)Bcap * L;
+    const int64_t first = (int64_t)chunk * (ITEMS * NT) + threadIdx.x;
+    const int32_t *__restrict__ ip = idx + (int64_t)t * cap;
+    uint32_t row[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)      // (requested before the number of valid ones is known)
+        row[i] = (uint32_t)ip[first + i * NT < cap ? first + i * NT : 0];
     const int64_t n = (int64_t)clamp_valid(n_valid, Bcap) * L;     // lookups of this table
-    const int64_t first = (int64_t)chunk * kCountChunk;
-    if (first >= n) return;
-    for (int i = threadIdx.x; i < kCountSlots; i += kWG) {
+    for (int i = threadIdx.x; i < SLOTS; i += NT) {
         s_tag[i] = kNoRow;
         s_cnt[i] = 0;
     }
     __syncthreads();
-    const int32_t *__restrict__ ip = idx + (int64_t)t * Bcap * L;
     uint32_t *cg = counts[t];
-    const int64_t last = first + kCountChunk < n ? first + kCountChunk : n;
-    for (int64_t q = first + threadIdx.x; q < last; q += kWG) {
-        const uint32_t r = (uint32_t)ip[q];
-        const uint32_t slot = (r * 2654435761u) >> 22;            // 10 bits
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        if (first + i * NT >= n) continue;
+        const uint32_t r = row[i];
+        const uint32_t slot = (r * 2654435761u) / (uint32_t)(0x100000000ull / SLOTS);
         const uint32_t seen = atomicCAS(&s_tag[slot], kNoRow, r);
         if (seen == kNoRow || seen == r)
             atomicAdd(&s_cnt[slot], 1u);
@@ -59,282 +86,416 @@ __global__ __launch_bounds__(kWG) void count_kernel(
             atomicAdd(&cg[r], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kCountSlots; i += kWG) {
+    for (int i = threadIdx.x; i < SLOTS; i += NT) {
         const uint32_t r = s_tag[i];
         if (r != kNoRow) atomicAdd(&cg[r], s_cnt[i]);
     }
 }
 
 // ---- selection ---------------------------------------------------------
-// state[t] = { c, e }: rows with count > c are taken, and the first e rows (by
-// row id) with count == c.
+// state[t]: while the histogram passes run, the H-th largest count is known to lie in
+// [c, c + 2^width), and e of the rows in that range (by count, then by id) are still to be
+// taken.  In the end width = 0: rows with count > c are taken, and the first e rows (by row
+// id) with count == c.
 struct SelState {
     uint32_t c, e;
+    int32_t width;
+    uint32_t pad;
 };
 
-__global__ void sel_set_state_kernel(SelState *state, int T, uint32_t c, uint32_t e)
+// Four neighbouring counters; a table's counters are only 4-byte aligned.
+typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ void load4(gptr<const uint32_t> cg, int64_t r, int64_t R,
+                                      uint32_t (&c)[4], bool (&in)[4])
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < T) state[t] = SelState{c, e};
+    if (r + 4 <= R) {
+        const u4 v = *(gptr<const u4>)(cg + r);
+        c[0] = v.x, c[1] = v.y, c[2] = v.z, c[3] = v.w;
+        in[0] = in[1] = in[2] = in[3] = true;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            in[j] = r + j < R;
+            c[j] = in[j] ? cg[r + j] : 0u;
+        }
+    }
 }
 
-// Radix select, pass p (0 = top digit).  While the passes run, state[t].c holds
-// the digits decided so far (lower digits zero) and state[t].e what is still to
-// be found among the rows that match them.
-__global__ __launch_bounds__(kWG) void sel_hist_kernel(
-    uint32_t *const *__restrict__ counts, int64_t R, const SelState *__restrict__ state,
-    int pass, uint32_t *__restrict__ hist)
+__global__ void sel_init_kernel(SelState *state, int T, uint32_t c, uint32_t e, int width,
+                                uint32_t *__restrict__ zero, int64_t n_zero)
 {
-    __shared__ uint32_t s_hist[256];
-    const int t = blockIdx.y;
-    s_hist[threadIdx.x] = 0;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < T) state[i] = SelState{c, e, width, 0u};
+    if (i < n_zero) zero[i] = 0u;
+}
+
+// Bin of a count in the first pass, and back: the bin's smallest count and the logarithm of
+// how many counts it holds.
+__device__ __forceinline__ uint32_t first_bin(uint32_t v)
+{
+    if (v < kExact) return v;
+    const int o = 31 - __clz((int)v);
+    return kExact + ((uint32_t)(o - kExactBits) << kSubBits) +
+           ((v >> (o - kSubBits)) & ((1u << kSubBits) - 1u));
+}
+__device__ __forceinline__ void first_bin_range(uint32_t bin, uint32_t &lo, int &width)
+{
+    lo = bin;
+    width = 0;
+    if (bin >= kExact) {
+        const uint32_t k = bin - kExact;
+        const int o = kExactBits + (int)(k >> kSubBits);
+        width = o - kSubBits;
+        lo = ((1u << kSubBits) + (k & ((1u << kSubBits) - 1u))) << width;
+    }
+}
+
+// One histogram pass.  FIRST: all counts, the bins above; else the counts of the range that
+// the passes before have left, by the next ten bits.  The last workgroup of a table to add
+// its bins picks the one with  #(rows in bins above) < e <= #(rows in it or above)  and
+// clears the histogram for the next pass.  A table has few workgroups: all of them add to
+// the bins of the smallest counts, and memory takes adds to one address one after the other
+// (0.14 us each).
+template <bool FIRST>
+__device__ __forceinline__ void sel_hist_pass(gptr<const uint32_t> cg, int64_t R, SelState &st,
+                                              uint32_t *__restrict__ ht,
+                                              uint32_t *__restrict__ done, uint32_t *s_hist)
+{
+    constexpr int NT = kHistThreads, NB = FIRST ? kBins : (int)kExact, PER = (NB + NT - 1) / NT;
+    __shared__ uint32_t s_part[NT / 64];
+    __shared__ bool s_last;
+    __shared__ SelState s_state;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int shift = st.width > kExactBits ? st.width - kExactBits : 0;
+    for (int i = tid; i < NB; i += NT) s_hist[i] = 0;
     __syncthreads();
-    const int shift = 24 - 8 * pass;
-    const uint32_t prefix = state[t].c;
-    const auto cg = as_global((const uint32_t *)counts[t]);
-    const int64_t base = (int64_t)blockIdx.x * kSelRows;
-    const int lane = threadIdx.x & 63;
-#pragma unroll 4
-    for (int k = 0; k < kSelSteps; ++k) {
-        const int64_t r = base + k * kWG + threadIdx.x;
-        uint32_t c = 0;
-        if (r < R) c = cg[r];
-        // rows whose higher digits differ from the prefix are out of the race
-        const bool in = r < R && (pass == 0 || (c >> (shift + 8)) == (prefix >> (shift + 8)));
-        const uint32_t d = (c >> shift) & 255u;
-        // Counters are mostly small, so most lanes of a wavefront share a digit:
-        // the first lane in the race adds for all that agree with it.
-        const unsigned long long racing = __ballot(in);
-        if (racing) {
-            const int lead = __ffsll((long long)racing) - 1;
-            const uint32_t d_lead = __shfl(d, lead);
-            const unsigned long long same = __ballot(in && d == d_lead);
-            if (lane == lead) atomicAdd(&s_hist[d_lead], (uint32_t)__popcll(same));
-            if (in && d != d_lead) atomicAdd(&s_hist[d], 1u);
+    // most counters are 0 or 1: those are counted in registers
+    uint32_t few[2] = {0, 0};
+    const int64_t stride = (int64_t)gridDim.x * kHistStep;
+    for (int64_t r0 = (int64_t)blockIdx.x * kHistStep + tid * 4; r0 < R; r0 += 4 * stride) {
+        uint32_t c[4][4];
+        bool in[4][4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) load4(cg, r0 + k * stride, R, c[k], in[k]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t v = c[k][j];
+                if (FIRST) {
+                    few[0] += in[k][j] && v == 0u;
+                    few[1] += v == 1u;
+                    if (v > 1u) atomicAdd(&s_hist[first_bin(v)], 1u);
+                } else if (in[k][j] && ((v - st.c) >> st.width) == 0u) {
+                    atomicAdd(&s_hist[(v - st.c) >> shift], 1u);
+                }
+            }
+    }
+    if (FIRST) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            for (int off = 32; off; off >>= 1) few[q] += __shfl_xor(few[q], off);
+            if (lane == 0 && few[q]) atomicAdd(&s_hist[q], few[q]);
         }
     }
     __syncthreads();
-    const uint32_t v = s_hist[threadIdx.x];
-    if (v) atomicAdd(&hist[((int64_t)t * 4 + pass) * 256 + threadIdx.x], v);
-}
-
-// Largest digit d with  #(rows above d) < e <= #(rows at or above d): every
-// thread owns a digit, the counts above it come from a suffix scan in LDS, and
-// the one thread whose digit satisfies the condition writes the state.
-__global__ __launch_bounds__(256) void sel_pick_kernel(SelState *__restrict__ state,
-                                                        int pass,
-                                                        const uint32_t *__restrict__ hist)
-{
-    __shared__ uint32_t s_suf[256];
-    const int t = blockIdx.x, d = threadIdx.x;
-    const uint32_t h = hist[((int64_t)t * 4 + pass) * 256 + d];
-    const SelState st = state[t];
-    s_suf[d] = h;
-    __syncthreads();
-    // inclusive suffix sums: s_suf[d] = sum of h over digits >= d
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t add = d + off < 256 ? s_suf[d + off] : 0u;
+    if (gridDim.x > 1) {
+        for (int i = tid; i < NB; i += NT)
+            if (s_hist[i]) atomicAdd(&ht[i], s_hist[i]);
+        // This workgroup's adds are done before it says so.  (They are device-scope and leave
+        // nothing behind in a cache; a fence would write the XCD's L2 back, once per wavefront:
+        // 181 instead of 32 us for the whole kernel at 26 x 1 M rows.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        s_suf[d] += add;
+        if (tid == 0) s_last = atomicAdd(done, 1u) == gridDim.x - 1;
         __syncthreads();
+        if (!s_last) return;
     }
-    const uint32_t at_or_above = s_suf[d], above = at_or_above - h;
-    // e >= 1 and the rows still in the race number at least e, so exactly one digit
-    // qualifies (and it is present: h > 0)
-    if (above < st.e && st.e <= at_or_above)
-        state[t] = SelState{st.c | ((uint32_t)d << (24 - 8 * pass)), st.e - above};
-}
 
-// Wavefront w of the workgroup takes rows base + (k * 4 + w) * 64 + lane in step
-// k; `gt` and `eq` are the ballots of that step.
-__device__ __forceinline__ void sel_ballots(gptr<const uint32_t> cg, int64_t R, int64_t row,
-                                            SelState st, unsigned long long &gt,
-                                            unsigned long long &eq)
-{
-    uint32_t c = 0;
-    const bool in = row < R;
-    if (in) c = cg[row];
-    gt = __ballot(in && c > st.c);
-    eq = __ballot(in && c == st.c);
-}
-
-__global__ __launch_bounds__(kWG) void sel_count_kernel(
-    uint32_t *const *__restrict__ counts, int64_t R, const SelState *__restrict__ state,
-    uint2 *__restrict__ block_counts, int nb)
-{
-    __shared__ uint32_t s_gt, s_eq;
-    const int t = blockIdx.y;
-    if (threadIdx.x == 0) s_gt = s_eq = 0;
+    // thread i owns bins [i * PER, (i + 1) * PER); rows above them from a suffix sum
+    uint32_t h[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int bin = tid * PER + q;
+        h[q] = bin >= NB ? 0u
+               : gridDim.x > 1
+                   ? __hip_atomic_load(&ht[bin], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                   : s_hist[bin];
+        sum += h[q];
+    }
+    if (gridDim.x > 1)
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (tid * PER + q < NB) ht[tid * PER + q] = 0u;
+    uint32_t incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t up = __shfl_down(incl, off);
+        if (lane + off < 64) incl += up;
+    }
+    if (lane == 0) s_part[wave] = incl;
     __syncthreads();
+    uint32_t above = incl - sum;
+    for (int w = wave + 1; w < NT / 64; ++w) above += s_part[w];
+    // e >= 1 and the rows still in the race number at least e, so exactly one bin qualifies
+#pragma unroll
+    for (int q = PER - 1; q >= 0; --q) {
+        if (above < st.e && st.e <= above + h[q]) {
+            const uint32_t bin = (uint32_t)(tid * PER + q);
+            uint32_t lo = st.c + (bin << shift);
+            int width = shift;
+            if (FIRST) first_bin_range(bin, lo, width);
+            s_state = SelState{lo, st.e - above, width, 0u};
+        }
+        above += h[q];
+    }
+    __syncthreads();
+    st = s_state;
+}
+
+__global__ __launch_bounds__(kHistThreads) void sel_hist_kernel(
+    uint32_t *const *__restrict__ counts, int64_t R, SelState *__restrict__ state,
+    uint32_t *__restrict__ hist, uint32_t *__restrict__ done, int pass)
+{
+    __shared__ uint32_t s_hist[kBins];
+    const int t = blockIdx.y;
+    SelState st = state[t];
+    if (st.width == 0) return;
+    const auto cg = as_global((const uint32_t *)counts[t]);
+    const int width = st.width;
+    if (pass == 0)
+        sel_hist_pass<true>(cg, R, st, hist + (int64_t)t * kBins, done + t * (kRefine + 1), s_hist);
+    else
+        sel_hist_pass<false>(cg, R, st, hist + (int64_t)t * kBins,
+                             done + t * (kRefine + 1) + pass, s_hist);
+    if (gridDim.x == 1)                    // a table of one workgroup needs no launch per pass
+        while (st.width > 0) {
+            __syncthreads();
+            sel_hist_pass<false>(cg, R, st, nullptr, nullptr, s_hist);
+        }
+    if (st.width < width && threadIdx.x == 0) state[t] = st;       // the workgroup that picked
+}
+
+// Bitmaps of "count > c" and "count == c" over 4096 rows, and how many bits each has there.
+__global__ __launch_bounds__(kWG) void sel_mark_kernel(
+    uint32_t *const *__restrict__ counts, int64_t R, const SelState *__restrict__ state,
+    uint32_t *__restrict__ gt_bits, uint32_t *__restrict__ eq_bits, int nb,
+    uint2 *__restrict__ block_totals)
+{
+    __shared__ uint32_t s_gt[kWG / 64], s_eq[kWG / 64];
+    const int t = blockIdx.y, blk = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const SelState st = state[t];
     const auto cg = as_global((const uint32_t *)counts[t]);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t base = (int64_t)blockIdx.x * kSelRows;
+    constexpr int K = kBlockRows / (kWG * 4);
+    uint32_t c[K][4];
+    bool in[K][4];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        load4(cg, (int64_t)blk * kBlockRows + (k * kWG + tid) * 4, R, c[k], in[k]);
+    const int64_t w0 = ((int64_t)t * nb + blk) * kBlockWords;
     uint32_t n_gt = 0, n_eq = 0;
-#pragma unroll 4
-    for (int k = 0; k < kSelSteps; ++k) {
-        unsigned long long gt, eq;
-        sel_ballots(cg, R, base + (k * 4 + wave) * 64 + lane, st, gt, eq);
-        n_gt += (uint32_t)__popcll(gt);
-        n_eq += (uint32_t)__popcll(eq);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        uint32_t gt = 0, eq = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            gt |= (in[k][j] && c[k][j] > st.c ? 1u : 0u) << j;
+            eq |= (in[k][j] && c[k][j] == st.c ? 1u : 0u) << j;
+        }
+        n_gt += __popc(gt);
+        n_eq += __popc(eq);
+        // eight lanes hold the 32 rows of a word
+        gt <<= 4 * (lane & 7);
+        eq <<= 4 * (lane & 7);
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) {
+            gt |= __shfl_xor(gt, off);
+            eq |= __shfl_xor(eq, off);
+        }
+        if ((lane & 7) == 0) {
+            gt_bits[w0 + (k * kWG + tid) / 8] = gt;
+            eq_bits[w0 + (k * kWG + tid) / 8] = eq;
+        }
+    }
+    for (int off = 32; off; off >>= 1) {
+        n_gt += __shfl_xor(n_gt, off);
+        n_eq += __shfl_xor(n_eq, off);
     }
     if (lane == 0) {
-        atomicAdd(&s_gt, n_gt);
-        atomicAdd(&s_eq, n_eq);
+        s_gt[wave] = n_gt;
+        s_eq[wave] = n_eq;
     }
     __syncthreads();
-    if (threadIdx.x == 0) block_counts[(int64_t)t * nb + blockIdx.x] = make_uint2(s_gt, s_eq);
+    if (tid == 0) {
+        n_gt = n_eq = 0;
+        for (int w = 0; w < kWG / 64; ++w) {
+            n_gt += s_gt[w];
+            n_eq += s_eq[w];
+        }
+        block_totals[(int64_t)t * nb + blk] = make_uint2(n_gt, n_eq);
+    }
 }
 
-// Exclusive scan of the block totals of one table; n_hot = what the write step
-// will emit (before any cap).  Each thread owns a contiguous piece of the
-// blocks; the 256 piece totals are scanned with wavefront shuffles.
-__global__ __launch_bounds__(kWG) void sel_scan_kernel(
-    const uint2 *__restrict__ block_counts, uint2 *__restrict__ block_before, int nb,
-    const SelState *__restrict__ state, uint32_t *__restrict__ n_hot)
+// Totals of kSuper blocks each, for tables of so many blocks that the last step's workgroups
+// should not each add up all blocks before theirs.
+__global__ __launch_bounds__(64) void sel_super_kernel(const uint2 *__restrict__ block_totals,
+                                                       int nb, uint2 *__restrict__ super_totals,
+                                                       int ns)
 {
-    __shared__ uint32_t s_wgt[4], s_weq[4];
-    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (nb + kWG - 1) / kWG;
-    const int b0 = tid * per, b1 = b0 + per < nb ? b0 + per : nb;
-    const uint2 *__restrict__ bc = block_counts + (int64_t)t * nb;
-    uint2 *__restrict__ bb = block_before + (int64_t)t * nb;
-    uint32_t gt = 0, eq = 0;
-    for (int b = b0; b < b1; ++b) {
-        gt += bc[b].x;
-        eq += bc[b].y;
+    const int t = blockIdx.y, b = blockIdx.x * kSuper + threadIdx.x;
+    uint2 v = make_uint2(0u, 0u);
+    if (b < nb) v = block_totals[(int64_t)t * nb + b];
+    for (int off = 32; off; off >>= 1) {
+        v.x += __shfl_xor(v.x, off);
+        v.y += __shfl_xor(v.y, off);
     }
-    uint32_t inc_gt = gt, inc_eq = eq;                  // inclusive within the wavefront
+    if (threadIdx.x == 0) super_totals[(int64_t)t * ns + blockIdx.x] = v;
+}
+
+// Sum over all threads of the workgroup, for every thread.
+__device__ __forceinline__ uint2 wg_sum(uint2 v, uint32_t (&s_x)[kWG / 64],
+                                        uint32_t (&s_y)[kWG / 64])
+{
+    for (int off = 32; off; off >>= 1) {
+        v.x += __shfl_xor(v.x, off);
+        v.y += __shfl_xor(v.y, off);
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        s_x[threadIdx.x >> 6] = v.x;
+        s_y[threadIdx.x >> 6] = v.y;
+    }
+    __syncthreads();
+    v = make_uint2(0u, 0u);
+    for (int w = 0; w < kWG / 64; ++w) {
+        v.x += s_x[w];
+        v.y += s_y[w];
+    }
+    return v;
+}
+
+// Ids and bitmap of kWriteBlocks blocks, four bitmap words per thread.
+__global__ __launch_bounds__(kWG) void sel_write_kernel(
+    const SelState *__restrict__ state, int64_t R, const uint32_t *__restrict__ gt_bits,
+    const uint32_t *__restrict__ eq_bits, int nb, const uint2 *__restrict__ block_totals,
+    const uint2 *__restrict__ super_totals, int ns, int32_t *const *__restrict__ hot_ids,
+    int cap, uint32_t *const *__restrict__ hot_bits, uint32_t *__restrict__ n_hot)
+{
+    static_assert(kWriteBlocks * kBlockWords == kWG * 4 && kSuper % kWriteBlocks == 0, "");
+    __shared__ uint32_t s_x[kWG / 64], s_y[kWG / 64];
+    const int t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int blk0 = blockIdx.x * kWriteBlocks;          // first block of this workgroup
+    const int word0 = blk0 * kBlockWords + tid * 4;      // first word of this thread
+    uint4 gt = make_uint4(0, 0, 0, 0), eq = gt;
+    if (word0 < nb * kBlockWords) {
+        const int64_t w = (int64_t)t * nb * kBlockWords + word0;
+        gt = *reinterpret_cast<const uint4 *>(gt_bits + w);
+        eq = *reinterpret_cast<const uint4 *>(eq_bits + w);
+    }
+    const uint32_t e = state[t].e;
+    // bits before this workgroup's: whole groups of blocks where there are such totals, and
+    // blocks
+    const uint2 *__restrict__ st = super_totals + (int64_t)t * ns;
+    const uint2 *__restrict__ bt = block_totals + (int64_t)t * nb;
+    const int sup = ns ? blk0 / kSuper : 0;
+    uint2 v = make_uint2(0u, 0u);
+    for (int i = tid; i < sup; i += kWG) {
+        v.x += st[i].x;
+        v.y += st[i].y;
+    }
+    for (int i = sup * kSuper + tid; i < blk0; i += kWG) {
+        v.x += bt[i].x;
+        v.y += bt[i].y;
+    }
+    const uint2 before = wg_sum(v, s_x, s_y);
+    if (n_hot && blockIdx.x == 0) {
+        v = make_uint2(0u, 0u);
+        for (int i = tid; i < (ns ? ns : nb); i += kWG) {
+            const uint2 x = ns ? st[i] : bt[i];
+            v.x += x.x;
+            v.y += x.y;
+        }
+        v = wg_sum(v, s_x, s_y);
+        if (tid == 0) n_hot[t] = v.x + (v.y < e ? v.y : e);
+    }
+    // ... then those of the threads before this one
+    uint32_t g[4] = {gt.x, gt.y, gt.z, gt.w}, q[4] = {eq.x, eq.y, eq.z, eq.w};
+    uint32_t n_gt = 0, n_eq = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        n_gt += __popc(g[k]);
+        n_eq += __popc(q[k]);
+    }
+    uint32_t inc_gt = n_gt, inc_eq = n_eq;
     for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t a = __shfl_up(inc_gt, off), c = __shfl_up(inc_eq, off);
+        const uint32_t a = __shfl_up(inc_gt, off), b = __shfl_up(inc_eq, off);
         if (lane >= off) {
             inc_gt += a;
-            inc_eq += c;
+            inc_eq += b;
         }
     }
+    __syncthreads();
     if (lane == 63) {
-        s_wgt[wave] = inc_gt;
-        s_weq[wave] = inc_eq;
+        s_x[wave] = inc_gt;
+        s_y[wave] = inc_eq;
     }
     __syncthreads();
-    uint32_t run_gt = inc_gt - gt, run_eq = inc_eq - eq, tot_gt = 0, tot_eq = 0;
-    for (int w = 0; w < 4; ++w) {
-        if (w < wave) {
-            run_gt += s_wgt[w];
-            run_eq += s_weq[w];
-        }
-        tot_gt += s_wgt[w];
-        tot_eq += s_weq[w];
+    uint32_t gb = before.x + inc_gt - n_gt, qb = before.y + inc_eq - n_eq;
+    for (int w = 0; w < wave; ++w) {
+        gb += s_x[w];
+        qb += s_y[w];
     }
-    for (int b = b0; b < b1; ++b) {
-        const uint2 v = bc[b];
-        bb[b] = make_uint2(run_gt, run_eq);
-        run_gt += v.x;
-        run_eq += v.y;
-    }
-    if (tid == 0 && n_hot) {
-        const uint32_t e = state[t].e;
-        n_hot[t] = tot_gt + (tot_eq < e ? tot_eq : e);
-    }
-}
-
-__global__ __launch_bounds__(kWG) void sel_write_kernel(
-    uint32_t *const *__restrict__ counts, int64_t R, const SelState *__restrict__ state,
-    const uint2 *__restrict__ block_before, int nb, int32_t *const *__restrict__ hot_ids,
-    int cap, uint32_t *const *__restrict__ hot_bits)
-{
-    // totals of every (step, wavefront) cell, then their exclusive prefix in row order
-    __shared__ uint32_t s_gt[kSelSteps * 4], s_eq[kSelSteps * 4];
-    const int t = blockIdx.y;
-    const SelState st = state[t];
-    const auto cg = as_global((const uint32_t *)counts[t]);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t base = (int64_t)blockIdx.x * kSelRows;
-    unsigned long long gts[kSelSteps], eqs[kSelSteps];
-#pragma unroll
-    for (int k = 0; k < kSelSteps; ++k) {
-        sel_ballots(cg, R, base + (k * 4 + wave) * 64 + lane, st, gts[k], eqs[k]);
-        if (lane == 0) {
-            s_gt[k * 4 + wave] = (uint32_t)__popcll(gts[k]);
-            s_eq[k * 4 + wave] = (uint32_t)__popcll(eqs[k]);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint2 before = block_before[(int64_t)t * nb + blockIdx.x];
-        uint32_t g = before.x, q = before.y;
-        for (int i = 0; i < kSelSteps * 4; ++i) {
-            const uint32_t a = s_gt[i], b = s_eq[i];
-            s_gt[i] = g;
-            s_eq[i] = q;
-            g += a;
-            q += b;
-        }
-    }
-    __syncthreads();
-    const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     int32_t *ids = hot_ids ? hot_ids[t] : nullptr;
     uint32_t *bits = hot_bits ? hot_bits[t] : nullptr;
     const int64_t words = (R + 31) >> 5;
 #pragma unroll
-    for (int k = 0; k < kSelSteps; ++k) {
-        const int64_t row0 = base + (k * 4 + wave) * 64;
-        if (row0 >= R) break;                     // uniform within the wavefront
-        const uint32_t g_before = s_gt[k * 4 + wave] + (uint32_t)__popcll(gts[k] & below);
-        const uint32_t q_before = s_eq[k * 4 + wave] + (uint32_t)__popcll(eqs[k] & below);
-        const bool is_gt = (gts[k] >> lane) & 1ull;
-        const bool is_eq = (eqs[k] >> lane) & 1ull;
-        const bool take = is_gt || (is_eq && q_before < st.e);
-        if (take && ids) {
-            const uint64_t pos = (uint64_t)g_before + (q_before < st.e ? q_before : st.e);
-            if (pos < (uint64_t)cap) ids[pos] = (int32_t)(row0 + lane);
+    for (int k = 0; k < 4; ++k) {
+        uint32_t take = g[k];
+        for (uint32_t left = g[k] | q[k]; left; left &= left - 1u) {
+            const int b = __ffs((int)left) - 1;
+            const bool is_gt = (g[k] >> b) & 1u;
+            if (is_gt || qb < e) {
+                const uint64_t pos = (uint64_t)gb + (qb < e ? qb : e);
+                if (ids && pos < (uint64_t)cap) ids[pos] = (word0 + k) * 32 + b;
+                take |= 1u << b;
+            } else if (g[k] == 0u) {
+                break;                   // no equal row is taken any more, and nothing else is left
+            }
+            gb += is_gt ? 1u : 0u;
+            qb += is_gt ? 0u : 1u;
         }
-        if (bits) {
-            const unsigned long long sel = __ballot(take);
-            const int64_t w0 = row0 >> 5;
-            if (lane == 0) bits[w0] = (uint32_t)sel;
-            if (lane == 1 && w0 + 1 < words) bits[w0 + 1] = (uint32_t)(sel >> 32);
-        }
+        if (bits && word0 + k < words) bits[word0 + k] = take;
     }
 }
 
 struct SelLayout {
-    int nb;
-    size_t hist, state, block_counts, block_before, total;
+    int nb, ns;
+    int64_t n_zero;          // words at the start that begin as zeros
+    size_t hist, done, supers, state, block_totals, gt_bits, eq_bits, total;
 };
 
 SelLayout make_sel_layout(int T, int64_t R)
 {
     SelLayout y;
-    y.nb = (int)((R + kSelRows - 1) / kSelRows);
+    y.nb = (int)((R + kBlockRows - 1) / kBlockRows);
+    y.ns = y.nb > kManyBlocks ? (y.nb + kSuper - 1) / kSuper : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
         off += align_up(bytes, 256);
         return o;
     };
-    y.hist = take((size_t)T * 4 * 256 * sizeof(uint32_t));
+    y.done = take((size_t)T * (kRefine + 1) * sizeof(uint32_t));
+    y.hist = take((size_t)T * kBins * sizeof(uint32_t));
+    y.n_zero = (int64_t)(off / sizeof(uint32_t));
     y.state = take((size_t)T * sizeof(SelState));
-    y.block_counts = take((size_t)T * y.nb * sizeof(uint2));
-    y.block_before = take((size_t)T * y.nb * sizeof(uint2));
+    y.supers = take((size_t)T * y.ns * sizeof(uint2));
+    y.block_totals = take((size_t)T * y.nb * sizeof(uint2));
+    y.gt_bits = take((size_t)T * y.nb * kBlockWords * sizeof(uint32_t));
+    y.eq_bits = take((size_t)T * y.nb * kBlockWords * sizeof(uint32_t));
     y.total = off;
     return y;
-}
-
-void compact(int T, int64_t R, uint32_t *const *counts, const SelLayout &y, char *w8,
-             int32_t *const *hot_ids, int cap, uint32_t *const *hot_bits, uint32_t *n_hot,
-             hipStream_t s)
-{
-    SelState *state = reinterpret_cast<SelState *>(w8 + y.state);
-    uint2 *bc = reinterpret_cast<uint2 *>(w8 + y.block_counts);
-    uint2 *bb = reinterpret_cast<uint2 *>(w8 + y.block_before);
-    launch(sel_count_kernel, dim3(y.nb, T), dim3(kWG), s, counts, R, (const SelState *)state,
-           bc, y.nb);
-    launch(sel_scan_kernel, dim3(T), dim3(kWG), s, (const uint2 *)bc, bb, y.nb,
-           (const SelState *)state, n_hot);
-    ProfScope prof("sel_write_kernel", s);
-    launch(sel_write_kernel, dim3(y.nb, T), dim3(kWG), s, counts, R, (const SelState *)state,
-           (const uint2 *)bb, y.nb, hot_ids, cap, hot_bits);
 }
 
 }  // namespace
@@ -344,12 +505,21 @@ int32_t launch_count_accesses(int T, const int32_t *idx, int Bcap, int L,
                               hipStream_t s)
 {
     const int64_t nnz = (int64_t)Bcap * L;
-    const int64_t chunks = (nnz + kCountChunk - 1) / kCountChunk;
-    if (chunks * T > 0x7fffffffLL)
+    if (nnz == 0) return SS_OK;
+    const auto chunks = [&](int per) { return (nnz + per - 1) / per; };
+    if (chunks(512) * T > 0x7fffffffLL)
         return fail(SS_ERR_UNSUPPORTED, "ss_count_accesses: grid too large");
     ProfScope prof("count_kernel", s);
-    launch(count_kernel, dim3((unsigned)(chunks * T)), dim3(kWG), s, idx, Bcap, L, n_valid,
-           counts, (int)chunks);
+#define SS_COUNT(NT_, I_, SLOTS_)                                                            \
+    launch(count_kernel<NT_, I_, SLOTS_>, dim3((unsigned)(chunks(NT_ * I_) * T)), dim3(NT_), s, \
+           idx, Bcap, L, n_valid, counts, (int)chunks(NT_ * I_))
+    // Rule (us; 256 x 2 / 1024 x 2 / 1024 x 8 lookups per workgroup): 26 tables x 163840 lookups
+    // 85 / 61 / 51, x 40000 21.5 / 17.7 / 15.7, x 20000 11.8 / 9.9 / 10.6; 5 x 60000 8.6 / 6.8 /
+    // 9.0; 26 x 8192 5.9 / 5.8 / 9.6; 1 x 65536 4.8 / 5.5 / 11.4.
+    if (chunks(8192) * T >= 100) SS_COUNT(1024, 8, 8192);
+    else if (chunks(2048) * T >= 128) SS_COUNT(1024, 2, 4096);
+    else SS_COUNT(256, 2, 1024);
+#undef SS_COUNT
     return check_launch("ss_count_accesses");
 }
 
@@ -362,22 +532,37 @@ int32_t launch_select_hot(int T, int64_t R, uint32_t *const *counts, bool top, u
     const SelLayout y = make_sel_layout(T, R);
     char *w8 = static_cast<char *>(ws);
     SelState *state = reinterpret_cast<SelState *>(w8 + y.state);
+    uint32_t *hist = reinterpret_cast<uint32_t *>(w8 + y.hist);
+    uint32_t *done = reinterpret_cast<uint32_t *>(w8 + y.done);
+    uint32_t *gt = reinterpret_cast<uint32_t *>(w8 + y.gt_bits);
+    uint32_t *eq = reinterpret_cast<uint32_t *>(w8 + y.eq_bits);
+    uint2 *blocks = reinterpret_cast<uint2 *>(w8 + y.block_totals);
+    uint2 *supers = reinterpret_cast<uint2 *>(w8 + y.supers);
+    const int64_t n_init = y.n_zero > T ? y.n_zero : T;
     // top-H starts from "nothing decided, e = H still to find"
-    launch(sel_set_state_kernel, dim3((T + 255) / 256), dim3(256), s, state, T, c, e);
+    launch(sel_init_kernel, dim3((unsigned)((n_init + 255) / 256)), dim3(256), s, state, T, c, e,
+           top ? 32 : 0, reinterpret_cast<uint32_t *>(w8), y.n_zero);
     if (top && e > 0) {
-        uint32_t *hist = reinterpret_cast<uint32_t *>(w8 + y.hist);
-        launch_zero_u32(hist, T * 4 * 256, s);
-        for (int pass = 0; pass < 4; ++pass) {
-            {
-                ProfScope prof("sel_hist_kernel", s);
-                launch(sel_hist_kernel, dim3(y.nb, T), dim3(kWG), s, counts, R,
-                       (const SelState *)state, pass, hist);
-            }
-            launch(sel_pick_kernel, dim3(T), dim3(256), s, state, pass,
-                   (const uint32_t *)hist);
-        }
+        int64_t per_table = (R + 4 * kHistStep - 1) / (4 * kHistStep), most = 1024 / T;
+        most = most < 1 ? 1 : most > 256 ? 256 : most;
+        if (per_table > most) per_table = most;
+        const dim3 grid((unsigned)per_table, T);
+        ProfScope prof("sel_hist_kernel", s);
+        for (int pass = 0; pass <= (per_table > 1 ? kRefine : 0); ++pass)
+            launch(sel_hist_kernel, grid, dim3(kHistThreads), s, counts, R, state, hist, done, pass);
     }
-    compact(T, R, counts, y, w8, hot_ids, cap, hot_bits, n_hot, s);
+    {
+        ProfScope prof("sel_mark_kernel", s);
+        launch(sel_mark_kernel, dim3(y.nb, T), dim3(kWG), s, counts, R, (const SelState *)state,
+               gt, eq, y.nb, blocks);
+    }
+    if (y.ns)
+        launch(sel_super_kernel, dim3(y.ns, T), dim3(64), s, (const uint2 *)blocks, y.nb, supers,
+               y.ns);
+    ProfScope prof("sel_write_kernel", s);
+    launch(sel_write_kernel, dim3((y.nb + kWriteBlocks - 1) / kWriteBlocks, T), dim3(kWG), s,
+           (const SelState *)state, R, (const uint32_t *)gt, (const uint32_t *)eq, y.nb,
+           (const uint2 *)blocks, (const uint2 *)supers, y.ns, hot_ids, cap, hot_bits, n_hot);
     return check_launch("ss_select_hot");
 }
 
