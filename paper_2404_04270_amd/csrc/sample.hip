@@ -8,99 +8,140 @@
 // up, so a pass costs 8 bytes per lookup whatever the row length, and up to 32
 // thresholds share that pass.
 //
-// G lanes share one sampled input and split its T*L lookups between them.  A
-// lookup maps its row to a hot slot by a branch-free lower-bound search in the
-// ascending hot_ids of its table; a lane runs up to four such searches
-// interleaved, since each step is one dependent load that only latency
-// bounds.  Per-threshold stale-lookup counts are summed over the group with
-// wavefront shuffles, turned into verdicts by the group's first lane, counted
-// per wavefront with ballots, per workgroup in LDS and once per workgroup in
-// global memory.
+// The thresholds are sorted on the host, so a lookup's drift falls into one class: the
+// first threshold it does not exceed.  An input can be dropped from the alpha-th smallest
+// class of its lookups on, so one number per input replaces a count per threshold.
+//
+// A workgroup takes 64 inputs, one per lane, and its wavefronts split the T * L lookups of
+// an input between them.  A lookup maps its row to a hot slot by a branch-free lower-bound
+// search in the ascending hot_ids of its table; a lane runs up to four such searches
+// interleaved, since each step is one dependent load that only latency bounds.  All lanes
+// of a wavefront search the same table: its popular rows and the first steps of every
+// search are the same few cache lines, and the lines that the loads bring to the compute
+// unit are what bounds the kernel (with neighbouring lanes in different tables, nearly as
+// many lines as lanes: 51.4 us for 65536 inputs of 26 lookups, 5000 hot rows per table and
+// 32 thresholds, 24.6 now; 84 and 40 with the hot rows scattered over the table).  Classes are counted per input in LDS, inputs per class in LDS, and each workgroup
+// adds its share to the counts at the end.
+#include <math.h>
+
 #include "ss_common.h"
 
 namespace ss {
 
-// Thresholds as the kernel compares them: widened to fp64 on the host, and -1
-// where no row may be stale (threshold 0 or an unused slot), since a drift is
-// never below 0.  They arrive as kernel arguments and stay in scalar registers.
+// Thresholds in ascending order as the kernel compares them: widened to fp64 on the host, -1
+// where no row may be stale (threshold 0), since a drift is never below 0, and +inf in unused
+// slots at the end; and which of the caller's thresholds each one is.
 struct Ladder {
     double thr[SS_MAX_THRESHOLDS];
+    uint8_t slot[SS_MAX_THRESHOLDS];
 };
 
-constexpr int kBatch = 4;     // searches a lane keeps in flight
+constexpr int kBatch = 4;        // searches a lane keeps in flight
+constexpr int kInputs = 64;      // inputs per workgroup and round
+constexpr int kMaxWaves = 8;
+constexpr unsigned kMaxGroups = 1024;     // what fits the chip at once; more would only add more to the counts
 
-template <int G>
-__global__ __launch_bounds__(kWG) void sample_drop_kernel(
+typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
     const int32_t *const *__restrict__ hot_ids, int H,
     const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
     int L, int TL, int alpha, Ladder ladder, int n_thr, uint32_t *__restrict__ counts)
 {
-    __shared__ uint32_t s_cnt[SS_MAX_THRESHOLDS];
-    if (threadIdx.x < SS_MAX_THRESHOLDS) s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-
-    constexpr int GROUPS = kWG / G;
-    const int g = threadIdx.x / G, c = threadIdx.x % G;
-    const int s = blockIdx.x * GROUPS + g;
-    const bool valid = s < S;
-
-    uint32_t cnt[SS_MAX_THRESHOLDS];
-#pragma unroll
-    for (int k = 0; k < SS_MAX_THRESHOLDS; ++k) cnt[k] = 0;
-
-    if (valid && H > 0) {
-        for (int q0 = c; q0 < TL; q0 += G * kBatch) {
+    constexpr int K = SS_MAX_THRESHOLDS;
+    static_assert(K == 32, "the class search takes five steps");
+    __shared__ double s_thr[K];
+    __shared__ uint32_t s_cnt[K][kInputs];      // lookups per class and input
+    __shared__ uint32_t s_inputs[K];            // inputs that can be dropped from class k on
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
+    if (tid < K) {
+        s_thr[tid] = ladder.thr[tid];
+        s_inputs[tid] = 0;
+    }
+    for (int s0 = blockIdx.x * kInputs; s0 < S; s0 += gridDim.x * kInputs) {
+        const int s = s0 + lane < S ? s0 + lane : S - 1;      // lanes past the last: not counted
+        for (int i = tid; i < K * kInputs; i += blockDim.x) (&s_cnt[0][0])[i] = 0;
+        __syncthreads();
+        for (int q0 = wave; q0 < TL && H > 0; q0 += waves * kBatch) {
             int32_t row[kBatch];
             int base[kBatch];
             gptr<const int32_t> ids[kBatch];
             gptr<const double> dr[kBatch];
-            bool live[kBatch];
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) {
-                const int q = q0 + i * G;
-                live[i] = q < TL;
-                const int qq = live[i] ? q : c;         // c < TL whenever q0 < TL
-                const int t = qq / L, l = qq - t * L;
+                const int q = q0 + i * waves < TL ? q0 + i * waves : q0;
+                const int t = q / L, l = q - t * L;
                 row[i] = sidx[((int64_t)t * S + s) * L + l];
                 ids[i] = as_global(hot_ids[t]);
                 dr[i] = as_global(drift[t]);
                 base[i] = 0;
             }
-            // lower bound: the last slot whose id is <= row (slot 0 if none is)
-            for (int n = H; n > 1;) {
+            // lower bound: the last slot whose id is <= row (slot 0 if none is), down to four
+            // candidates, which one load fetches
+            for (int n = H; n > 4;) {
                 const int half = n >> 1;
 #pragma unroll
                 for (int i = 0; i < kBatch; ++i)
                     if (ids[i][base[i] + half] <= row[i]) base[i] += half;
                 n -= half;
             }
+            bool found[kBatch];
+            double d[kBatch];
+            if (H >= 4) {
+                i4 four[kBatch];
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const bool hot = live[i] && ids[i][base[i]] == row[i];
-                const double d = dr[i][base[i]];
+                for (int i = 0; i < kBatch; ++i) {
+                    base[i] = base[i] <= H - 4 ? base[i] : H - 4;
+                    four[i] = *(gptr<const i4>)(ids[i] + base[i]);
+                }
 #pragma unroll
-                for (int k = 0; k < SS_MAX_THRESHOLDS; ++k) {
-                    // same verdict as ss_detect_stale; a NaN drift compares false
-                    const bool stale = hot && d <= ladder.thr[k];
-                    cnt[k] += stale ? 1u : 0u;
+                for (int i = 0; i < kBatch; ++i) {
+                    found[i] = four[i].x == row[i] || four[i].y == row[i] || four[i].z == row[i] ||
+                               four[i].w == row[i];
+                    base[i] += four[i].w <= row[i] ? 3 : four[i].z <= row[i] ? 2
+                               : four[i].y <= row[i] ? 1 : 0;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    for (int h = 1; h < H; ++h)
+                        if (ids[i][h] <= row[i]) base[i] = h;
+                    found[i] = ids[i][base[i]] == row[i];
                 }
             }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) d[i] = dr[i][base[i]];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                // first threshold that the drift does not exceed: same verdict as
+                // ss_detect_stale; a NaN drift exceeds all of them
+                int k = 0;
+#pragma unroll
+                for (int half = K / 2; half > 0; half >>= 1)
+                    k += d[i] <= s_thr[k + half - 1] ? 0 : half;
+                if (q0 + i * waves < TL && found[i] && d[i] <= s_thr[k])
+                    atomicAdd(&s_cnt[k][lane], 1u);
+            }
         }
-    }
-
-    const int lane = threadIdx.x & 63;
+        __syncthreads();
+        if (wave == 0 && s0 + lane < S) {
+            int64_t below = 0;
+            int first = K;
 #pragma unroll
-    for (int k = 0; k < SS_MAX_THRESHOLDS; ++k) {
-        uint32_t v = cnt[k];
-#pragma unroll
-        for (int off = G / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, G);
-        const bool drop = valid && c == 0 && k < n_thr && (int64_t)v >= (int64_t)alpha;
-        const unsigned long long bal = __ballot(drop);
-        if (lane == 0 && bal) atomicAdd(&s_cnt[k], (uint32_t)__popcll(bal));
+            for (int k = 0; k < K; ++k) {
+                below += s_cnt[k][lane];
+                first = first == K && below >= alpha ? k : first;
+            }
+            if (first < K) atomicAdd(&s_inputs[first], 1u);
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    if ((int)threadIdx.x < n_thr && s_cnt[threadIdx.x])
-        atomicAdd(&counts[threadIdx.x], s_cnt[threadIdx.x]);
+    if (tid < n_thr) {
+        uint32_t c = 0;
+        for (int k = 0; k <= tid; ++k) c += s_inputs[k];
+        if (c) atomicAdd(&counts[ladder.slot[tid]], c);
+    }
 }
 
 int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const *drift,
@@ -111,18 +152,29 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
     launch_zero_u32(counts, n_thr, s);
     if (S > 0) {
         Ladder ladder;
-        for (int k = 0; k < SS_MAX_THRESHOLDS; ++k)
-            ladder.thr[k] = k < n_thr && thresholds[k] > 0.0f ? (double)thresholds[k] : -1.0;
+        for (int k = 0; k < SS_MAX_THRESHOLDS; ++k) {
+            ladder.thr[k] = INFINITY;
+            ladder.slot[k] = 0;
+        }
+        for (int k = 0; k < n_thr; ++k) {         // insertion sort
+            const double thr = thresholds[k] > 0.0f ? (double)thresholds[k] : -1.0;
+            int i = k;
+            for (; i > 0 && ladder.thr[i - 1] > thr; --i) {
+                ladder.thr[i] = ladder.thr[i - 1];
+                ladder.slot[i] = ladder.slot[i - 1];
+            }
+            ladder.thr[i] = thr;
+            ladder.slot[i] = (uint8_t)k;
+        }
         const int TL = T * L;
-        int g = 1;
-        while (g < 64 && g * kBatch < TL) g <<= 1;
-        const int groups = kWG / g;
-        const unsigned grid = (unsigned)(((int64_t)S + groups - 1) / groups);
+        int waves = (TL + kBatch - 1) / kBatch;
+        if (waves > kMaxWaves) waves = kMaxWaves;
+        unsigned grid = (unsigned)(((int64_t)S + kInputs - 1) / kInputs);
+        if (grid > kMaxGroups) grid = kMaxGroups;
         ProfScope prof("sample_drop_kernel", s);
-        SS_DISPATCH_G(g, launch(sample_drop_kernel<G>, dim3(grid), dim3(kWG), s,
-                                (const int32_t *const *)hot_ids, H,
-                                (const double *const *)drift, sidx, S, L, TL, alpha,
-                                ladder, n_thr, counts));
+        launch(sample_drop_kernel, dim3(grid), dim3(64 * waves), s,
+               (const int32_t *const *)hot_ids, H, (const double *const *)drift, sidx, S, L, TL,
+               alpha, ladder, n_thr, counts);
     }
     return check_launch("ss_sample_drop");
 }
