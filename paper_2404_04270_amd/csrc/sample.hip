@@ -39,9 +39,93 @@ struct Ladder {
 constexpr int kBatch = 4;        // searches a lane keeps in flight
 constexpr int kInputs = 64;      // inputs per workgroup and round
 constexpr int kMaxWaves = 8;
-constexpr unsigned kMaxGroups = 1024;     // what fits the chip at once; more would only add more to the counts
+// More workgroups only add more to the few words of the counts (us for 65536 inputs of 26
+// lookups / 44414 of 12 / 190000 of 2, at 256, 512, 1024 and 2048 workgroups: 31.8 / 17.3 / 17.8,
+// 24.8 / 15.6 / 16.5, 25.0 / 15.8 / 18.8, 25.0 / 16.3 / 18.8).
+constexpr int64_t kMaxGroups = 512;
 
 typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Classes of kBatch lookups of input s: q0, q0 + step, ... of its TL (those at TL or beyond:
+// none).  The class of a lookup is the first threshold its row's drift does not exceed, K where
+// there is none or the row is not hot.
+__device__ __forceinline__ void lookup_classes(
+    const int32_t *const *__restrict__ hot_ids, int H, const double *const *__restrict__ drift,
+    const int32_t *__restrict__ sidx, int S, int L, int TL, int s, int q0, int step,
+    const double *s_thr, int (&cls)[kBatch])
+{
+    constexpr int K = SS_MAX_THRESHOLDS;
+    static_assert(K == 32, "the class search takes five steps");
+    double d[kBatch];
+    int32_t row[kBatch];
+    int base[kBatch];
+    gptr<const int32_t> ids[kBatch];
+    gptr<const double> dr[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+        const int q = q0 + i * step < TL ? q0 + i * step : q0;
+        const int t = q / L, l = q - t * L;
+        row[i] = sidx[((int64_t)t * S + s) * L + l];
+        ids[i] = as_global(hot_ids[t]);
+        dr[i] = as_global(drift[t]);
+        base[i] = 0;
+    }
+    // lower bound: the last slot whose id is <= row (slot 0 if none is), down to four
+    // candidates, which one load fetches
+    for (int n = H; n > 4;) {
+        const int half = n >> 1;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+            if (ids[i][base[i] + half] <= row[i]) base[i] += half;
+        n -= half;
+    }
+    bool found[kBatch];
+    if (H >= 4) {
+        i4 four[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            base[i] = base[i] <= H - 4 ? base[i] : H - 4;
+            four[i] = *(gptr<const i4>)(ids[i] + base[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            found[i] = four[i].x == row[i] || four[i].y == row[i] || four[i].z == row[i] ||
+                       four[i].w == row[i];
+            base[i] += four[i].w <= row[i] ? 3 : four[i].z <= row[i] ? 2
+                       : four[i].y <= row[i] ? 1 : 0;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            for (int h = 1; h < H; ++h)
+                if (ids[i][h] <= row[i]) base[i] = h;
+            found[i] = ids[i][base[i]] == row[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) d[i] = dr[i][base[i]];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+        // same verdict as ss_detect_stale; a NaN drift exceeds all thresholds
+        int k = 0;
+#pragma unroll
+        for (int half = K / 2; half > 0; half >>= 1) k += d[i] <= s_thr[k + half - 1] ? 0 : half;
+        cls[i] = q0 + i * step < TL && found[i] && d[i] <= s_thr[k] ? k : K;
+    }
+}
+
+// Adds the workgroup's inputs per class to the counts: threshold k drops those of classes 0 .. k.
+// Few workgroups: all of them add to the same few words of memory, one after the other.
+__device__ __forceinline__ void add_counts(const uint32_t *s_inputs, const Ladder &ladder,
+                                           int n_thr, uint32_t *__restrict__ counts)
+{
+    const int tid = threadIdx.x;
+    if (tid < n_thr) {
+        uint32_t c = 0;
+        for (int k = 0; k <= tid; ++k) c += s_inputs[k];
+        if (c) atomicAdd(&counts[ladder.slot[tid]], c);
+    }
+}
 
 __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
     const int32_t *const *__restrict__ hot_ids, int H,
@@ -49,7 +133,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
     int L, int TL, int alpha, Ladder ladder, int n_thr, uint32_t *__restrict__ counts)
 {
     constexpr int K = SS_MAX_THRESHOLDS;
-    static_assert(K == 32, "the class search takes five steps");
     __shared__ double s_thr[K];
     __shared__ uint32_t s_cnt[K][kInputs];      // lookups per class and input
     __shared__ uint32_t s_inputs[K];            // inputs that can be dropped from class k on
@@ -59,70 +142,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
         s_thr[tid] = ladder.thr[tid];
         s_inputs[tid] = 0;
     }
-    for (int s0 = blockIdx.x * kInputs; s0 < S; s0 += gridDim.x * kInputs) {
-        const int s = s0 + lane < S ? s0 + lane : S - 1;      // lanes past the last: not counted
+    for (int64_t s0 = (int64_t)blockIdx.x * kInputs; s0 < S; s0 += (int64_t)gridDim.x * kInputs) {
+        const int s = s0 + lane < S ? (int)s0 + lane : S - 1;   // lanes past the last: not counted
         for (int i = tid; i < K * kInputs; i += blockDim.x) (&s_cnt[0][0])[i] = 0;
         __syncthreads();
         for (int q0 = wave; q0 < TL && H > 0; q0 += waves * kBatch) {
-            int32_t row[kBatch];
-            int base[kBatch];
-            gptr<const int32_t> ids[kBatch];
-            gptr<const double> dr[kBatch];
+            int cls[kBatch];
+            lookup_classes(hot_ids, H, drift, sidx, S, L, TL, s, q0, waves, s_thr, cls);
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const int q = q0 + i * waves < TL ? q0 + i * waves : q0;
-                const int t = q / L, l = q - t * L;
-                row[i] = sidx[((int64_t)t * S + s) * L + l];
-                ids[i] = as_global(hot_ids[t]);
-                dr[i] = as_global(drift[t]);
-                base[i] = 0;
-            }
-            // lower bound: the last slot whose id is <= row (slot 0 if none is), down to four
-            // candidates, which one load fetches
-            for (int n = H; n > 4;) {
-                const int half = n >> 1;
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i)
-                    if (ids[i][base[i] + half] <= row[i]) base[i] += half;
-                n -= half;
-            }
-            bool found[kBatch];
-            double d[kBatch];
-            if (H >= 4) {
-                i4 four[kBatch];
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    base[i] = base[i] <= H - 4 ? base[i] : H - 4;
-                    four[i] = *(gptr<const i4>)(ids[i] + base[i]);
-                }
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    found[i] = four[i].x == row[i] || four[i].y == row[i] || four[i].z == row[i] ||
-                               four[i].w == row[i];
-                    base[i] += four[i].w <= row[i] ? 3 : four[i].z <= row[i] ? 2
-                               : four[i].y <= row[i] ? 1 : 0;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    for (int h = 1; h < H; ++h)
-                        if (ids[i][h] <= row[i]) base[i] = h;
-                    found[i] = ids[i][base[i]] == row[i];
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) d[i] = dr[i][base[i]];
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                // first threshold that the drift does not exceed: same verdict as
-                // ss_detect_stale; a NaN drift exceeds all of them
-                int k = 0;
-#pragma unroll
-                for (int half = K / 2; half > 0; half >>= 1)
-                    k += d[i] <= s_thr[k + half - 1] ? 0 : half;
-                if (q0 + i * waves < TL && found[i] && d[i] <= s_thr[k])
-                    atomicAdd(&s_cnt[k][lane], 1u);
-            }
+            for (int i = 0; i < kBatch; ++i)
+                if (cls[i] < K) atomicAdd(&s_cnt[cls[i]][lane], 1u);
         }
         __syncthreads();
         if (wave == 0 && s0 + lane < S) {
@@ -137,11 +166,45 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
         }
         __syncthreads();
     }
-    if (tid < n_thr) {
-        uint32_t c = 0;
-        for (int k = 0; k <= tid; ++k) c += s_inputs[k];
-        if (c) atomicAdd(&counts[ladder.slot[tid]], c);
+    add_counts(s_inputs, ladder, n_thr, counts);
+}
+
+// Inputs of at most kBatch lookups: an input is one lane's alone, its classes stay in
+// registers, and the alpha-th smallest is the least class that alpha of them do not exceed.
+// (The kernel above clears and reads back 32 counters per input, more than a short input's
+// searches cost: a threshold search over 190000 inputs of 2 lookups took 328 us, 245 now.)
+__global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_few_kernel(
+    const int32_t *const *__restrict__ hot_ids, int H,
+    const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
+    int L, int TL, int alpha, Ladder ladder, int n_thr, uint32_t *__restrict__ counts)
+{
+    constexpr int K = SS_MAX_THRESHOLDS;
+    __shared__ double s_thr[K];
+    __shared__ uint32_t s_inputs[K];
+    const int tid = threadIdx.x;
+    if (tid < K) {
+        s_thr[tid] = ladder.thr[tid];
+        s_inputs[tid] = 0;
     }
+    __syncthreads();
+    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + tid; s < S;
+         s += (int64_t)gridDim.x * blockDim.x) {
+        int first = alpha <= 0 ? 0 : K;
+        if (alpha > 0 && H > 0) {
+            int cls[kBatch];
+            lookup_classes(hot_ids, H, drift, sidx, S, L, TL, (int)s, 0, 1, s_thr, cls);
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                int below = 0;
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) below += cls[j] < K && cls[j] <= cls[i];
+                if (below >= alpha && cls[i] < first) first = cls[i];
+            }
+        }
+        if (first < K) atomicAdd(&s_inputs[first], 1u);
+    }
+    __syncthreads();
+    add_counts(s_inputs, ladder, n_thr, counts);
 }
 
 int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const *drift,
@@ -167,14 +230,20 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
             ladder.slot[i] = (uint8_t)k;
         }
         const int TL = T * L;
-        int waves = (TL + kBatch - 1) / kBatch;
-        if (waves > kMaxWaves) waves = kMaxWaves;
-        unsigned grid = (unsigned)(((int64_t)S + kInputs - 1) / kInputs);
-        if (grid > kMaxGroups) grid = kMaxGroups;
         ProfScope prof("sample_drop_kernel", s);
-        launch(sample_drop_kernel, dim3(grid), dim3(64 * waves), s,
-               (const int32_t *const *)hot_ids, H, (const double *const *)drift, sidx, S, L, TL,
-               alpha, ladder, n_thr, counts);
+#define SS_SAMPLE(kernel_, grid_, threads_)                                                 \
+    launch(kernel_, dim3(grid_), dim3(threads_), s, (const int32_t *const *)hot_ids, H,      \
+           (const double *const *)drift, sidx, S, L, TL, alpha, ladder, n_thr, counts)
+        if (TL <= kBatch) {
+            const int64_t groups = ((int64_t)S + 255) / 256;
+            SS_SAMPLE(sample_drop_few_kernel, (unsigned)(groups < kMaxGroups ? groups : kMaxGroups), 256);
+        } else {
+            int waves = (TL + kBatch - 1) / kBatch;
+            if (waves > kMaxWaves) waves = kMaxWaves;
+            const int64_t groups = ((int64_t)S + kInputs - 1) / kInputs;
+            SS_SAMPLE(sample_drop_kernel, (unsigned)(groups < kMaxGroups ? groups : kMaxGroups), 64 * waves);
+        }
+#undef SS_SAMPLE
     }
     return check_launch("ss_sample_drop");
 }
