@@ -560,6 +560,39 @@ __device__ __forceinline__ const f4 *grad_ptr(const f4 *table_base, uint32_t smp
     return table_base + ((uint64_t)smp * d4 + col);
 }
 
+// sum + the leading sums of strips q, q + 1, ... up to the one in which their run ends, in
+// strip order (column c of a lane group of G); *ended: whether it ends in this workgroup.
+// The hot rows' runs cross all strips, 64 of them where a row is 64 bytes: taken one at a time
+// each costs a trip to LDS for its state and one for its sum, so eight are requested together
+// (26 tables x 2048 lookups of 64 bytes: the kernel takes 7.0 instead of 9.4 us).  With 16 strips
+// or fewer and rows that leave lanes idle the registers cost more than the trips (14 tables x
+// 82096 lookups of 160 bytes: 41.4 us, 40.1 one at a time).
+template <int G, int NG, bool FULL>
+__device__ __forceinline__ f4 stitch(f4 sum, const f4 *s_lead, const uint8_t *s_lead_state, int q,
+                                     int c, bool *ended)
+{
+    constexpr int U = NG > 16 ? 8 : !FULL ? 1 : NG < 8 ? NG : 8;
+    bool open = true;
+    for (; open && q < NG; q += U) {
+        f4 v[U];
+        uint8_t st[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = q + u < NG ? q + u : NG - 1;
+            st[u] = s_lead_state[k];
+            v[u] = s_lead[k * G + c];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool take = open && q + u < NG;
+            if (take) sum = sum + v[u];
+            open = open && !(take && st[u] == 1);
+        }
+    }
+    *ended = !open;
+    return sum;
+}
+
 template <int G, int S, bool FULL, typename TS>
 __global__ __launch_bounds__(kApplyWG) void apply_kernel(
     float *const *__restrict__ weights, const uint2 *__restrict__ ent, int NP,
@@ -669,12 +702,8 @@ __global__ __launch_bounds__(kApplyWG) void apply_kernel(
         // stitch the runs that cross strip borders, in strip order; acc is the
         // sum of the run that leaves the strip to the right
         if (has_trail) {
-            f4 sum = acc;
             bool ended = false;
-            for (int q = g + 1; q < NG; ++q) {
-                sum = sum + s_lead[q * G + c];
-                if (s_lead_state[q] == 1) { ended = true; break; }
-            }
+            const f4 sum = stitch<G, NG, FULL>(acc, s_lead, s_lead_state, g + 1, c, &ended);
             if (ended) {
                 if (active)
                     *row_ptr<G, FULL>(Wc, row[S - 1], d4) = sgd(w_trail, sum, lr);
@@ -685,13 +714,10 @@ __global__ __launch_bounds__(kApplyWG) void apply_kernel(
         if (g == 0) {
             uint8_t st = state;
             if (st != 0) {
+                bool ended = st == 1;
                 f4 sum = s_lead[c];
-                int q = 0;
-                while (st == 2 && q + 1 < NG) {
-                    ++q;
-                    sum = sum + s_lead[q * G + c];
-                    st = s_lead_state[q];
-                }
+                if (!ended) sum = stitch<G, NG, FULL>(sum, s_lead, s_lead_state, 1, c, &ended);
+                st = ended ? 1 : 2;
                 if (active)
                     part_lead[((int64_t)t * wgs_per_table + wg) * D4 + col] = sum;
             }
