@@ -59,12 +59,51 @@ __global__ __launch_bounds__(kWG) void forward_kernel(
     trace_end(ts, trace_t0);
 }
 
+// Bags of fewer than 2^BITS lookups (BITS = 2, 3, 4), several per lane group: about a dozen
+// rows in flight.
+constexpr int bags_per_group(int bits) { return bits == 2 ? 4 : bits == 3 ? 2 : 1; }
+
+template <int G, bool FULL, int BITS, typename TS>
+__global__ __launch_bounds__(kWG) void forward_short_kernel(
+    const float *const *__restrict__ weights, const int32_t *__restrict__ idx,
+    int Bcap, int L, const int32_t *__restrict__ n_valid,
+    float *__restrict__ out, int D4, int tiles_per_table, int pinned_blocks, TS ts)
+{
+    constexpr int GROUPS = kWG / G, V = bags_per_group(BITS);
+    const unsigned long long trace_t0 = trace_begin<TS>();
+    int t, tile;
+    block_to_table_pinned(blockIdx.x, tiles_per_table, pinned_blocks, t, tile);
+    const int n = clamp_valid(n_valid, Bcap);
+    const int j0 = tile * GROUPS * V + (int)threadIdx.x / G;       // bags j0 + v * GROUPS
+    if (j0 >= n) return;
+    const int c = threadIdx.x % G;
+    const uint32_t d4 = FULL ? (uint32_t)G : (uint32_t)D4;
+    const auto W = as_global(reinterpret_cast<const f4 *>(weights[t]));
+    const int32_t *__restrict__ ip[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int j = j0 + v * GROUPS;
+        ip[v] = idx + ((int64_t)t * Bcap + (v == 0 || j < n ? j : j0)) * L;
+    }
+    f4 *__restrict__ o = reinterpret_cast<f4 *>(out) + ((int64_t)t * Bcap + j0) * d4;
+
+    for (int col = c; FULL ? col == c : col < D4; col += G) {
+        const auto Wc = W + col;            // this lane's f4 of row 0
+        f4 acc[V];
+        pool_bags<G, FULL, BITS, V>(Wc, ip, L, d4, acc);
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (v == 0 || j0 + v * GROUPS < n) o[(int64_t)v * GROUPS * d4 + col] = acc[v];
+    }
+    trace_end(ts, trace_t0);
+}
+
 int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
                        const int32_t *n_valid, float *out, hipStream_t s)
 {
     const int D4 = tb->dim / 4;
     const int g = lanes_per_row(tb->dim);
-    const int bags = (kWG / g) * (L == 1 ? kOneHotBags : 1);
+    const int bags = (kWG / g) * (L == 1 ? kOneHotBags : L < kLongBag ? bags_per_group(bag_bits(L)) : 1);
     const int tiles = (Bcap + bags - 1) / bags;
     const int64_t blocks = (int64_t)tiles * tb->num_tables;
     if (blocks > 0x7fffffffLL)
@@ -76,12 +115,15 @@ int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
                                             tb->weights, idx, Bcap, n_valid, out,
                                             D4, tiles, (tb->num_tables / 8) * 8 * tiles));
     } else {
-#define SS_FWD(F_)                                                                \
-    SS_DISPATCH_G(g, launch(SS_BOTH(forward_kernel, G, F_), dim3((unsigned)blocks),       \
-                            dim3(kWG), s, tb->weights, idx, Bcap, L, n_valid, out,  \
-                            D4, tiles, (tb->num_tables / 8) * 8 * tiles))
+#define SS_FWD1(K_, ...)                                                               \
+    launch(SS_BOTH(K_, G, __VA_ARGS__), dim3((unsigned)blocks), dim3(kWG), s, tb->weights, \
+           idx, Bcap, L, n_valid, out, D4, tiles, (tb->num_tables / 8) * 8 * tiles)
+#define SS_FWD(F_)                                                                     \
+    SS_DISPATCH_G(g, if (L >= kLongBag) { SS_FWD1(forward_kernel, F_); }                \
+                     else { SS_DISPATCH_BAG(L, SS_FWD1(forward_short_kernel, F_, BITS)); })
         if (D4 == g) { SS_FWD(true); } else { SS_FWD(false); }
 #undef SS_FWD
+#undef SS_FWD1
     }
     return check_launch("ss_embbag_forward");
 }

@@ -98,6 +98,24 @@ template <int N> __device__ __forceinline__ void add_rows(f4 &acc, const f4 (&v)
     for (int k = 0; k < N; ++k) acc = acc + v[k];
 }
 
+// Makes the compiler wait for a piece's row numbers, and so for all loads before them, and
+// compute nothing from them earlier.
+template <int N> __device__ __forceinline__ void arrived(int32_t (&r)[N])
+{
+    if constexpr (N >= 8) {
+#pragma unroll
+        for (int k = 0; k < N; k += 8)
+            asm volatile("" : "+v"(r[k]), "+v"(r[k + 1]), "+v"(r[k + 2]), "+v"(r[k + 3]),
+                              "+v"(r[k + 4]), "+v"(r[k + 5]), "+v"(r[k + 6]), "+v"(r[k + 7]));
+    } else if constexpr (N == 4) {
+        asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    } else if constexpr (N == 2) {
+        asm volatile("" : "+v"(r[0]), "+v"(r[1]));
+    } else {
+        asm volatile("" : "+v"(r[0]));
+    }
+}
+
 // Sum of the rows of a bag of m lookups at q, this lane's f4 of them, in bag order.
 template <int G, bool FULL, typename P>
 __device__ __forceinline__ f4 pool_bag(P Wc, const int32_t *__restrict__ q, int m, uint32_t d4)
@@ -118,6 +136,10 @@ __device__ __forceinline__ f4 pool_bag(P Wc, const int32_t *__restrict__ q, int 
     if (m & 4) { fetch_ids(rd, q); q += 4; }
     if (m & 2) { fetch_ids(re, q); q += 2; }
     if (m & 1) { fetch_ids(rf, q); }
+    // Without a power of two for the row length the compiler would otherwise begin with the row
+    // addresses piece by piece and wait for each piece's row numbers in turn (27.5 instead of
+    // 21.2 us at 14 tables x 5131 bags of 16 x 40 floats).
+    if (!FULL) { arrived(ra); arrived(rb); arrived(rd); arrived(re); arrived(rf); }
     f4 a[16], b[8], d[4], e[2], f[1];
     unset_rows(a); unset_rows(b); unset_rows(d); unset_rows(e); unset_rows(f);
     if (m & 16) fetch_rows<16, G, FULL>(a, ra, Wc, d4);
@@ -132,5 +154,89 @@ __device__ __forceinline__ f4 pool_bag(P Wc, const int32_t *__restrict__ q, int 
     if (m & 1) add_rows(acc, f);
     return acc;
 }
+
+// Sums of the rows of V bags of m lookups each, this lane's f4 of them, in bag order; q[0]
+// is a valid bag, q[v] the row numbers of bag v (of bag 0 again where there is none).  BITS:
+// m < 2^BITS, or any m with BITS = 4.  A wavefront's registers are sized for the longest bag
+// its kernel may meet: with those of pool_bag (164, 198 where rows leave lanes idle: two or
+// three wavefronts per SIMD) a bag of three keeps three loads in flight where there is room
+// for 31, so short bags have kernels of their own, and take several bags at once (lookup
+// kernel, us per training step: 2 tables x 32157 bags of 2, 64 floats, 56.8 instead of 60.6;
+// 5 x 29847 of 4, 208 floats, 165 instead of 191).
+// Long bags go in rounds of 16 here, with more wavefronts beside each other.  The
+// normalization wants that (3 x 12237 bags of 17, 200 floats, 11 k rows: 260 us per training
+// step, 287 with pool_bag); the lookup does not where rows come from memory (8 x 4096 bags of
+// 20, 128 floats, 10 M rows: 93 us per step, 88 with pool_bag).
+template <int G, bool FULL, int BITS, int V, typename P>
+__device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ const (&q0)[V], int m,
+                                          uint32_t d4, f4 (&acc)[V])
+{
+    static_assert(BITS < 4 || V == 1, "long bags are taken one at a time");
+    const int32_t *__restrict__ q[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        acc[v] = f4{0.f, 0.f, 0.f, 0.f};
+        q[v] = q0[v] + (BITS == 4 ? m & ~15 : 0);
+    }
+    // loads come back in the order they were issued: all row numbers first,
+    // so that no wait for a row number also waits for rows
+    int32_t ra[16] = {}, rb[V][8] = {}, rd[V][4] = {}, re[V][2] = {}, rf[V][1] = {};
+    if (BITS == 4 && m >= 16) fetch_ids(ra, q0[0]);
+#define SS_PIECES(DO_)                                                             \
+    if (BITS >= 4 && (m & 8)) { DO_(rb, b, 8) }                                    \
+    if (BITS >= 3 && (m & 4)) { DO_(rd, d, 4) }                                    \
+    if (m & 2) { DO_(re, e, 2) }                                                   \
+    if (m & 1) { DO_(rf, f, 1) }
+#define SS_FETCH_IDS(r_, x_, n_)                                                   \
+    _Pragma("unroll") for (int v = 0; v < V; ++v) { fetch_ids(r_[v], q[v]); q[v] += n_; }
+#define SS_FETCH_ROWS(r_, x_, n_)                                                  \
+    _Pragma("unroll") for (int v = 0; v < V; ++v) fetch_rows<n_, G, FULL>(x_[v], r_[v], Wc, d4);
+#define SS_ADD_ROWS(r_, x_, n_)                                                    \
+    _Pragma("unroll") for (int v = 0; v < V; ++v) add_rows(acc[v], x_[v]);
+    SS_PIECES(SS_FETCH_IDS)
+    // All row numbers are waited for here.  Left to the compiler, which does not know which
+    // pieces were requested, the wait for a later piece's row numbers covers the rows of the
+    // earlier ones.
+    if constexpr (BITS >= 4) arrived(ra);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        if constexpr (BITS >= 4) arrived(rb[v]);
+        if constexpr (BITS >= 3) arrived(rd[v]);
+        arrived(re[v]);
+        arrived(rf[v]);
+    }
+    if constexpr (BITS == 4) {
+        const int32_t *__restrict__ qa = q0[0];
+        for (int left = m >> 4; left > 0; --left) {
+            f4 a[16];
+            fetch_rows<16, G, FULL>(a, ra, Wc, d4);
+            qa += 16;
+            if (left > 1) fetch_ids(ra, qa);
+            add_rows(acc[0], a);
+        }
+    }
+    f4 b[V][8], d[V][4], e[V][2], f[V][1];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        unset_rows(b[v]); unset_rows(d[v]); unset_rows(e[v]); unset_rows(f[v]);
+    }
+    SS_PIECES(SS_FETCH_ROWS)
+    SS_PIECES(SS_ADD_ROWS)
+#undef SS_PIECES
+#undef SS_FETCH_IDS
+#undef SS_FETCH_ROWS
+#undef SS_ADD_ROWS
+}
+
+// The kernel for bags of L lookups: BITS of pool_bags.
+inline int bag_bits(int L) { return L < 4 ? 2 : L < 8 ? 3 : 4; }
+constexpr int kLongBag = 16;       // bags that the lookup takes with pool_bag
+
+#define SS_DISPATCH_BAG(L, ...)                                 \
+    switch (bag_bits(L)) {                                      \
+    case 2: { constexpr int BITS = 2; __VA_ARGS__; } break;     \
+    case 3: { constexpr int BITS = 3; __VA_ARGS__; } break;     \
+    default: { constexpr int BITS = 4; __VA_ARGS__; } break;    \
+    }
 
 }  // namespace ss

@@ -52,6 +52,10 @@ __device__ __forceinline__ float hdot(f4 a, f4 b)
 {
     return fmaf(a.x, b.x, a.y * b.y) + fmaf(a.z, b.z, a.w * b.w);
 }
+__device__ __forceinline__ f4 fma4(f4 a, f4 b, f4 c)
+{
+    return f4{fmaf(a.x, b.x, c.x), fmaf(a.y, b.y, c.y), fmaf(a.z, b.z, c.z), fmaf(a.w, b.w, c.w)};
+}
 template <typename A, typename B>
 __device__ __forceinline__ A mul_rounded(A a, B b)
 {
@@ -120,7 +124,7 @@ __device__ __forceinline__ void pool_row(const XSource &src, int t, int64_t vec,
 
 // The V vectors j0 + k * NG of table t (those at n or beyond: vector j0 again, which is
 // always valid), everything that does not depend on another load requested at once.
-template <int G, int P, int V, XFrom FROM>
+template <int G, int P, int V, XFrom FROM, int BITS>
 __device__ __forceinline__ void fetch_x(const XSource &src, int t, int Bcap, int j0, int NG,
                                         int n, int c, int D4, f4 (&v)[V][P])
 {
@@ -147,8 +151,9 @@ __device__ __forceinline__ void fetch_x(const XSource &src, int t, int Bcap, int
                 // lanes past the row form the sum of column 0 and hold zeros, as after load_row
                 const auto Wc = as_global(reinterpret_cast<const f4 *>(src.weights[t])) +
                                 (FROM == kBagFull || c < D4 ? c : 0);
-                v[k][0] = pool_bag<G, FROM == kBagFull>(Wc, src.idx + vec * src.L, src.L,
-                                                        FROM == kBagFull ? G : D4);
+                const int32_t *__restrict__ const q[1] = {src.idx + vec * src.L};
+                pool_bags<G, FROM == kBagFull, BITS, 1>(Wc, q, src.L, FROM == kBagFull ? G : D4,
+                                                        v[k]);
                 if (FROM == kBag && c >= D4) v[k][0] = f4{0.f, 0.f, 0.f, 0.f};
             } else if constexpr (FROM == kBag)
                 pool_row<G, P>(src, t, vec, c, D4, v[k]);
@@ -169,7 +174,7 @@ template <int P, XFrom FROM> constexpr int ln_fwd_vectors()
     return P > 1 || FROM == kBag || FROM == kBagFull ? 1 : 4;
 }
 
-template <int G, int P, XFrom FROM>
+template <int G, int P, XFrom FROM, int BITS>
 __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     XSource src, int Bcap, const int32_t *__restrict__ n_valid,
     const float *__restrict__ gamma, const float *__restrict__ beta, float eps,
@@ -186,7 +191,7 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     const float inv_d = 1.0f / (float)(D4 * 4);
 
     f4 v[V][P];
-    fetch_x<G, P, V, FROM>(src, t, Bcap, j0, NG, n, c, D4, v);
+    fetch_x<G, P, V, FROM, BITS>(src, t, Bcap, j0, NG, n, c, D4, v);
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const int j = j0 + k * NG;
@@ -205,8 +210,7 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
                 q += hdot(v[k][i], v[k][i]);
             }
         }
-        const float var = mul_rounded(group_sum<G>(q), inv_d);
-        const float rs = 1.0f / sqrtf(var + eps);
+        const float rs = 1.0f / sqrtf(fmaf(group_sum<G>(q), inv_d, eps));
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             const int col = c + i * G;
@@ -233,7 +237,7 @@ template <int P, XFrom FROM> constexpr int ln_bwd_vectors()
     return P > 1 || FROM == kBag || FROM == kBagFull ? 1 : 2;
 }
 
-template <int G, int P, XFrom FROM>
+template <int G, int P, XFrom FROM, int BITS>
 __global__ __launch_bounds__(kWG) void ln_backward_kernel(
     const float *dy, XSource src, int Bcap,
     const int32_t *__restrict__ n_valid, const float *__restrict__ gamma,
@@ -271,7 +275,7 @@ __global__ __launch_bounds__(kWG) void ln_backward_kernel(
             mu[k] = mean[vec];
             rs[k] = rstd[vec];
         }
-        fetch_x<G, P, V, FROM>(src, t, Bcap, j0, NG, n, c, D4, xv);
+        fetch_x<G, P, V, FROM, BITS>(src, t, Bcap, j0, NG, n, c, D4, xv);
 #pragma unroll
         for (int k = 0; k < V; ++k) {
             if (j0 + k * NG >= n) break;
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(kWG) void ln_backward_kernel(
                     const f4 gd = mul_rounded(gam[i], dv[k][i]);
                     s1 += hdot(gam[i], dv[k][i]);
                     s2 += hdot(gd, xv[k][i]);
-                    acc_g[i] = acc_g[i] + dv[k][i] * xv[k][i];
+                    acc_g[i] = fma4(dv[k][i], xv[k][i], acc_g[i]);
                     acc_b[i] = acc_b[i] + dv[k][i];
                 }
             }
@@ -294,8 +298,10 @@ __global__ __launch_bounds__(kWG) void ln_backward_kernel(
 #pragma unroll
             for (int i = 0; i < P; ++i) {
                 const int col = c + i * G;
-                if (col < D4)
-                    op[col] = (mul_rounded(gam[i], dv[k][i]) - m1 - xv[k][i] * m2) * rs[k];
+                if (col < D4) {
+                    const f4 gd = fma4(gam[i], dv[k][i], f4{-m1, -m1, -m1, -m1});
+                    op[col] = fma4(-xv[k][i], f4{m2, m2, m2, m2}, gd) * rs[k];
+                }
             }
         }
     }
@@ -394,14 +400,15 @@ int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *co
     if ((int64_t)tiles * T > 0x7fffffffLL)
         return fail(SS_ERR_UNSUPPORTED, "ss_layernorm_forward: grid too large");
     ProfScope prof(x ? "ln_forward_kernel" : "ln_forward_pool_kernel", s);
-#define SS_LN_FWD1(P_, F_)                                                                   \
-    launch(ln_forward_kernel<G, P_, F_>, dim3((unsigned)(tiles * T)), dim3(kWG), s, src, Bcap, \
+#define SS_LN_FWD1(P_, F_, BITS_)                                                                 \
+    launch(ln_forward_kernel<G, P_, F_, BITS_>, dim3((unsigned)(tiles * T)), dim3(kWG), s, src, Bcap, \
            n_valid, gamma, beta, eps, y, mean, rstd, D4, tiles)
 #define SS_LN_FWD(P_)                                                                        \
-    if (x) { SS_LN_FWD1(P_, kMemory); }                                                      \
-    else if (L == 1) { SS_LN_FWD1(P_, kOneHot); }                                            \
-    else if (P_ == 1 && D4 == g) { SS_LN_FWD1(P_, (P_ == 1 ? kBagFull : kBag)); }             \
-    else { SS_LN_FWD1(P_, kBag); }
+    if (x) { SS_LN_FWD1(P_, kMemory, 4); }                                                   \
+    else if (L == 1) { SS_LN_FWD1(P_, kOneHot, 4); }                                         \
+    else if constexpr (P_ > 1) { SS_LN_FWD1(P_, kBag, 4); }                                  \
+    else if (D4 == g) { SS_DISPATCH_BAG(L, SS_LN_FWD1(1, kBagFull, BITS)); }                 \
+    else { SS_DISPATCH_BAG(L, SS_LN_FWD1(1, kBag, BITS)); }
     SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_FWD(1); } else {
         if (D4 <= 64) { SS_LN_FWD(1); } else if (D4 <= 128) { SS_LN_FWD(2); } else { SS_LN_FWD(4); }
     });
@@ -432,14 +439,15 @@ int32_t launch_layernorm_backward(int T, int dim, const float *dy, const float *
     f4 *pb = params ? pg + (size_t)T * wgs * D4 : nullptr;
     {
         ProfScope prof(x ? "ln_backward_kernel" : "ln_backward_pool_kernel", s);
-#define SS_LN_BWD1(P_, F_)                                                                   \
-    launch(ln_backward_kernel<G, P_, F_>, dim3((unsigned)(wgs * T)), dim3(kWG), s, dy, src,   \
+#define SS_LN_BWD1(P_, F_, BITS_)                                                                 \
+    launch(ln_backward_kernel<G, P_, F_, BITS_>, dim3((unsigned)(wgs * T)), dim3(kWG), s, dy, src,   \
            Bcap, n_valid, gamma, mean, rstd, dx, D4, plan.tiles, wgs, pg, pb)
 #define SS_LN_BWD(P_)                                                                        \
-    if (x) { SS_LN_BWD1(P_, kMemory); }                                                      \
-    else if (L == 1) { SS_LN_BWD1(P_, kOneHot); }                                            \
-    else if (P_ == 1 && D4 == g) { SS_LN_BWD1(P_, (P_ == 1 ? kBagFull : kBag)); }             \
-    else { SS_LN_BWD1(P_, kBag); }
+    if (x) { SS_LN_BWD1(P_, kMemory, 4); }                                                   \
+    else if (L == 1) { SS_LN_BWD1(P_, kOneHot, 4); }                                         \
+    else if constexpr (P_ > 1) { SS_LN_BWD1(P_, kBag, 4); }                                  \
+    else if (D4 == g) { SS_DISPATCH_BAG(L, SS_LN_BWD1(1, kBagFull, BITS)); }                 \
+    else { SS_DISPATCH_BAG(L, SS_LN_BWD1(1, kBag, BITS)); }
         SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_BWD(1); } else {
             if (D4 <= 64) { SS_LN_BWD(1); } else if (D4 <= 128) { SS_LN_BWD(2); } else { SS_LN_BWD(4); }
         });
