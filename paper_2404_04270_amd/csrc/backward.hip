@@ -565,13 +565,13 @@ __device__ __forceinline__ const f4 *grad_ptr(const f4 *table_base, uint32_t smp
 // The hot rows' runs cross all strips, 64 of them where a row is 64 bytes: taken one at a time
 // each costs a trip to LDS for its state and one for its sum, so eight are requested together
 // (26 tables x 2048 lookups of 64 bytes: the kernel takes 7.0 instead of 9.4 us).  With 16 strips
-// or fewer and rows that leave lanes idle the registers cost more than the trips (14 tables x
-// 82096 lookups of 160 bytes: 41.4 us, 40.1 one at a time).
-template <int G, int NG, bool FULL>
+// or fewer the registers cost more than the trips (14 tables x 82096 lookups of 160 bytes: 41.4
+// us, 40.1 one at a time; a training step with 26 x 8192 of 256 bytes: 46.8 and 46.3).
+template <int G, int NG>
 __device__ __forceinline__ f4 stitch(f4 sum, const f4 *s_lead, const uint8_t *s_lead_state, int q,
                                      int c, bool *ended)
 {
-    constexpr int U = NG > 16 ? 8 : !FULL ? 1 : NG < 8 ? NG : 8;
+    constexpr int U = NG > 16 ? 8 : 1;
     bool open = true;
     for (; open && q < NG; q += U) {
         f4 v[U];
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(kApplyWG) void apply_kernel(
         // sum of the run that leaves the strip to the right
         if (has_trail) {
             bool ended = false;
-            const f4 sum = stitch<G, NG, FULL>(acc, s_lead, s_lead_state, g + 1, c, &ended);
+            const f4 sum = stitch<G, NG>(acc, s_lead, s_lead_state, g + 1, c, &ended);
             if (ended) {
                 if (active)
                     *row_ptr<G, FULL>(Wc, row[S - 1], d4) = sgd(w_trail, sum, lr);
@@ -716,7 +716,7 @@ __global__ __launch_bounds__(kApplyWG) void apply_kernel(
             if (st != 0) {
                 bool ended = st == 1;
                 f4 sum = s_lead[c];
-                if (!ended) sum = stitch<G, NG, FULL>(sum, s_lead, s_lead_state, 1, c, &ended);
+                if (!ended) sum = stitch<G, NG>(sum, s_lead, s_lead_state, 1, c, &ended);
                 st = ended ? 1 : 2;
                 if (active)
                     part_lead[((int64_t)t * wgs_per_table + wg) * D4 + col] = sum;
@@ -1088,7 +1088,11 @@ int32_t launch_backward_apply(const ss_tables *tb, int Bcap, int L, const float 
     const int g = lanes_per_row(tb->dim);
     const int ng = kApplyWG / g;
     const int strip = pick_strip(g);
-    const int wgs = y.NP / (ng * strip);
+    // Workgroups that hold lookups: the padding behind them is sentinels.  Where one holds all of
+    // a table's lookups no run can leave it, and the fixup launch is left out (2.3 us and its
+    // launch: 31.4 instead of 33.7 us per training step at 8 tables x 128 lookups x 64 bytes).
+    const int64_t nnz = (int64_t)Bcap * L;
+    const int wgs = (int)((nnz + ng * strip - 1) / (ng * strip));
     uint32_t *trail_row = reinterpret_cast<uint32_t *>(w8 + y.trail_row);
     uint8_t *lead_state = reinterpret_cast<uint8_t *>(w8 + y.lead_state);
     f4 *part_lead = reinterpret_cast<f4 *>(w8 + y.part_lead);
@@ -1105,6 +1109,7 @@ int32_t launch_backward_apply(const ss_tables *tb, int Bcap, int L, const float 
                             lead_state, part_lead, part_trail))
     {
         ProfScope prof("apply_kernel", s);
+        if (record_after && wgs == 1) stop_event_for_next_launch(record_after);
         // a row that fills its group of lanes exactly needs no column loop and no guard
         const bool full = D4 == g && (int64_t)Bcap * tb->dim * 4 <= 0xFFFFFFFFLL;
         if (strip == 8) {
@@ -1114,6 +1119,7 @@ int32_t launch_backward_apply(const ss_tables *tb, int Bcap, int L, const float 
         }
     }
 #undef SS_APPLY
+    if (wgs == 1) return check_launch("ss_embbag_backward_apply");
     ProfScope prof("fixup_kernel", s);
     // apply workgroups looked at per workgroup of this launch
     const int per_chunk = (int64_t)wgs * T <= 2048 ? 1 : kWG / g;
