@@ -373,8 +373,9 @@ int32_t ss_layernorm_forward(int32_t num_tables, int32_t dim, const float *x,
  *     dbeta[t][d]  = sum_{j < n_valid} dy[t][j][d]
  * dx is the gradient ss_embbag_backward_update expects.  dx may be dy itself.
  * dgamma / dbeta (device fp32 [T][dim]) may be NULL; if either is given, ws must
- * hold ss_layernorm_backward_workspace_bytes(...) bytes, 256-byte aligned.  The
- * sums over the batch are taken in a fixed order.
+ * hold ss_layernorm_backward_workspace_bytes(...) bytes, 256-byte aligned (the
+ * size falls in none of its arguments: a workspace for the largest batch serves
+ * the smaller ones).  The sums over the batch are taken in a fixed order.
  */
 int32_t ss_layernorm_backward(int32_t num_tables, int32_t dim, const float *dy,
                               const float *x, int32_t Bcap, const int32_t *n_valid,

@@ -386,6 +386,20 @@ BackwardPlan plan_backward(int T, int dim, int Bcap)
     return p;
 }
 
+// Partial rows of all tables that a workspace holds: at least those of every split of this
+// and of every smaller batch, so that a program can size it once for its largest.  (A smaller
+// batch may get more workgroups: 26 tables of 64 floats take 64 per table at 4096 vectors and
+// 79 at 2520.)  With 8 vectors per group T * ceil(Bcap / 8 ng); with fewer, which takes T * Bcap
+// below 2 * kLnMinWgs * ng * tiles, at most T * ceil(Bcap / 2 ng) and under 2 * kLnMinWgs + T.
+int64_t partial_rows(int T, int dim, int Bcap)
+{
+    const int ng = kWG / lanes_per_row(dim);
+    const auto wgs = [&](int tiles) { return ((int64_t)Bcap + ng * tiles - 1) / (ng * tiles); };
+    const int64_t most = T * wgs(kLnMaxTiles), few = T * wgs(2), split = 2 * kLnMinWgs + T;
+    const int64_t fine = few < split ? few : split;
+    return most > fine ? most : fine;
+}
+
 }  // namespace
 
 int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *const *weights,
@@ -419,7 +433,7 @@ int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *co
 
 size_t layernorm_backward_ws_bytes(int T, int dim, int Bcap)
 {
-    return align_up((size_t)2 * T * plan_backward(T, dim, Bcap).wgs * dim * sizeof(float), 256);
+    return align_up((size_t)2 * partial_rows(T, dim, Bcap) * dim * sizeof(float), 256);
 }
 
 int32_t launch_layernorm_backward(int T, int dim, const float *dy, const float *x,
