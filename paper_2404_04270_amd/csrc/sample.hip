@@ -13,15 +13,17 @@
 // class of its lookups on, so one number per input replaces a count per threshold.
 //
 // A workgroup takes 64 inputs, one per lane, and its wavefronts split the T * L lookups of
-// an input between them.  A lookup maps its row to a hot slot by a branch-free lower-bound
+// an input between them (fewer inputs, and several lanes for each, where a sample is small and
+// its inputs are long).  A lookup maps its row to a hot slot by a branch-free lower-bound
 // search in the ascending hot_ids of its table; a lane runs up to four such searches
 // interleaved, since each step is one dependent load that only latency bounds.  All lanes
 // of a wavefront search the same table: its popular rows and the first steps of every
 // search are the same few cache lines, and the lines that the loads bring to the compute
 // unit are what bounds the kernel (with neighbouring lanes in different tables, nearly as
 // many lines as lanes: 51.4 us for 65536 inputs of 26 lookups, 5000 hot rows per table and
-// 32 thresholds, 24.6 now; 84 and 40 with the hot rows scattered over the table).  Classes are counted per input in LDS, inputs per class in LDS, and each workgroup
-// adds its share to the counts at the end.
+// 32 thresholds, 24.6 now; 84 and 40 with the hot rows scattered over the table).  Classes are
+// counted per input in LDS, inputs per class in LDS, and each workgroup adds its share to the
+// counts at the end.
 #include <math.h>
 
 #include "ss_common.h"
@@ -37,7 +39,6 @@ struct Ladder {
 };
 
 constexpr int kBatch = 4;        // searches a lane keeps in flight
-constexpr int kInputs = 64;      // inputs per workgroup and round
 constexpr int kMaxWaves = 8;
 // More workgroups only add more to the few words of the counts (us for 65536 inputs of 26
 // lookups / 44414 of 12 / 190000 of 2, at 256, 512, 1024 and 2048 workgroups: 31.8 / 17.3 / 17.8,
@@ -46,25 +47,26 @@ constexpr int64_t kMaxGroups = 512;
 
 typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
 
-// Classes of kBatch lookups of input s: q0, q0 + step, ... of its TL (those at TL or beyond:
+// Classes of N lookups of input s: q0, q0 + step, ... of its TL (those at TL or beyond:
 // none).  The class of a lookup is the first threshold its row's drift does not exceed, K where
 // there is none or the row is not hot.
+template <int N>
 __device__ __forceinline__ void lookup_classes(
     const int32_t *const *__restrict__ hot_ids, int H, const double *const *__restrict__ drift,
-    const int32_t *__restrict__ sidx, int S, int L, int TL, int s, int q0, int step,
-    const double *s_thr, int (&cls)[kBatch])
+    const int32_t *__restrict__ sidx, int S, uint32_t L, uint32_t TL, int s, uint32_t q0,
+    uint32_t step, const double *s_thr, int (&cls)[N])
 {
     constexpr int K = SS_MAX_THRESHOLDS;
     static_assert(K == 32, "the class search takes five steps");
-    double d[kBatch];
-    int32_t row[kBatch];
-    int base[kBatch];
-    gptr<const int32_t> ids[kBatch];
-    gptr<const double> dr[kBatch];
+    double d[N];
+    int32_t row[N];
+    int base[N];
+    gptr<const int32_t> ids[N];
+    gptr<const double> dr[N];
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-        const int q = q0 + i * step < TL ? q0 + i * step : q0;
-        const int t = q / L, l = q - t * L;
+    for (int i = 0; i < N; ++i) {
+        const uint32_t q = q0 + i * step < TL ? q0 + i * step : q0;    // TL < 2^31
+        const uint32_t t = q / L, l = q - t * L;
         row[i] = sidx[((int64_t)t * S + s) * L + l];
         ids[i] = as_global(hot_ids[t]);
         dr[i] = as_global(drift[t]);
@@ -75,20 +77,20 @@ __device__ __forceinline__ void lookup_classes(
     for (int n = H; n > 4;) {
         const int half = n >> 1;
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i)
+        for (int i = 0; i < N; ++i)
             if (ids[i][base[i] + half] <= row[i]) base[i] += half;
         n -= half;
     }
-    bool found[kBatch];
+    bool found[N];
     if (H >= 4) {
-        i4 four[kBatch];
+        i4 four[N];
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             base[i] = base[i] <= H - 4 ? base[i] : H - 4;
             four[i] = *(gptr<const i4>)(ids[i] + base[i]);
         }
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             found[i] = four[i].x == row[i] || four[i].y == row[i] || four[i].z == row[i] ||
                        four[i].w == row[i];
             base[i] += four[i].w <= row[i] ? 3 : four[i].z <= row[i] ? 2
@@ -96,16 +98,16 @@ __device__ __forceinline__ void lookup_classes(
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             for (int h = 1; h < H; ++h)
                 if (ids[i][h] <= row[i]) base[i] = h;
             found[i] = ids[i][base[i]] == row[i];
         }
     }
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) d[i] = dr[i][base[i]];
+    for (int i = 0; i < N; ++i) d[i] = dr[i][base[i]];
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
+    for (int i = 0; i < N; ++i) {
         // same verdict as ss_detect_stale; a NaN drift exceeds all thresholds
         int k = 0;
 #pragma unroll
@@ -127,6 +129,8 @@ __device__ __forceinline__ void add_counts(const uint32_t *s_inputs, const Ladde
     }
 }
 
+// I inputs per workgroup and round, 64 / I lanes of each wavefront for one.
+template <int I>
 __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
     const int32_t *const *__restrict__ hot_ids, int H,
     const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
@@ -134,32 +138,34 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
 {
     constexpr int K = SS_MAX_THRESHOLDS;
     __shared__ double s_thr[K];
-    __shared__ uint32_t s_cnt[K][kInputs];      // lookups per class and input
+    __shared__ uint32_t s_cnt[K][I];            // lookups per class and input
     __shared__ uint32_t s_inputs[K];            // inputs that can be dropped from class k on
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
+    const int tid = threadIdx.x, in = tid & (I - 1);
+    // lookups q0, q0 + step, ... of its input are this lane's
+    const uint32_t first_q = I == 64 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid / I;
+    const uint32_t step = blockDim.x / I;
     if (tid < K) {
         s_thr[tid] = ladder.thr[tid];
         s_inputs[tid] = 0;
     }
-    for (int64_t s0 = (int64_t)blockIdx.x * kInputs; s0 < S; s0 += (int64_t)gridDim.x * kInputs) {
-        const int s = s0 + lane < S ? (int)s0 + lane : S - 1;   // lanes past the last: not counted
-        for (int i = tid; i < K * kInputs; i += blockDim.x) (&s_cnt[0][0])[i] = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * I; s0 < S; s0 += (int64_t)gridDim.x * I) {
+        const int s = s0 + in < S ? (int)s0 + in : S - 1;       // lanes past the last: not counted
+        for (int i = tid; i < K * I; i += blockDim.x) (&s_cnt[0][0])[i] = 0;
         __syncthreads();
-        for (int q0 = wave; q0 < TL && H > 0; q0 += waves * kBatch) {
+        for (uint32_t q0 = first_q; q0 < (uint32_t)TL && H > 0; q0 += step * kBatch) {
             int cls[kBatch];
-            lookup_classes(hot_ids, H, drift, sidx, S, L, TL, s, q0, waves, s_thr, cls);
+            lookup_classes(hot_ids, H, drift, sidx, S, L, TL, s, q0, step, s_thr, cls);
 #pragma unroll
             for (int i = 0; i < kBatch; ++i)
-                if (cls[i] < K) atomicAdd(&s_cnt[cls[i]][lane], 1u);
+                if (cls[i] < K) atomicAdd(&s_cnt[cls[i]][in], 1u);
         }
         __syncthreads();
-        if (wave == 0 && s0 + lane < S) {
+        if (tid < I && s0 + tid < S) {
             int64_t below = 0;
             int first = K;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                below += s_cnt[k][lane];
+                below += s_cnt[k][tid];
                 first = first == K && below >= alpha ? k : first;
             }
             if (first < K) atomicAdd(&s_inputs[first], 1u);
@@ -238,10 +244,23 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
             const int64_t groups = ((int64_t)S + 255) / 256;
             SS_SAMPLE(sample_drop_few_kernel, (unsigned)(groups < kMaxGroups ? groups : kMaxGroups), 256);
         } else {
-            int waves = (TL + kBatch - 1) / kBatch;
+            // With 64 inputs each there are S / 64 workgroups, and a lane of eight wavefronts has
+            // TL / 32 rounds of searches before it.  Where both leave the chip waiting an input
+            // gets 4 or 16 lanes of every wavefront (us with 64 / 16 / 4 inputs per workgroup,
+            // 5000 hot rows: 1000 inputs of 1280 lookups 267 / 80 / 41, 3000 of 1280 280 / 107 /
+            // 109, 1000 of 48 19.4 / 9.9 / 9.0, 5950 of 520 121 / 91 / 99, 12000 of 520 132 / 156 /
+            // 191; 100 hot rows, 3000 of 1280: 131 / 44 / 30).
+            int I = 64;
+            if (S < 8192 && TL > kMaxWaves * kBatch) I = 16;
+            if (S < 4096 && TL > kMaxWaves * kBatch * 4) I = 4;
+            const int per_wave = kBatch * (64 / I);
+            int waves = (TL + per_wave - 1) / per_wave;
             if (waves > kMaxWaves) waves = kMaxWaves;
-            const int64_t groups = ((int64_t)S + kInputs - 1) / kInputs;
-            SS_SAMPLE(sample_drop_kernel, (unsigned)(groups < kMaxGroups ? groups : kMaxGroups), 64 * waves);
+            const int64_t groups = ((int64_t)S + I - 1) / I;
+            const unsigned grid = (unsigned)(groups < kMaxGroups ? groups : kMaxGroups);
+            if (I == 64) SS_SAMPLE(sample_drop_kernel<64>, grid, 64 * waves);
+            else if (I == 16) SS_SAMPLE(sample_drop_kernel<16>, grid, 64 * waves);
+            else SS_SAMPLE(sample_drop_kernel<4>, grid, 64 * waves);
         }
 #undef SS_SAMPLE
     }
