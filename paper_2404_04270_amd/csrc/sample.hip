@@ -175,11 +175,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_kernel(
     add_counts(s_inputs, ladder, n_thr, counts);
 }
 
-// Inputs of at most kBatch lookups: an input is one lane's alone, its classes stay in
+// Inputs of at most N lookups: an input is one lane's alone, its classes stay in
 // registers, and the alpha-th smallest is the least class that alpha of them do not exceed.
 // (The kernel above clears and reads back 32 counters per input, more than a short input's
 // searches cost: a threshold search over 190000 inputs of 2 lookups took 328 us, 245 now.)
-__global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_few_kernel(
+template <int N>
+__global__ __launch_bounds__(256) void sample_drop_few_kernel(
     const int32_t *const *__restrict__ hot_ids, int H,
     const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
     int L, int TL, int alpha, Ladder ladder, int n_thr, uint32_t *__restrict__ counts)
@@ -197,13 +198,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_drop_few_kernel(
          s += (int64_t)gridDim.x * blockDim.x) {
         int first = alpha <= 0 ? 0 : K;
         if (alpha > 0 && H > 0) {
-            int cls[kBatch];
+            int cls[N];
             lookup_classes(hot_ids, H, drift, sidx, S, L, TL, (int)s, 0, 1, s_thr, cls);
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
+            for (int i = 0; i < N; ++i) {
                 int below = 0;
 #pragma unroll
-                for (int j = 0; j < kBatch; ++j) below += cls[j] < K && cls[j] <= cls[i];
+                for (int j = 0; j < N; ++j) below += cls[j] < K && cls[j] <= cls[i];
                 if (below >= alpha && cls[i] < first) first = cls[i];
             }
         }
@@ -240,9 +241,15 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
 #define SS_SAMPLE(kernel_, grid_, threads_)                                                 \
     launch(kernel_, dim3(grid_), dim3(threads_), s, (const int32_t *const *)hot_ids, H,      \
            (const double *const *)drift, sidx, S, L, TL, alpha, ladder, n_thr, counts)
-        if (TL <= kBatch) {
+        // Five to eight lookups: where the workgroups of the general kernel, 64 inputs each, would
+        // go round more than once (us, general kernel and this one, 5 and 8 lookups, 100 hot rows:
+        // 65536 inputs 14.7 / 10.8 and 15.2 / 11.4, 28000 10.5 / 9.9 and 10.7 / 10.5; 5000 hot rows:
+        // 65536 19.9 / 17.7 and 24.1 / 22.3, 28000 12.8 / 14.4 and 14.9 / 16.9).
+        if (TL <= kBatch || (TL <= 2 * kBatch && S > 64 * kMaxGroups)) {
             const int64_t groups = ((int64_t)S + 255) / 256;
-            SS_SAMPLE(sample_drop_few_kernel, (unsigned)(groups < kMaxGroups ? groups : kMaxGroups), 256);
+            const unsigned grid = (unsigned)(groups < kMaxGroups ? groups : kMaxGroups);
+            if (TL <= kBatch) SS_SAMPLE(sample_drop_few_kernel<kBatch>, grid, 256);
+            else SS_SAMPLE(sample_drop_few_kernel<2 * kBatch>, grid, 256);
         } else {
             // With 64 inputs each there are S / 64 workgroups, and a lane of eight wavefronts has
             // TL / 32 rounds of searches before it.  Where both leave the chip waiting an input

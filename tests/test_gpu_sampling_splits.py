@@ -56,3 +56,9 @@ def test_few_inputs(T, L, S):
                                    (3, 11, 8192), (4, 8, 8191)])
 def test_borders_of_the_sample_size(T, L, S):
     check(T, L, S)
+
+
+@pytest.mark.parametrize("T,L", [(5, 1), (3, 2), (7, 1), (2, 4), (9, 1)])
+@pytest.mark.parametrize("S", [32_768, 32_769])
+def test_five_to_eight_lookups_in_registers(T, L, S):
+    check(T, L, S)
