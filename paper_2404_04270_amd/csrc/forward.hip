@@ -120,7 +120,7 @@ int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
            idx, Bcap, L, n_valid, out, D4, tiles, (tb->num_tables / 8) * 8 * tiles)
 #define SS_FWD(F_)                                                                     \
     SS_DISPATCH_G(g, if (L >= kLongBag) { SS_FWD1(forward_kernel, F_); }                \
-                     else { SS_DISPATCH_BAG(L, SS_FWD1(forward_short_kernel, F_, BITS)); })
+                     else { SS_DISPATCH_SHORT_BAG(L, SS_FWD1(forward_short_kernel, F_, BITS)); })
         if (D4 == g) { SS_FWD(true); } else { SS_FWD(false); }
 #undef SS_FWD
 #undef SS_FWD1

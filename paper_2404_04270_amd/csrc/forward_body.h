@@ -157,7 +157,7 @@ __device__ __forceinline__ f4 pool_bag(P Wc, const int32_t *__restrict__ q, int 
 
 // Sums of the rows of V bags of m lookups each, this lane's f4 of them, in bag order; q[0]
 // is a valid bag, q[v] the row numbers of bag v (of bag 0 again where there is none).  BITS:
-// m < 2^BITS, or any m with BITS = 4.  A wavefront's registers are sized for the longest bag
+// m < 2^BITS, or any m with BITS = 5.  A wavefront's registers are sized for the longest bag
 // its kernel may meet: with those of pool_bag (164, 198 where rows leave lanes idle: two or
 // three wavefronts per SIMD) a bag of three keeps three loads in flight where there is room
 // for 31, so short bags have kernels of their own, and take several bags at once (lookup
@@ -176,12 +176,12 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         acc[v] = f4{0.f, 0.f, 0.f, 0.f};
-        q[v] = q0[v] + (BITS == 4 ? m & ~15 : 0);
+        q[v] = q0[v] + (BITS == 5 ? m & ~15 : 0);
     }
     // loads come back in the order they were issued: all row numbers first,
     // so that no wait for a row number also waits for rows
     int32_t ra[16] = {}, rb[V][8] = {}, rd[V][4] = {}, re[V][2] = {}, rf[V][1] = {};
-    if (BITS == 4 && m >= 16) fetch_ids(ra, q0[0]);
+    if (BITS == 5 && m >= 16) fetch_ids(ra, q0[0]);
 #define SS_PIECES(DO_)                                                             \
     if (BITS >= 4 && (m & 8)) { DO_(rb, b, 8) }                                    \
     if (BITS >= 3 && (m & 4)) { DO_(rd, d, 4) }                                    \
@@ -197,7 +197,7 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
     // All row numbers are waited for here.  Left to the compiler, which does not know which
     // pieces were requested, the wait for a later piece's row numbers covers the rows of the
     // earlier ones.
-    if constexpr (BITS >= 4) arrived(ra);
+    if constexpr (BITS == 5) arrived(ra);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         if constexpr (BITS >= 4) arrived(rb[v]);
@@ -205,7 +205,7 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
         arrived(re[v]);
         arrived(rf[v]);
     }
-    if constexpr (BITS == 4) {
+    if constexpr (BITS == 5) {
         const int32_t *__restrict__ qa = q0[0];
         for (int left = m >> 4; left > 0; --left) {
             f4 a[16];
@@ -229,14 +229,17 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 }
 
 // The kernel for bags of L lookups: BITS of pool_bags.
-inline int bag_bits(int L) { return L < 4 ? 2 : L < 8 ? 3 : 4; }
 constexpr int kLongBag = 16;       // bags that the lookup takes with pool_bag
+inline int bag_bits(int L) { return L < 4 ? 2 : L < 8 ? 3 : L < kLongBag ? 4 : 5; }
 
-#define SS_DISPATCH_BAG(L, ...)                                 \
+#define SS_DISPATCH_SHORT_BAG(L, ...)                           \
     switch (bag_bits(L)) {                                      \
     case 2: { constexpr int BITS = 2; __VA_ARGS__; } break;     \
     case 3: { constexpr int BITS = 3; __VA_ARGS__; } break;     \
     default: { constexpr int BITS = 4; __VA_ARGS__; } break;    \
     }
+#define SS_DISPATCH_BAG(L, ...)                                 \
+    if ((L) >= kLongBag) { constexpr int BITS = 5; __VA_ARGS__; } \
+    else { SS_DISPATCH_SHORT_BAG(L, __VA_ARGS__) }
 
 }  // namespace ss
