@@ -64,13 +64,10 @@ __device__ __forceinline__ void forward_onehot_body(
     }
 }
 
-// Multi-hot bags.  All lanes of a workgroup see the same bag length, so the bag
-// is cut into pieces of 16, 8, 4, 2 and 1 lookups by scalar branches on the bits
-// of the length: every piece is straight-line code with a known number of row
-// loads, all pieces are requested before the first add (up to 31 loads in
-// flight per lane), and the rows are added in bag order.  Bags of 32 lookups or
-// more first run full rounds of 16.  FULL (a row fills its group of lanes
-// exactly) turns the row address into shifts.
+// Pieces of a multi-hot bag.  All lanes of a workgroup see the same bag length, so a bag is
+// cut into pieces of 16, 8, 4, 2 and 1 lookups by scalar branches on the bits of the length:
+// every piece is straight-line code with a known number of row loads.  FULL (a row fills its
+// group of lanes exactly) turns the row address into shifts.
 template <int N>
 __device__ __forceinline__ void fetch_ids(int32_t (&r)[N], const int32_t *__restrict__ ip)
 {
@@ -116,57 +113,18 @@ template <int N> __device__ __forceinline__ void arrived(int32_t (&r)[N])
     }
 }
 
-// Sum of the rows of a bag of m lookups at q, this lane's f4 of them, in bag order.
-template <int G, bool FULL, typename P>
-__device__ __forceinline__ f4 pool_bag(P Wc, const int32_t *__restrict__ q, int m, uint32_t d4)
-{
-    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
-    for (; m >= 32; m -= 16, q += 16) {
-        int32_t r[16];
-        f4 a[16];
-        fetch_ids(r, q);
-        fetch_rows<16, G, FULL>(a, r, Wc, d4);
-        add_rows(acc, a);
-    }
-    // loads come back in the order they were issued: all row numbers first,
-    // so that no wait for a row number also waits for rows
-    int32_t ra[16] = {}, rb[8] = {}, rd[4] = {}, re[2] = {}, rf[1] = {};
-    if (m & 16) { fetch_ids(ra, q); q += 16; }
-    if (m & 8) { fetch_ids(rb, q); q += 8; }
-    if (m & 4) { fetch_ids(rd, q); q += 4; }
-    if (m & 2) { fetch_ids(re, q); q += 2; }
-    if (m & 1) { fetch_ids(rf, q); }
-    // Without a power of two for the row length the compiler would otherwise begin with the row
-    // addresses piece by piece and wait for each piece's row numbers in turn (27.5 instead of
-    // 21.2 us at 14 tables x 5131 bags of 16 x 40 floats).
-    if (!FULL) { arrived(ra); arrived(rb); arrived(rd); arrived(re); arrived(rf); }
-    f4 a[16], b[8], d[4], e[2], f[1];
-    unset_rows(a); unset_rows(b); unset_rows(d); unset_rows(e); unset_rows(f);
-    if (m & 16) fetch_rows<16, G, FULL>(a, ra, Wc, d4);
-    if (m & 8) fetch_rows<8, G, FULL>(b, rb, Wc, d4);
-    if (m & 4) fetch_rows<4, G, FULL>(d, rd, Wc, d4);
-    if (m & 2) fetch_rows<2, G, FULL>(e, re, Wc, d4);
-    if (m & 1) fetch_rows<1, G, FULL>(f, rf, Wc, d4);
-    if (m & 16) add_rows(acc, a);
-    if (m & 8) add_rows(acc, b);
-    if (m & 4) add_rows(acc, d);
-    if (m & 2) add_rows(acc, e);
-    if (m & 1) add_rows(acc, f);
-    return acc;
-}
-
 // Sums of the rows of V bags of m lookups each, this lane's f4 of them, in bag order; q[0]
 // is a valid bag, q[v] the row numbers of bag v (of bag 0 again where there is none).  BITS:
 // m < 2^BITS, or any m with BITS = 5.  A wavefront's registers are sized for the longest bag
-// its kernel may meet: with those of pool_bag (164, 198 where rows leave lanes idle: two or
-// three wavefronts per SIMD) a bag of three keeps three loads in flight where there is room
+// its kernel may meet: with those of the lookup of long bags (164 to 168: three wavefronts
+// per SIMD) a bag of three keeps three loads in flight where there is room
 // for 31, so short bags have kernels of their own, and take several bags at once (lookup
 // kernel, us per training step: 2 tables x 32157 bags of 2, 64 floats, 56.8 instead of 60.6;
 // 5 x 29847 of 4, 208 floats, 165 instead of 191).
 // Long bags go in rounds of 16 here, with more wavefronts beside each other.  The
 // normalization wants that (3 x 12237 bags of 17, 200 floats, 11 k rows: 260 us per training
-// step, 287 with pool_bag); the lookup does not where rows come from memory (8 x 4096 bags of
-// 20, 128 floats, 10 M rows: 93 us per step, 88 with pool_bag).
+// step, 287 with up to 31 loads in flight); the lookup does not where rows come from memory
+// (8 x 4096 bags of 20, 128 floats, 10 M rows: 93 us per step, 88 with its own kernel).
 template <int G, bool FULL, int BITS, int V, typename P>
 __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ const (&q0)[V], int m,
                                           uint32_t d4, f4 (&acc)[V])
@@ -229,7 +187,7 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 }
 
 // The kernel for bags of L lookups: BITS of pool_bags.
-constexpr int kLongBag = 16;       // bags that the lookup takes with pool_bag
+constexpr int kLongBag = 16;       // bags that the lookup has a kernel of its own for
 inline int bag_bits(int L) { return L < 4 ? 2 : L < 8 ? 3 : L < kLongBag ? 4 : 5; }
 
 #define SS_DISPATCH_SHORT_BAG(L, ...)                           \
