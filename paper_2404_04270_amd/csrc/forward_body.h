@@ -115,16 +115,18 @@ template <int N> __device__ __forceinline__ void arrived(int32_t (&r)[N])
 
 // Sums of the rows of V bags of m lookups each, this lane's f4 of them, in bag order; q[0]
 // is a valid bag, q[v] the row numbers of bag v (of bag 0 again where there is none).  BITS:
-// m < 2^BITS, or any m with BITS = 5.  A wavefront's registers are sized for the longest bag
+// m < 2^BITS, or any m >= 8 with BITS = 5.  A wavefront's registers are sized for the longest bag
 // its kernel may meet: with those of the lookup of long bags (164 to 168: three wavefronts
 // per SIMD) a bag of three keeps three loads in flight where there is room
 // for 31, so short bags have kernels of their own, and take several bags at once (lookup
 // kernel, us per training step: 2 tables x 32157 bags of 2, 64 floats, 56.8 instead of 60.6;
 // 5 x 29847 of 4, 208 floats, 165 instead of 191).
-// Long bags go in rounds of 16 here, with more wavefronts beside each other.  The
-// normalization wants that (3 x 12237 bags of 17, 200 floats, 11 k rows: 260 us per training
-// step, 287 with up to 31 loads in flight); the lookup does not where rows come from memory
-// (8 x 4096 bags of 20, 128 floats, 10 M rows: 93 us per step, 88 with its own kernel).
+// Long bags go in rounds of 8 here, with more wavefronts beside each other (82 registers; 130
+// with rounds of 16).  The normalization wants that (us of its forward and its backward pass with
+// rounds of 16, of 8, and with four rows of one bag at a time as it once had them: 8 tables x 8192
+// bags of 17 x 88 floats 40.7 / 26.9 / 36.5 and 49.1 / 36.8 / 55.4, of 40 x 64 32.6 / 30.2 / 42.2
+// and 39.5 / 38.7 / 90.8); the lookup of long bags does not where rows come from memory (rounds of
+// 16: 8 x 4096 bags of 20, 128 floats, 10 M rows: 93 us per step, 88 with its own kernel).
 template <int G, bool FULL, int BITS, int V, typename P>
 __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ const (&q0)[V], int m,
                                           uint32_t d4, f4 (&acc)[V])
@@ -134,14 +136,14 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         acc[v] = f4{0.f, 0.f, 0.f, 0.f};
-        q[v] = q0[v] + (BITS == 5 ? m & ~15 : 0);
+        q[v] = q0[v] + (BITS == 5 ? m & ~7 : 0);
     }
     // loads come back in the order they were issued: all row numbers first,
     // so that no wait for a row number also waits for rows
-    int32_t ra[16] = {}, rb[V][8] = {}, rd[V][4] = {}, re[V][2] = {}, rf[V][1] = {};
-    if (BITS == 5 && m >= 16) fetch_ids(ra, q0[0]);
+    int32_t ra[8] = {}, rb[V][8] = {}, rd[V][4] = {}, re[V][2] = {}, rf[V][1] = {};
+    if (BITS == 5) fetch_ids(ra, q0[0]);
 #define SS_PIECES(DO_)                                                             \
-    if (BITS >= 4 && (m & 8)) { DO_(rb, b, 8) }                                    \
+    if (BITS == 4 && (m & 8)) { DO_(rb, b, 8) }                                    \
     if (BITS >= 3 && (m & 4)) { DO_(rd, d, 4) }                                    \
     if (m & 2) { DO_(re, e, 2) }                                                   \
     if (m & 1) { DO_(rf, f, 1) }
@@ -158,17 +160,17 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
     if constexpr (BITS == 5) arrived(ra);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        if constexpr (BITS >= 4) arrived(rb[v]);
+        if constexpr (BITS == 4) arrived(rb[v]);
         if constexpr (BITS >= 3) arrived(rd[v]);
         arrived(re[v]);
         arrived(rf[v]);
     }
     if constexpr (BITS == 5) {
         const int32_t *__restrict__ qa = q0[0];
-        for (int left = m >> 4; left > 0; --left) {
-            f4 a[16];
-            fetch_rows<16, G, FULL>(a, ra, Wc, d4);
-            qa += 16;
+        for (int left = m >> 3; left > 0; --left) {
+            f4 a[8];
+            fetch_rows<8, G, FULL>(a, ra, Wc, d4);
+            qa += 8;
             if (left > 1) fetch_ids(ra, qa);
             add_rows(acc[0], a);
         }
