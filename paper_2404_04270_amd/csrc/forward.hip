@@ -139,7 +139,7 @@ int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
 {
     const int D4 = tb->dim / 4;
     const int g = lanes_per_row(tb->dim);
-    const int bags = (kWG / g) * (L == 1 ? kOneHotBags : L < kLongBag ? bags_per_group(bag_bits(L)) : 1);
+    const int bags = (kWG / g) * (L == 1 ? kOneHotBags : bags_per_group(L < 4 ? 2 : L < 8 ? 3 : 4));
     const int tiles = (Bcap + bags - 1) / bags;
     const int64_t blocks = (int64_t)tiles * tb->num_tables;
     if (blocks > 0x7fffffffLL)
@@ -156,7 +156,7 @@ int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
            idx, Bcap, L, n_valid, out, D4, tiles, (tb->num_tables / 8) * 8 * tiles)
 #define SS_FWD(F_)                                                                     \
     SS_DISPATCH_G(g, if (L >= kLongBag) { SS_FWD1(forward_kernel, F_); }                \
-                     else { SS_DISPATCH_SHORT_BAG(L, SS_FWD1(forward_short_kernel, F_, BITS)); })
+                     else { SS_DISPATCH_LOOKUP_BAG(L, SS_FWD1(forward_short_kernel, F_, BITS)); })
         if (D4 == g) { SS_FWD(true); } else { SS_FWD(false); }
 #undef SS_FWD
 #undef SS_FWD1

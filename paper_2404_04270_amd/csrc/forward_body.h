@@ -113,20 +113,25 @@ template <int N> __device__ __forceinline__ void arrived(int32_t (&r)[N])
     }
 }
 
+constexpr int kRounds = 5;
+
 // Sums of the rows of V bags of m lookups each, this lane's f4 of them, in bag order; q[0]
 // is a valid bag, q[v] the row numbers of bag v (of bag 0 again where there is none).  BITS:
-// m < 2^BITS, or any m >= 8 with BITS = 5.  A wavefront's registers are sized for the longest bag
+// m < 2^BITS, or any m >= 8 with BITS = kRounds.  A wavefront's registers are sized for the longest bag
 // its kernel may meet: with those of the lookup of long bags (164 to 168: three wavefronts
 // per SIMD) a bag of three keeps three loads in flight where there is room
 // for 31, so short bags have kernels of their own, and take several bags at once (lookup
 // kernel, us per training step: 2 tables x 32157 bags of 2, 64 floats, 56.8 instead of 60.6;
 // 5 x 29847 of 4, 208 floats, 165 instead of 191).
-// Long bags go in rounds of 8 here, with more wavefronts beside each other (82 registers; 130
-// with rounds of 16).  The normalization wants that (us of its forward and its backward pass with
-// rounds of 16, of 8, and with four rows of one bag at a time as it once had them: 8 tables x 8192
-// bags of 17 x 88 floats 40.7 / 26.9 / 36.5 and 49.1 / 36.8 / 55.4, of 40 x 64 32.6 / 30.2 / 42.2
-// and 39.5 / 38.7 / 90.8); the lookup of long bags does not where rows come from memory (rounds of
-// 16: 8 x 4096 bags of 20, 128 floats, 10 M rows: 93 us per step, 88 with its own kernel).
+// kRounds: rounds of 8 rows, so more wavefronts beside each other (82 registers; 130 with rounds
+// of 16).  The normalization wants that (us of its forward and its backward pass with rounds of
+// 16, of 8, and with four rows of one bag at a time as it once had them: 8 tables x 8192 bags of
+// 17 x 88 floats 40.7 / 26.9 / 36.5 and 49.1 / 36.8 / 55.4, of 40 x 64 32.6 / 30.2 / 42.2 and
+// 39.5 / 38.7 / 90.8), also for bags of 8 to 15 (against all of a bag's rows at once and four at a
+// time: 2 x 59010 of 12 x 128 37.4 / 45.1 / 44.3 forward, of 15 x 200 129 / 143 / 141 backward; at
+// 8 x 1024 up to 0.6 us slower in the kernel, no slower in a stream); the lookup of long bags does
+// not where rows come from memory (rounds of 16: 8 x 4096 bags of 20, 128 floats, 10 M rows: 93 us
+// per step, 88 with its own kernel).
 template <int G, bool FULL, int BITS, int V, typename P>
 __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ const (&q0)[V], int m,
                                           uint32_t d4, f4 (&acc)[V])
@@ -136,12 +141,12 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         acc[v] = f4{0.f, 0.f, 0.f, 0.f};
-        q[v] = q0[v] + (BITS == 5 ? m & ~7 : 0);
+        q[v] = q0[v] + (BITS == kRounds ? m & ~7 : 0);
     }
     // loads come back in the order they were issued: all row numbers first,
     // so that no wait for a row number also waits for rows
     int32_t ra[8] = {}, rb[V][8] = {}, rd[V][4] = {}, re[V][2] = {}, rf[V][1] = {};
-    if (BITS == 5) fetch_ids(ra, q0[0]);
+    if (BITS == kRounds) fetch_ids(ra, q0[0]);
 #define SS_PIECES(DO_)                                                             \
     if (BITS == 4 && (m & 8)) { DO_(rb, b, 8) }                                    \
     if (BITS >= 3 && (m & 4)) { DO_(rd, d, 4) }                                    \
@@ -157,7 +162,7 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
     // All row numbers are waited for here.  Left to the compiler, which does not know which
     // pieces were requested, the wait for a later piece's row numbers covers the rows of the
     // earlier ones.
-    if constexpr (BITS == 5) arrived(ra);
+    if constexpr (BITS == kRounds) arrived(ra);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         if constexpr (BITS == 4) arrived(rb[v]);
@@ -165,7 +170,7 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
         arrived(re[v]);
         arrived(rf[v]);
     }
-    if constexpr (BITS == 5) {
+    if constexpr (BITS == kRounds) {
         const int32_t *__restrict__ qa = q0[0];
         for (int left = m >> 3; left > 0; --left) {
             f4 a[8];
@@ -188,18 +193,16 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 #undef SS_ADD_ROWS
 }
 
-// The kernel for bags of L lookups: BITS of pool_bags.
-constexpr int kLongBag = 16;       // bags that the lookup has a kernel of its own for
-inline int bag_bits(int L) { return L < 4 ? 2 : L < 8 ? 3 : L < kLongBag ? 4 : 5; }
-
-#define SS_DISPATCH_SHORT_BAG(L, ...)                           \
-    switch (bag_bits(L)) {                                      \
-    case 2: { constexpr int BITS = 2; __VA_ARGS__; } break;     \
-    case 3: { constexpr int BITS = 3; __VA_ARGS__; } break;     \
-    default: { constexpr int BITS = 4; __VA_ARGS__; } break;    \
-    }
-#define SS_DISPATCH_BAG(L, ...)                                 \
-    if ((L) >= kLongBag) { constexpr int BITS = 5; __VA_ARGS__; } \
-    else { SS_DISPATCH_SHORT_BAG(L, __VA_ARGS__) }
+// The kernel for bags of L lookups: BITS of pool_bags.  The lookup's bags of kLongBag and more
+// have a kernel of their own.
+constexpr int kLongBag = 16;
+#define SS_DISPATCH_LOOKUP_BAG(L, ...)                          \
+    if ((L) < 4) { constexpr int BITS = 2; __VA_ARGS__; }       \
+    else if ((L) < 8) { constexpr int BITS = 3; __VA_ARGS__; }  \
+    else { constexpr int BITS = 4; __VA_ARGS__; }
+#define SS_DISPATCH_LN_BAG(L, ...)                              \
+    if ((L) < 4) { constexpr int BITS = 2; __VA_ARGS__; }       \
+    else if ((L) < 8) { constexpr int BITS = 3; __VA_ARGS__; }  \
+    else { constexpr int BITS = kRounds; __VA_ARGS__; }
 
 }  // namespace ss

@@ -421,8 +421,8 @@ int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *co
     if (x) { SS_LN_FWD1(P_, kMemory, 4); }                                                   \
     else if (L == 1) { SS_LN_FWD1(P_, kOneHot, 4); }                                         \
     else if constexpr (P_ > 1) { SS_LN_FWD1(P_, kBag, 4); }                                  \
-    else if (D4 == g) { SS_DISPATCH_BAG(L, SS_LN_FWD1(1, kBagFull, BITS)); }                 \
-    else { SS_DISPATCH_BAG(L, SS_LN_FWD1(1, kBag, BITS)); }
+    else if (D4 == g) { SS_DISPATCH_LN_BAG(L, SS_LN_FWD1(1, kBagFull, BITS)); }                 \
+    else { SS_DISPATCH_LN_BAG(L, SS_LN_FWD1(1, kBag, BITS)); }
     SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_FWD(1); } else {
         if (D4 <= 64) { SS_LN_FWD(1); } else if (D4 <= 128) { SS_LN_FWD(2); } else { SS_LN_FWD(4); }
     });
@@ -460,8 +460,8 @@ int32_t launch_layernorm_backward(int T, int dim, const float *dy, const float *
     if (x) { SS_LN_BWD1(P_, kMemory, 4); }                                                   \
     else if (L == 1) { SS_LN_BWD1(P_, kOneHot, 4); }                                         \
     else if constexpr (P_ > 1) { SS_LN_BWD1(P_, kBag, 4); }                                  \
-    else if (D4 == g) { SS_DISPATCH_BAG(L, SS_LN_BWD1(1, kBagFull, BITS)); }                 \
-    else { SS_DISPATCH_BAG(L, SS_LN_BWD1(1, kBag, BITS)); }
+    else if (D4 == g) { SS_DISPATCH_LN_BAG(L, SS_LN_BWD1(1, kBagFull, BITS)); }                 \
+    else { SS_DISPATCH_LN_BAG(L, SS_LN_BWD1(1, kBag, BITS)); }
         SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_BWD(1); } else {
             if (D4 <= 64) { SS_LN_BWD(1); } else if (D4 <= 128) { SS_LN_BWD(2); } else { SS_LN_BWD(4); }
         });
