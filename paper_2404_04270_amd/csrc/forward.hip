@@ -33,7 +33,9 @@ __global__ __launch_bounds__(kWG) void forward_onehot_kernel(
     trace_end(ts, trace_t0);
 }
 
-// Bags of 16 lookups and more: all pieces are requested before the first add (up to 31 loads
+constexpr int kLongBag = 16;
+
+// Bags of kLongBag lookups and more: all pieces are requested before the first add (up to 31 loads
 // in flight per lane), and the rows are added in bag order.  Bags of 32 or more first run full
 // rounds of 16.  (The loop body stays in the kernel: as a function of its own the same text
 // compiles to piece-by-piece waits where rows leave lanes idle, 20.1 instead of 15.9 us at 14
@@ -95,17 +97,14 @@ __global__ __launch_bounds__(kWG) void forward_kernel(
     trace_end(ts, trace_t0);
 }
 
-// Bags of fewer than 2^BITS lookups (BITS = 2, 3, 4), several per lane group: about a dozen
-// rows in flight.
-constexpr int bags_per_group(int bits) { return bits == 2 ? 4 : bits == 3 ? 2 : 1; }
-
-template <int G, bool FULL, int BITS, typename TS>
+// Bags of fewer than 2^BITS lookups (BITS = 2, 3, 4), V per lane group.
+template <int G, bool FULL, int BITS, int V, typename TS>
 __global__ __launch_bounds__(kWG) void forward_short_kernel(
     const float *const *__restrict__ weights, const int32_t *__restrict__ idx,
     int Bcap, int L, const int32_t *__restrict__ n_valid,
     float *__restrict__ out, int D4, int tiles_per_table, int pinned_blocks, TS ts)
 {
-    constexpr int GROUPS = kWG / G, V = bags_per_group(BITS);
+    constexpr int GROUPS = kWG / G;
     const unsigned long long trace_t0 = trace_begin<TS>();
     int t, tile;
     block_to_table_pinned(blockIdx.x, tiles_per_table, pinned_blocks, t, tile);
@@ -139,7 +138,15 @@ int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
 {
     const int D4 = tb->dim / 4;
     const int g = lanes_per_row(tb->dim);
-    const int bags = (kWG / g) * (L == 1 ? kOneHotBags : bags_per_group(L < 4 ? 2 : L < 8 ? 3 : 4));
+    const int groups = kWG / g;
+    // Bags of a lane group.  Two of fewer than 8 lookups where that leaves four workgroups per
+    // compute unit (us of the kernel with one, two and four per group, bags of 2 or 3, and before
+    // the kernels for short bags: 26 tables x 2000 x 36 floats 6.3 / 5.7 / 6.1, then 8.7; 5 x 20000
+    // x 208 31.8 / 28.2 / 29.4, 54; but 5 x 777 x 36 4.2 / 4.1 / 4.2, 4.1; 1 x 777 x 1024 4.7 / 5.2
+    // / 6.7, 4.6; 1 x 6000 x 208 4.6 / 4.9 / 4.8, 4.5).
+    const bool two = L > 1 && L < 8 &&
+                     (int64_t)tb->num_tables * ((Bcap + groups - 1) / groups) >= 2048;
+    const int bags = groups * (L == 1 ? kOneHotBags : two ? 2 : 1);
     const int tiles = (Bcap + bags - 1) / bags;
     const int64_t blocks = (int64_t)tiles * tb->num_tables;
     if (blocks > 0x7fffffffLL)
@@ -156,7 +163,11 @@ int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
            idx, Bcap, L, n_valid, out, D4, tiles, (tb->num_tables / 8) * 8 * tiles)
 #define SS_FWD(F_)                                                                     \
     SS_DISPATCH_G(g, if (L >= kLongBag) { SS_FWD1(forward_kernel, F_); }                \
-                     else { SS_DISPATCH_LOOKUP_BAG(L, SS_FWD1(forward_short_kernel, F_, BITS)); })
+                     else if (L >= 8) { SS_FWD1(forward_short_kernel, F_, 4, 1); }      \
+                     else if (L >= 4 && two) { SS_FWD1(forward_short_kernel, F_, 3, 2); } \
+                     else if (L >= 4) { SS_FWD1(forward_short_kernel, F_, 3, 1); }      \
+                     else if (two) { SS_FWD1(forward_short_kernel, F_, 2, 2); }         \
+                     else { SS_FWD1(forward_short_kernel, F_, 2, 1); })
         if (D4 == g) { SS_FWD(true); } else { SS_FWD(false); }
 #undef SS_FWD
 #undef SS_FWD1

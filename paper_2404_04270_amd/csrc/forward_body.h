@@ -120,9 +120,9 @@ constexpr int kRounds = 5;
 // m < 2^BITS, or any m >= 8 with BITS = kRounds.  A wavefront's registers are sized for the longest bag
 // its kernel may meet: with those of the lookup of long bags (164 to 168: three wavefronts
 // per SIMD) a bag of three keeps three loads in flight where there is room
-// for 31, so short bags have kernels of their own, and take several bags at once (lookup
-// kernel, us per training step: 2 tables x 32157 bags of 2, 64 floats, 56.8 instead of 60.6;
-// 5 x 29847 of 4, 208 floats, 165 instead of 191).
+// for 31, so short bags have kernels of their own (the lookup kernel at 2 tables x 32157 bags
+// of 2 x 64 floats 6.2 instead of 10.0 us, 5 x 29847 of 4 x 208 56 instead of 90), and in large
+// launches of the lookup two bags per lane group.
 // kRounds: rounds of 8 rows, so more wavefronts beside each other (82 registers; 130 with rounds
 // of 16).  The normalization wants that (us of its forward and its backward pass with rounds of
 // 16, of 8, and with four rows of one bag at a time as it once had them: 8 tables x 8192 bags of
@@ -193,13 +193,7 @@ __device__ __forceinline__ void pool_bags(P Wc, const int32_t *__restrict__ cons
 #undef SS_ADD_ROWS
 }
 
-// The kernel for bags of L lookups: BITS of pool_bags.  The lookup's bags of kLongBag and more
-// have a kernel of their own.
-constexpr int kLongBag = 16;
-#define SS_DISPATCH_LOOKUP_BAG(L, ...)                          \
-    if ((L) < 4) { constexpr int BITS = 2; __VA_ARGS__; }       \
-    else if ((L) < 8) { constexpr int BITS = 3; __VA_ARGS__; }  \
-    else { constexpr int BITS = 4; __VA_ARGS__; }
+// The normalization's kernel for bags of L lookups: BITS of pool_bags.
 #define SS_DISPATCH_LN_BAG(L, ...)                              \
     if ((L) < 4) { constexpr int BITS = 2; __VA_ARGS__; }       \
     else if ((L) < 8) { constexpr int BITS = 3; __VA_ARGS__; }  \
