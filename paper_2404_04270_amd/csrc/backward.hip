@@ -564,7 +564,9 @@ __device__ __forceinline__ const f4 *grad_ptr(const f4 *table_base, uint32_t smp
 // strip order (column c of a lane group of G); *ended: whether it ends in this workgroup.
 // The hot rows' runs cross all strips, 64 of them where a row is 64 bytes: taken one at a time
 // each costs a trip to LDS for its state and one for its sum, so eight are requested together
-// (26 tables x 2048 lookups of 64 bytes: the kernel takes 7.0 instead of 9.4 us).  With 16 strips
+// (26 tables x 2048 lookups of 64 bytes: the kernel takes 7.0 instead of 9.4 us), after the first
+// one alone: a run that is not a hot row's mostly ends there (update of 8 tables x 8192 uniform
+// lookups of 64 bytes 9.3 us, 10.0 with eight at once, 8.9 with one at a time).  With 16 strips
 // or fewer the registers cost more than the trips (14 tables x 82096 lookups of 160 bytes: 41.4
 // us, 40.1 one at a time; a training step with 26 x 8192 of 256 bytes: 46.8 and 46.3).
 template <int G, int NG>
@@ -573,6 +575,11 @@ __device__ __forceinline__ f4 stitch(f4 sum, const f4 *s_lead, const uint8_t *s_
 {
     constexpr int U = NG > 16 ? 8 : 1;
     bool open = true;
+    if (U > 1 && q < NG) {               // most runs end in the next strip
+        sum = sum + s_lead[q * G + c];
+        open = s_lead_state[q] != 1;
+        ++q;
+    }
     for (; open && q < NG; q += U) {
         f4 v[U];
         uint8_t st[U];
