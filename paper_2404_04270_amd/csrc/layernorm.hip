@@ -178,15 +178,15 @@ template <int G, int P, XFrom FROM, int BITS>
 __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     XSource src, int Bcap, const int32_t *__restrict__ n_valid,
     const float *__restrict__ gamma, const float *__restrict__ beta, float eps,
-    float *y, float *__restrict__ mean, float *__restrict__ rstd, int D4,
-    int tiles_per_table)
+    float *y, float *__restrict__ mean, float *__restrict__ rstd, int D4)
 {
     constexpr int NG = kWG / G, V = ln_fwd_vectors<P, FROM>();
-    const int t = blockIdx.x / tiles_per_table;
-    const int tile = blockIdx.x - t * tiles_per_table;
+    const int t = blockIdx.y;
+    const int64_t tile = blockIdx.x + (int64_t)blockIdx.z * gridDim.x;
     const int n = clamp_valid(n_valid, Bcap);
     const int g = threadIdx.x / G, c = threadIdx.x % G;
-    const int j0 = tile * NG * V + g;         // vectors j0 + k * NG
+    if (tile * NG * V >= n) return;
+    const int j0 = (int)tile * NG * V + g;    // vectors j0 + k * NG
     if (j0 >= n) return;                      // whole groups leave together
     const float inv_d = 1.0f / (float)(D4 * 4);
 
@@ -371,6 +371,7 @@ __global__ __launch_bounds__(kWG) void ln_param_reduce_kernel(
 // (bags of 20) takes 27.7 or 30.2 us instead of 25.9.
 constexpr int kLnMaxTiles = 8;
 constexpr int kLnMinWgs = 512;
+constexpr int kMaxTiles = 1 << 23;           // forward: workgroups of a table in one grid dimension
 
 struct BackwardPlan {
     int tiles, wgs;
@@ -413,10 +414,14 @@ int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *co
     const int tiles = (Bcap + per_tile - 1) / per_tile;
     if ((int64_t)tiles * T > 0x7fffffffLL)
         return fail(SS_ERR_UNSUPPORTED, "ss_layernorm_forward: grid too large");
+    // A launch's threads in one dimension are counted in 32 bits (without an error: the rest of
+    // the grid does not run), and one vector per lane group takes 2^24 workgroups for 64 GiB of y.
+    const int slices = (tiles - 1) / kMaxTiles + 1;
+    const dim3 grid((unsigned)((tiles - 1) / slices + 1), T, slices);
     ProfScope prof(x ? "ln_forward_kernel" : "ln_forward_pool_kernel", s);
 #define SS_LN_FWD1(P_, F_, BITS_)                                                                 \
-    launch(ln_forward_kernel<G, P_, F_, BITS_>, dim3((unsigned)(tiles * T)), dim3(kWG), s, src, Bcap, \
-           n_valid, gamma, beta, eps, y, mean, rstd, D4, tiles)
+    launch(ln_forward_kernel<G, P_, F_, BITS_>, grid, dim3(kWG), s, src, Bcap, n_valid, gamma, \
+           beta, eps, y, mean, rstd, D4)
 #define SS_LN_FWD(P_)                                                                        \
     if (x) { SS_LN_FWD1(P_, kMemory, 4); }                                                   \
     else if (L == 1) { SS_LN_FWD1(P_, kOneHot, 4); }                                         \
