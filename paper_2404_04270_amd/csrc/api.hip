@@ -39,8 +39,14 @@ int32_t check_tables(const ss_tables *tb, const char *who)
     return SS_OK;
 }
 
+thread_local bool t_grid_refused = false;
+
 int32_t check_launch(const char *who)
 {
+    if (t_grid_refused) {
+        t_grid_refused = false;
+        return fail(SS_ERR_UNSUPPORTED, "%s: grid too large", who);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail(SS_ERR_HIP, "%s: %s", who, hipGetErrorString(e));

@@ -114,11 +114,18 @@ __device__ __forceinline__ void trace_end(TraceSlot ts, unsigned long long t0)
 void stop_event_for_next_launch(hipEvent_t ev);
 hipEvent_t take_stop_event();
 
+// The GPU counts a launch's threads per dimension in 32 bits, and the runtime lets a larger grid
+// through with its size wrapped: part of the work would silently not be done.  Such a launch is
+// left out, as are those that follow it, until check_launch() reports it.
+extern thread_local bool t_grid_refused;
+
 template <typename K, typename... Args>
 inline void launch_with_events(K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args)
 {
     hipEvent_t e0, e1;
     const hipEvent_t stop = take_stop_event();
+    if ((uint64_t)grid.x * block.x > 0xFFFFFFFFull) t_grid_refused = true;
+    if (t_grid_refused) return;
     if (prof_events(&e0, &e1)) {
         hipExtLaunchKernelGGL(kernel, grid, block, 0, s, e0, e1, 0, args...);
         if (stop) (void)hipEventRecord(stop, s);
