@@ -23,10 +23,11 @@
 // two passes move.  One-hot bags have a form of their own (one load of the row
 // number and one of the row per vector, those of 4 or 2 vectors together, where
 // the bag loop asked for four rows of one bag and then waited): 21.1 instead of
-// 28.0 us forward, 25.1 instead of 30.8 backward at 26 x 8192 x 64.  The forward
-// pass streams y past the caches as the plain lookup does.  Multi-hot bags are
-// pooled by the lookup kernel's own code: 29.0 instead of 33.7 us forward, 25.9
-// instead of 49.0 backward at 8 tables x 4096 bags of 20 x 128.
+// 28.0 us forward, 25.1 instead of 30.8 backward at 26 x 8192 x 64.  Bags of
+// several lookups are pooled by pool_bags (rows of at most 256 floats: all rows
+// of a bag of up to 7 at once, longer ones in rounds of 8): 19.9 instead of 25.8
+// us forward, 27.5 instead of 49.1 backward at 8 tables x 4096 bags of 20 x 128.
+// Longer rows keep the loop that asks for four rows of a bag at a time.
 #include "forward_body.h"
 #include "ss_common.h"
 
@@ -174,7 +175,7 @@ template <int P, XFrom FROM> constexpr int ln_fwd_vectors()
     return P > 1 || FROM == kBag || FROM == kBagFull ? 1 : 4;
 }
 
-template <int G, int P, XFrom FROM, int BITS>
+template <int G, int P, XFrom FROM, int BITS, bool STREAM>
 __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     XSource src, int Bcap, const int32_t *__restrict__ n_valid,
     const float *__restrict__ gamma, const float *__restrict__ beta, float eps,
@@ -218,8 +219,8 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
                 f4 o = v[k][i] * rs;
                 if (gamma) o = o * reinterpret_cast<const f4 *>(gamma)[(int64_t)t * D4 + col];
                 if (beta) o = o + reinterpret_cast<const f4 *>(beta)[(int64_t)t * D4 + col];
-                if (FROM == kMemory) yp[col] = o;
-                else __builtin_nontemporal_store(o, &yp[col]);
+                if (STREAM) __builtin_nontemporal_store(o, &yp[col]);
+                else yp[col] = o;
             }
         }
         if (c == 0) {
@@ -418,21 +419,32 @@ int32_t launch_layernorm_forward(int T, int dim, const float *x, const float *co
     // the grid does not run), and one vector per lane group takes 2^24 workgroups for 64 GiB of y.
     const int slices = (tiles - 1) / kMaxTiles + 1;
     const dim3 grid((unsigned)((tiles - 1) / slices + 1), T, slices);
+    // y is streamed past the caches where it would not stay in the L2s anyway: whoever reads it
+    // next (the dense model) then loses nothing, and the tables' rows are not pushed out.  us per
+    // training step, streamed and not, in a graph: 26 x 32768 x 64 (218 MB) with nobody reading y
+    // 280 / 291, with a scaling of it 356 / 363, a transposing copy 377 / 388, a concatenation of
+    // its tables 382 / 389; 26 x 8192 x 64 (54 MB) 75.6 / 81.2, 99.0 / 100.8, 104.7 / 108.7, 108.5 /
+    // 107.1; 26 x 2048 x 64 (14 MB) 39.2 / 40.4, 45.0 / 45.7, 48.3 / 48.5, 47.8 / 46.8; 26 x 512 x 64
+    // (3 MB) 28.9 / 29.0, 32.1 / 32.2, 33.8 / 33.6, 35.7 / 34.4.
+    const bool stream_y = !x && (int64_t)T * Bcap * dim * 4 >= 32 << 20;
     ProfScope prof(x ? "ln_forward_kernel" : "ln_forward_pool_kernel", s);
-#define SS_LN_FWD1(P_, F_, BITS_)                                                                 \
-    launch(ln_forward_kernel<G, P_, F_, BITS_>, grid, dim3(kWG), s, src, Bcap, n_valid, gamma, \
-           beta, eps, y, mean, rstd, D4)
+#define SS_LN_FWD2(P_, F_, BITS_, S_)                                                        \
+    launch(ln_forward_kernel<G, P_, F_, BITS_, S_>, grid, dim3(kWG), s, src, Bcap, n_valid,  \
+           gamma, beta, eps, y, mean, rstd, D4)
+#define SS_LN_FWD1(P_, F_, BITS_)                                                            \
+    if (stream_y) { SS_LN_FWD2(P_, F_, BITS_, true); } else { SS_LN_FWD2(P_, F_, BITS_, false); }
 #define SS_LN_FWD(P_)                                                                        \
-    if (x) { SS_LN_FWD1(P_, kMemory, 4); }                                                   \
+    if (x) { SS_LN_FWD2(P_, kMemory, 4, false); }                                            \
     else if (L == 1) { SS_LN_FWD1(P_, kOneHot, 4); }                                         \
     else if constexpr (P_ > 1) { SS_LN_FWD1(P_, kBag, 4); }                                  \
-    else if (D4 == g) { SS_DISPATCH_LN_BAG(L, SS_LN_FWD1(1, kBagFull, BITS)); }                 \
+    else if (D4 == g) { SS_DISPATCH_LN_BAG(L, SS_LN_FWD1(1, kBagFull, BITS)); }              \
     else { SS_DISPATCH_LN_BAG(L, SS_LN_FWD1(1, kBag, BITS)); }
     SS_DISPATCH_G(g, if constexpr (G < 64) { SS_LN_FWD(1); } else {
         if (D4 <= 64) { SS_LN_FWD(1); } else if (D4 <= 128) { SS_LN_FWD(2); } else { SS_LN_FWD(4); }
     });
 #undef SS_LN_FWD
 #undef SS_LN_FWD1
+#undef SS_LN_FWD2
     return check_launch("ss_layernorm_forward");
 }
 
