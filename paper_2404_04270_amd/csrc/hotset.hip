@@ -26,7 +26,7 @@
 // "equal to c", and their bits per 4096 rows; the last step works on these
 // bitmaps, a sixteenth of the counters: every workgroup adds up what lies
 // before its 32768 rows, ranks its bits, and writes ids in ascending order and
-// the bitmap.  26 x 1 M rows: histogram 32 us (and 3 x 1.5), bitmaps 18, ids 7, instead of
+// the bitmap.  26 x 1 M rows: histogram 28 us (and 3 x 1.2), bitmaps 18, ids 5, instead of
 // four histogram passes of 34 us with 5 us each to pick a digit, 25 to count, 54 to write;
 // one table of 200 M rows 0.39 instead of 3.2 ms.
 #include "ss_common.h"
@@ -49,9 +49,9 @@ constexpr int kBins = (int)kExact + ((32 - kExactBits) << kSubBits);
 constexpr int kRefine = 3;               // passes that split a bin, kExactBits each
 
 // NT threads with ITEMS lookups each, all requested before the first is counted.  What
-// bounds it is the rate of adds to memory (about 30 per nanosecond): fewer, the
-// more lookups share an LDS table; but a small batch wants many short workgroups, each of
-// which is one chain of trips to memory (row ids, LDS slots, counters).
+// bounds it is the rate of adds to memory (about 30 per nanosecond, far fewer to rows next to
+// each other): fewer, the more lookups share an LDS table; but few lookups want many short
+// workgroups, each of which is one chain of trips to memory (row ids, LDS slots, counters).
 template <int NT, int ITEMS, int SLOTS>
 __global__ __launch_bounds__(NT) void count_kernel(
     const int32_t *__restrict__ idx, int Bcap, int L, const int32_t *__restrict__ n_valid,
@@ -538,18 +538,20 @@ int32_t launch_count_accesses(int T, const int32_t *idx, int Bcap, int L,
     const int64_t nnz = (int64_t)Bcap * L;
     if (nnz == 0) return SS_OK;
     const auto chunks = [&](int per) { return (nnz + per - 1) / per; };
-    if (chunks(512) * T > 0x7fffffffLL)
+    if (chunks(2048) * T > 0x7fffffffLL)
         return fail(SS_ERR_UNSUPPORTED, "ss_count_accesses: grid too large");
     ProfScope prof("count_kernel", s);
 #define SS_COUNT(NT_, I_, SLOTS_)                                                            \
     launch(count_kernel<NT_, I_, SLOTS_>, dim3((unsigned)(chunks(NT_ * I_) * T)), dim3(NT_), s, \
            idx, Bcap, L, n_valid, counts, (int)chunks(NT_ * I_))
-    // Rule (us; 256 x 2 / 1024 x 2 / 1024 x 8 lookups per workgroup): 26 tables x 163840 lookups
-    // 85 / 61 / 51, x 40000 21.5 / 17.7 / 15.7, x 20000 11.8 / 9.9 / 10.6; 5 x 60000 8.6 / 6.8 /
-    // 9.0; 26 x 8192 5.9 / 5.8 / 9.6; 1 x 65536 4.8 / 5.5 / 11.4.
-    if (chunks(8192) * T >= 100) SS_COUNT(1024, 8, 8192);
-    else if (chunks(2048) * T >= 128) SS_COUNT(1024, 2, 4096);
-    else SS_COUNT(256, 2, 1024);
+    // Rule (us; 1024 x 2 and 1024 x 8 lookups per workgroup, popular rows next to each other / scattered
+    // over the table, and 2048 lookups by 256 threads as it once was): 8 tables x 81920 36.0 / 17.1
+    // and 21.8 / 15.7, 36.9 / 18.3; 40 x 16384 19.0 / 13.5 and 14.5 / 13.3, 20.0 / 14.5; 26 x 16384
+    // 13.5 / 11.8 and 12.6 / 12.1, 13.7 / 12.2; 26 x 8192 8.7 / 6.7 and 10.2 / 10.0, 9.5 / 8.3;
+    // 1 x 65536 12.5 / 4.6 and 10.2 / 10.2, 14.2 / 6.3.  (Smaller workgroups send the same popular
+    // rows to memory more often: 512 lookups each take 29.8 / 4.9 at 1 x 65536.)
+    if (nnz * T >= 64 * 8192) SS_COUNT(1024, 8, 8192);
+    else SS_COUNT(1024, 2, 4096);
 #undef SS_COUNT
     return check_launch("ss_count_accesses");
 }
