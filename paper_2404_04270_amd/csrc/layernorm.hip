@@ -230,9 +230,9 @@ __global__ __launch_bounds__(kWG) void ln_forward_kernel(
     }
 }
 
-// Workgroup b of a table takes vectors [b * NG * tiles, (b+1) * NG * tiles); group g
-// takes every NG-th of them, V at a time (tiles is a multiple of V).  Partial parameter gradients: one row
-// of dim floats per workgroup for dgamma and one for dbeta.
+// Workgroup b of a table takes vectors [b * NG * tiles, (b+1) * NG * tiles); group g takes
+// every NG-th of them, V at a time (tiles is a multiple of V).  Partial parameter gradients:
+// one row of dim floats per workgroup for dgamma and one for dbeta.
 template <int P, XFrom FROM> constexpr int ln_bwd_vectors()
 {
     return P > 1 || FROM == kBag || FROM == kBagFull ? 1 : 2;

@@ -303,7 +303,7 @@ int32_t launch_count_accesses(int T, const int32_t *idx, int Bcap, int L,
                               hipStream_t s);
 size_t select_hot_ws_bytes(int T, int64_t R);
 // Rows with count > c, and the first e rows (by id) with count == c; with `top`
-// set, c and e are first replaced by the outcome of a radix select for the e
+// set, c and e are first replaced by the outcome of a search for the e
 // largest counts.
 int32_t launch_select_hot(int T, int64_t R, uint32_t *const *counts, bool top, uint32_t c,
                           uint32_t e, int32_t *const *hot_ids, int cap,

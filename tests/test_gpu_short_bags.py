@@ -1,6 +1,6 @@
-"""Lookup of short bags at the edges of how its kernels cut their work: bags below 4 (four per
-lane group, with remainders), below 8 (two per group), below 16, and from there on; rows that
-fill their lanes and rows that do not, rows of more than 64 f4; n_valid inside a tile.  And
+"""Lookup of short bags at the edges of how its kernels cut their work: bags below 4, below 8,
+below 16, and from there on, in launches of one bag per lane group; rows that fill their lanes
+and rows that do not, rows of more than 64 f4; n_valid inside a tile.  And
 ss_sample_drop for inputs of at most four lookups, which one lane each takes.
 
 The lookup adds rows in bag order in fp32, so numpy's fp32 sum in that order is bit for bit the
