@@ -117,12 +117,12 @@ constexpr int kRounds = 5;
 
 // Sums of the rows of V bags of m lookups each, this lane's f4 of them, in bag order; q[0]
 // is a valid bag, q[v] the row numbers of bag v (of bag 0 again where there is none).  BITS:
-// m < 2^BITS, or any m >= 8 with BITS = kRounds.  A wavefront's registers are sized for the longest bag
-// its kernel may meet: with those of the lookup of long bags (164 to 168: three wavefronts
-// per SIMD) a bag of three keeps three loads in flight where there is room
-// for 31, so short bags have kernels of their own (the lookup kernel at 2 tables x 32157 bags
-// of 2 x 64 floats 6.2 instead of 10.0 us, 5 x 29847 of 4 x 208 56 instead of 90), and in large
-// launches of the lookup two bags per lane group.
+// m < 2^BITS, or any m >= 8 with BITS = kRounds.  A wavefront's registers are sized for the
+// longest bag its kernel may meet: with those of the lookup of long bags (164 to 168: three
+// wavefronts per SIMD) a bag of three keeps three loads in flight where there is room for 31,
+// so short bags have kernels of their own (the lookup kernel at 2 tables x 32157 bags of 2 x 64
+// floats 6.2 instead of 10.0 us, 5 x 29847 of 4 x 208 56 instead of 90), and in large launches
+// of the lookup two bags per lane group.
 // kRounds: rounds of 8 rows, so more wavefronts beside each other (82 registers; 130 with rounds
 // of 16).  The normalization wants that (us of its forward and its backward pass with rounds of
 // 16, of 8, and with four rows of one bag at a time as it once had them: 8 tables x 8192 bags of
