@@ -253,13 +253,19 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
         } else {
             // With 64 inputs each there are S / 64 workgroups, and a lane of eight wavefronts has
             // TL / 32 rounds of searches before it.  Where both leave the chip waiting an input
-            // gets 4 or 16 lanes of every wavefront (us with 64 / 16 / 4 inputs per workgroup,
-            // 5000 hot rows: 1000 inputs of 1280 lookups 267 / 80 / 41, 3000 of 1280 280 / 107 /
-            // 109, 1000 of 48 19.4 / 9.9 / 9.0, 5950 of 520 121 / 91 / 99, 12000 of 520 132 / 156 /
-            // 191; 100 hot rows, 3000 of 1280: 131 / 44 / 30).
+            // gets 4 or 16 lanes of every wavefront.  us with 64 / 16 / 4 inputs per workgroup, and
+            // with a group of lanes per input and no regard to tables as it once was, 5000 hot rows
+            // next to each other and Zipf lookups; the same scattered and uniform:
+            //    2000 inputs of 1280   208 / 63 / 32, 42        275 / 89 / 76, 102
+            //    9000 of 1280          227 / 152 / 122, 135     277 / 325 / 306, 408
+            //    4096 of 520           76 / 28 / 31, 41         116 / 58 / 68, 98
+            //    9000 of 520           88 / 64 / 63, 77         125 / 137 / 144, 200
+            //   12000 of 520           94 / 65 / 81, 99         131 / 158 / 190, 261
+            //   16000 of 520           95 / 80 / 102, 125       144 / 207 / 249, 347
+            //    5950 of 104           23 / 14 / 19, 22         32 / 24 / 27, 37
             int I = 64;
-            if (S < 8192 && TL > kMaxWaves * kBatch) I = 16;
-            if (S < 4096 && TL > kMaxWaves * kBatch * 4) I = 4;
+            if (TL > kMaxWaves * kBatch && S <= 12288) I = 16;
+            if ((TL > kMaxWaves * kBatch * 4 && S <= 4096) || (TL > 1024 && S <= 16384)) I = 4;
             const int per_wave = kBatch * (64 / I);
             int waves = (TL + per_wave - 1) / per_wave;
             if (waves > kMaxWaves) waves = kMaxWaves;

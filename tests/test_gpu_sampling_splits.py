@@ -1,5 +1,5 @@
 """ss_sample_drop where an input is split over several lanes of a wavefront: 64, 16 and 4 inputs
-per workgroup (samples of fewer than 8192 and 4096 inputs, inputs of more than 32 and 128
+per workgroup (samples of up to 12288, 4096 and 16384 inputs, inputs of more than 32, 128 and 1024
 lookups), at and beside those borders, with remainders of every size.  Integer counts, held to
 exact equality with numpy.
 """
@@ -53,7 +53,9 @@ def test_few_inputs(T, L, S):
 
 
 @pytest.mark.parametrize("T,L,S", [(3, 43, 4095), (3, 43, 4096), (3, 11, 4095), (3, 11, 8191),
-                                   (3, 11, 8192), (4, 8, 8191)])
+                                   (3, 11, 8192), (4, 8, 8191), (3, 43, 4097), (3, 11, 12_288),
+                                   (3, 11, 12_289), (33, 32, 4097), (41, 25, 16_384),
+                                   (41, 25, 16_385), (32, 32, 4097)])
 def test_borders_of_the_sample_size(T, L, S):
     check(T, L, S)
 
