@@ -485,13 +485,14 @@ __global__ __launch_bounds__(kWG) void sel_write_kernel(
     // Many: the wavefront writes two words' ids at a time, one lane per row.
     const uint32_t wave_row0 = (uint32_t)(word0 - lane * 4) * 32u;
     const uint32_t below = lane & 31 ? ~0u >> (32 - (lane & 31)) : 0u;
-    for (int j = 0; j < 64; ++j) {
+    for (int j0 = 0; j0 < 64; j0 += 4) {
+        if (__builtin_amdgcn_readlane(pos[0], j0) >= (uint32_t)cap) return;     // as all that follow
 #pragma unroll
-        for (int k = 0; k < 4; k += 2) {
+        for (int i = 0; i < 8; ++i) {
+            const int j = j0 + i / 2, k = (i & 1) * 2;
             const uint32_t lo = __builtin_amdgcn_readlane(take[k], j);
             const uint32_t hi = __builtin_amdgcn_readlane(take[k + 1], j);
             const uint32_t p0 = __builtin_amdgcn_readlane(pos[k], j);
-            if (p0 >= (uint32_t)cap) return;             // so are all that follow
             const uint32_t mine = lane < 32 ? lo : hi;
             const uint32_t p = p0 + (lane < 32 ? 0u : (uint32_t)__popc(lo)) + __popc(mine & below);
             if ((mine >> (lane & 31)) & 1u && p < (uint32_t)cap)
