@@ -414,9 +414,9 @@ int32_t ss_embbag_forward_grouped(const ss_tables *tables, const int32_t *idx,
     if (rc) return rc;
     if (can_fuse_forward_group(tables, Bcap, L)) {
         uint2 *ent;
-        int NP;
-        backward_first_buffers(tables->num_tables, Bcap, L, tables->dim, bwd_ws, &ent, &NP);
-        return launch_forward_group(tables, idx, Bcap, n_valid, out, ent, NP, s);
+        int NP, fill;
+        backward_first_buffers(tables->num_tables, Bcap, L, tables->dim, bwd_ws, &ent, &NP, &fill);
+        return launch_forward_group(tables, idx, Bcap, n_valid, out, ent, NP, fill, s);
     }
     rc = launch_forward(tables, idx, Bcap, L, n_valid, out, s);
     if (rc) return rc;

@@ -8,9 +8,8 @@
 //     run).  The lists hold (row, sample) pairs: the sample number is all the
 //     gradient gather needs.
 //       - up to 16384 lookups per table: one launch; the table is cut into
-//         classes by the low bits of the row id and a 1024-thread workgroup per
-//         class runs an LSD radix sort on the remaining bits with keys and
-//         sample numbers in registers and the exchange buffers in LDS;
+//         classes by a hash of the row id and a workgroup per class groups its
+//         lookups in LDS (group_body.h), without sorting them;
 //       - more: one pass of a global LSD radix sort on the low bits (two
 //         launches: per-tile digit histograms, then a stable scatter whose
 //         workgroups each derive their own offsets from the histograms; the
@@ -21,8 +20,8 @@
 //       - row ids of 10 bits or fewer with that many lookups: the one global
 //         pass is all it takes (further passes of the same kind exist for row
 //         ids whose remaining bits would not leave a bucket anything to sort).
-//     A lookup whose row is stale is given the sentinel key when the keys are
-//     first read, so it sorts behind all real lookups and costs nothing later.
+//     A lookup whose row is stale becomes a sentinel behind the real lookups of its
+//     class or table before any later stage sees it, and costs nothing there.
 //     Ranking inside a wavefront uses ballots: the lanes that hold the same
 //     digit are found with one ballot per digit bit, a popcount of the lower
 //     lanes gives the rank, and one lane per digit bumps the wavefront's LDS
@@ -70,16 +69,16 @@ constexpr int kApplyWG = 256;           // apply stage: threads per workgroup (5
 
 // Stage 1a (class sort, one launch for up to 16384 lookups per table) lives in
 // group_body.h, shared with the fused forward + grouping launch.
-template <int ITEMS, bool PACKED, typename TS>
-__global__ __launch_bounds__(1024) void class_sort_kernel(
+template <int NT, int ITEMS, bool PACKED, typename TS>
+__global__ __launch_bounds__(NT) void class_sort_kernel(
     const int32_t *__restrict__ idx, int Bcap, int L,
     const int32_t *__restrict__ n_valid, const uint32_t *const *__restrict__ bits,
-    int key_bits, int class_bits, int val_bits, uint2 *__restrict__ out_ent, int NP,
+    int key_bits, int class_bits, int pos_bits, uint2 *__restrict__ out_ent, int NP, int fill,
     TS ts)
 {
     const unsigned long long trace_t0 = trace_begin<TS>();
-    class_sort_body<ITEMS, PACKED>(blockIdx.x, blockIdx.y, idx, Bcap, L, n_valid, bits,
-                                   key_bits, class_bits, val_bits, out_ent, NP);
+    class_sort_body<NT, ITEMS, PACKED>(blockIdx.x, blockIdx.y, idx, Bcap, L, n_valid, bits,
+                                   key_bits, class_bits, pos_bits, out_ent, NP, fill);
     trace_end(ts, trace_t0);
 }
 
@@ -642,18 +641,20 @@ __global__ __launch_bounds__(kApplyWG) void apply_kernel(
     // only the last group looks at it: does its last run come from an earlier workgroup?
     const uint32_t before_wg = (g == NG - 1 && wg_base > 0) ? ep[wg_base - 1].x : kNoPrev;
 
-    // Stale and padding lookups carry the sentinel key, the largest there is:
-    // they form the last run of the table, which never ends and is never stored.
+    // Stale and padding lookups carry the sentinel key: runs of it lie between the classes of
+    // the one-launch sort and behind the table's last row, and are never stored.
     // Their second word is a valid sample number, so gradient loads need no guard.
     //   end[i]: a run ends at lookup i;  put[i]: ... and it began in this strip,
-    //   so its sum is complete here and the row is updated right away.
+    //   so its sum is complete here and the row is updated right away;  came[i]: ... and it
+    //   came in from the left.
     const bool cont = row[0] == prev;       // the first run began before the strip
-    bool end[S], put[S];
+    bool end[S], put[S], came[S];
     bool open = cont;
 #pragma unroll
     for (int i = 0; i < S; ++i) {
         end[i] = (i < S - 1 ? row[i + 1] : next) != row[i];
         put[i] = end[i] && !open && row[i] != kNoRow;
+        came[i] = end[i] && open;
         open = open && !end[i];
     }
     const bool through = open;              // one run covers the strip and goes on
@@ -700,8 +701,7 @@ __global__ __launch_bounds__(kApplyWG) void apply_kernel(
             acc = end[i] ? f4{0.f, 0.f, 0.f, 0.f} : acc;
             if (put[i] && active)
                 *row_ptr<G, FULL>(Wc, row[i], d4) = sgd(wv[i], run, lr);
-            // the only other run that can end is the one that came in from the left
-            if (end[i] && !put[i]) s_lead[tid] = run;
+            if (came[i]) s_lead[tid] = run;
         }
         if (through) s_lead[tid] = acc;
         __syncthreads();
@@ -907,6 +907,13 @@ __global__ __launch_bounds__(kWG) void fixup_kernel(
     trace_end(ts, trace_t0);
 }
 
+// Strip length (lookups per lane group in the apply stage), as measured: 4 for
+// rows of 256 bytes (18.3 against 18.8 us at 26 tables x 8192 lookups), 8 for
+// longer rows (40.2 against 42.1 us at 8 tables x 81920 lookups of 512 bytes:
+// fewer pieces to stitch) and for shorter ones (8.3 against 10.2 us at 26 tables
+// x 2048 lookups of 64 bytes, where a workgroup holds 64 groups).
+int pick_strip(int lanes_per_group) { return lanes_per_group == 16 ? 4 : 8; }
+
 struct Layout {
     int NP, tiles, max_wgs;
     size_t ent0, ent1, hist, bucket, trail_row, lead_state, part_lead,
@@ -954,12 +961,15 @@ int key_bits_for(int64_t rows)
 // pieces: one more bit than the row ids need when rows is a power of two.
 int radix_bits_for(int64_t rows) { return key_bits_for(rows + 1); }
 
-// Strip length (lookups per lane group in the apply stage), as measured: 4 for
-// rows of 256 bytes (18.3 against 18.8 us at 26 tables x 8192 lookups), 8 for
-// longer rows (40.2 against 42.1 us at 8 tables x 81920 lookups of 512 bytes:
-// fewer pieces to stitch) and for shorter ones (8.3 against 10.2 us at 26 tables
-// x 2048 lookups of 64 bytes, where a workgroup holds 64 groups).
-int pick_strip(int lanes_per_group) { return lanes_per_group == 16 ? 4 : 8; }
+// Entries of a table's grouped list that the apply stage looks at: whole workgroups, and the one
+// behind them.
+int apply_reads(const Layout &y, int Bcap, int L, int dim)
+{
+    const int g = lanes_per_row(dim);
+    const int64_t per_wg = (int64_t)(kApplyWG / g) * pick_strip(g), nnz = (int64_t)Bcap * L;
+    const int64_t n = (nnz + per_wg - 1) / per_wg * per_wg + 1;
+    return (int)(n < y.NP ? n : y.NP);
+}
 
 }  // namespace
 
@@ -969,12 +979,13 @@ size_t backward_ws_bytes(int T, int Bcap, int L, int dim)
 }
 
 void backward_first_buffers(int T, int Bcap, int L, int dim, void *ws, uint2 **ent,
-                            int *NP)
+                            int *NP, int *fill)
 {
     const Layout y = make_layout(T, Bcap, L, dim);
     char *w8 = static_cast<char *>(ws);
     *ent = reinterpret_cast<uint2 *>(w8 + y.ent0);
     *NP = y.NP;
+    *fill = apply_reads(y, Bcap, L, dim);
 }
 
 // Which of the two pair buffers holds the sorted lists after stage 1.
@@ -1028,26 +1039,27 @@ int32_t launch_backward_prepare(const ss_tables *tb, const int32_t *idx, int Bca
     const int key_bits = key_bits_for(tb->rows);
 
     if (y.NP <= kLdsSortMax) {
-        const ClassSortPlan cp = plan_class_sort(y.NP, Bcap, key_bits);
+        const ClassSortPlan cp = plan_class_sort(T, Bcap * L, key_bits);
         const dim3 grid(1 << cp.class_bits, T);
+        const int fill = apply_reads(y, Bcap, L, tb->dim);
         ProfScope prof("class_sort_kernel", s);
         if (record_after) stop_event_for_next_launch(record_after);     // the only launch
-#define SS_LDS_SORT(I, P)                                                          \
-    launch(SS_BOTH(class_sort_kernel, I, P), grid, dim3(1024), s, idx, Bcap, L, n_valid,     \
-           tb->stale_bits, key_bits, cp.class_bits, cp.val_bits, ent[0],            \
-           y.NP)
-        if (cp.packed) {
-            if (cp.items == 2) { SS_LDS_SORT(2, true); }
-            else if (cp.items == 4) { SS_LDS_SORT(4, true); }
-            else if (cp.items == 8) { SS_LDS_SORT(8, true); }
-            else { SS_LDS_SORT(16, true); }
-        } else {
-            if (cp.items == 2) { SS_LDS_SORT(2, false); }
-            else if (cp.items == 4) { SS_LDS_SORT(4, false); }
-            else if (cp.items == 8) { SS_LDS_SORT(8, false); }
-            else { SS_LDS_SORT(16, false); }
-        }
-#undef SS_LDS_SORT
+#define SS_SORT(NT_, I_)                                                             \
+    if (cp.threads == NT_ && cp.items == I_) {                                       \
+        if (cp.packed)                                                               \
+            launch(SS_BOTH(class_sort_kernel, NT_, I_, true), grid, dim3(NT_), s, idx, Bcap, L,  \
+                   n_valid, tb->stale_bits, key_bits, cp.class_bits, cp.pos_bits, ent[0], y.NP, fill); \
+        else                                                                         \
+            launch(SS_BOTH(class_sort_kernel, NT_, I_, false), grid, dim3(NT_), s, idx, Bcap, L, \
+                   n_valid, tb->stale_bits, key_bits, cp.class_bits, cp.pos_bits, ent[0], y.NP, fill); \
+    }
+        SS_SORT(512, 1)
+        SS_SORT(512, 2)
+        SS_SORT(512, 4)
+        SS_SORT(512, 8)
+        SS_SORT(1024, 8)
+        SS_SORT(1024, 16)
+#undef SS_SORT
     } else {
         // the (row, sample) pairs go to buffer 1 and are scattered into buffer 0, where
         // the buckets are then sorted in place (buffer 1 is their spare)

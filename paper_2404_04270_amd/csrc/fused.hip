@@ -20,8 +20,8 @@ __global__ __launch_bounds__(1024) void forward_group_kernel(
     const float *const *__restrict__ weights, const int32_t *__restrict__ idx,
     int Bcap, const int32_t *__restrict__ n_valid, float *__restrict__ out, int D4,
     int tiles_per_table, const uint32_t *const *__restrict__ bits,
-    int key_bits, int class_bits, int val_bits, uint2 *__restrict__ out_ent, int NP,
-    int group_blocks, bool interleave)
+    int key_bits, int class_bits, int pos_bits, uint2 *__restrict__ out_ent, int NP,
+    int fill, int group_blocks, bool interleave)
 {
     // Roles are interleaved (one grouping workgroup, two gather workgroups, ...)
     // while both last, so that every CU starts with a mix of the two.
@@ -38,8 +38,8 @@ __global__ __launch_bounds__(1024) void forward_group_kernel(
     }
     if (gb >= 0) {
         const int classes = 1 << class_bits;
-        class_sort_body<ITEMS, true>(gb % classes, gb / classes, idx, Bcap, 1, n_valid,
-                                     bits, key_bits, class_bits, val_bits, out_ent, NP);
+        class_sort_body<1024, ITEMS, true>(gb % classes, gb / classes, idx, Bcap, 1, n_valid,
+                                     bits, key_bits, class_bits, pos_bits, out_ent, NP, fill);
     } else {
         forward_onehot_body<G, 1024>(fb, weights, idx, Bcap, n_valid, out, D4,
                                      tiles_per_table);
@@ -53,17 +53,17 @@ bool can_fuse_forward_group(const ss_tables *tb, int Bcap, int L)
     if (NP > 16384) return false;
     int key_bits = 1;
     while (key_bits < 31 && (1LL << key_bits) < tb->rows) ++key_bits;
-    return plan_class_sort(NP, Bcap, key_bits).packed;
+    return plan_class_sort(tb->num_tables, Bcap, key_bits, 1024).packed;
 }
 
 int32_t launch_forward_group(const ss_tables *tb, const int32_t *idx, int Bcap,
                              const int32_t *n_valid, float *out, uint2 *ent, int NP,
-                             hipStream_t s)
+                             int fill, hipStream_t s)
 {
     const int T = tb->num_tables, D4 = tb->dim / 4;
     int key_bits = 1;
     while (key_bits < 31 && (1LL << key_bits) < tb->rows) ++key_bits;
-    const ClassSortPlan cp = plan_class_sort(NP, Bcap, key_bits);
+    const ClassSortPlan cp = plan_class_sort(tb->num_tables, Bcap, key_bits, 1024);
     const int g = lanes_per_row(tb->dim);
     const int bags = (1024 / g) * kOneHotBags;
     const int tiles = (Bcap + bags - 1) / bags;
@@ -76,9 +76,10 @@ int32_t launch_forward_group(const ss_tables *tb, const int32_t *idx, int Bcap,
     SS_DISPATCH_G(g, launch(forward_group_kernel<G, I>, dim3((unsigned)blocks),     \
                             dim3(1024), s, tb->weights, idx, Bcap, n_valid, out, D4, \
                             tiles, tb->stale_bits, key_bits, cp.class_bits,   \
-                            cp.val_bits, ent, NP, group_blocks,                     \
+                            cp.pos_bits, ent, NP, fill, group_blocks,                    \
                             (int64_t)tiles * T >= 2 * (int64_t)group_blocks))
-    if (cp.items == 2) { SS_FG(2); }
+    if (cp.items == 1) { SS_FG(1); }
+    else if (cp.items == 2) { SS_FG(2); }
     else if (cp.items == 4) { SS_FG(4); }
     else if (cp.items == 8) { SS_FG(8); }
     else { SS_FG(16); }

@@ -286,13 +286,14 @@ int32_t launch_backward_apply(const ss_tables *tb, int Bcap, int L, const float 
                               hipEvent_t record_after = nullptr);
 size_t backward_ws_bytes(int T, int Bcap, int L, int dim);
 // Where stage 1 of the backward pass leaves a table's grouped lookups when it
-// takes the one-launch path (buffer 0 of the workspace), and the padded length.
+// takes the one-launch path (buffer 0 of the workspace), the padded length, and how much
+// of it the update reads.
 void backward_first_buffers(int T, int Bcap, int L, int dim, void *ws, uint2 **ent,
-                            int *NP);
+                            int *NP, int *fill);
 bool can_fuse_forward_group(const ss_tables *tb, int Bcap, int L);
 int32_t launch_forward_group(const ss_tables *tb, const int32_t *idx, int Bcap,
                              const int32_t *n_valid, float *out, uint2 *ent, int NP,
-                             hipStream_t s);
+                             int fill, hipStream_t s);
 size_t filter_ws_bytes(int T, int B, int L);
 int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const *drift,
                            const int32_t *sidx, int S, int L, int alpha,

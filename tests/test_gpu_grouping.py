@@ -1,0 +1,76 @@
+"""The one-launch grouping of a table's lookups, at the borders of its plan: no lookup may be lost,
+doubled or filed under another row.  Weights, gradients and the learning rate are small whole
+numbers, so every sum is exact in fp32 whatever its order and the result has to be equal."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(kind, shape, R, gen):
+    dev = "cuda"
+    if kind == "one":                      # a single class holds all lookups
+        return torch.full(shape, R - 1, device=dev)
+    if kind == "few":                      # rows a power of two apart, below the votes of a heavy row
+        n = max(1, min(25, R // 64))
+        return torch.randint(0, n, shape, device=dev, generator=gen) * (R // n)
+    if kind == "uniform":
+        return torch.randint(0, R, shape, device=dev, generator=gen)
+    u = torch.rand(shape, device=dev, dtype=torch.float64, generator=gen)       # skewed
+    return ((R + 1.0) ** (u ** 3) - 1.0).long().clamp_(0, R - 1)
+
+
+@pytest.mark.parametrize("T,R,B,L,kind,stale", [
+    (1, 1, 1, 1, "one", 0.0), (2, 2, 300, 1, "uniform", 0.0),
+    (3, 64, 255, 1, "skewed", 0.3), (3, 64, 256, 1, "one", 0.0), (3, 4096, 257, 1, "few", 0.0),
+    (5, 1000, 128, 4, "skewed", 0.5), (5, 1000, 171, 3, "uniform", 1.0),
+    (40, 5000, 1000, 1, "skewed", 0.1), (7, 65536, 2048, 1, "few", 0.2),
+    (9, 65537, 2049, 1, "skewed", 0.0), (100, 500, 4096, 1, "uniform", 0.0),
+    (2, 1 << 20, 4097, 1, "few", 0.0), (26, 100000, 8192, 1, "skewed", 0.2),
+    (30, 300, 8191, 1, "uniform", 0.0), (1, 1 << 20, 16384, 1, "one", 0.0),
+    (1, 1 << 20, 16383, 1, "few", 0.0), (70, 3000, 16384, 1, "skewed", 0.1),
+    (1, 200_000_000, 8192, 1, "skewed", 0.0),          # row and position need 64 bits
+    (2, 20_000_000, 700, 20, "uniform", 0.3),
+])
+def test_grouping_loses_nothing(T, R, B, L, kind, stale):
+    from paper_2404_04270_amd import binding as Bd
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T * 1000003 + B * 31 + L)
+    D = 4
+    weights = [torch.zeros(R, D, device="cuda") for _ in range(T)]
+    tables = Bd.Tables(weights)
+    bits = tables.new_bits()
+    idx = _rows(kind, (T, B, L), R, gen)
+    flagged = torch.zeros(T, R, dtype=torch.bool, device="cuda") if stale else None
+    if stale:
+        for t in range(T):
+            rows = idx[t].unique()
+            rows = rows[torch.rand(rows.numel(), device="cuda", generator=gen) < stale]
+            flagged[t, rows] = True
+            word = torch.zeros(bits[t].numel(), dtype=torch.int64, device="cuda")
+            word.index_add_(0, rows >> 5, torch.ones_like(rows) << (rows & 31))
+            bits[t].copy_(torch.where(word >= 1 << 31, word - (1 << 32), word))
+    n = B - B // 3
+    n_valid = torch.tensor([n], dtype=torch.int32, device="cuda")
+    grad = torch.randint(-8, 9, (T, B, D), device="cuda", generator=gen).float()
+    ws = torch.empty(Bd.ss_backward_workspace_bytes(T, B, L, D), dtype=torch.uint8, device="cuda")
+    for valid, count in ((None, B), (n_valid, n)):
+        before = [w.clone() for w in weights] if R <= 1 << 20 else None
+        ws.fill_(0xA5)                     # nothing may depend on what the workspace held
+        Bd.ss_embbag_backward_update(tables, idx.int(), valid, grad, 1.0, ws)
+        for t in range(T):
+            rows, sums = idx[t, :count].unique(return_inverse=True)
+            want = torch.zeros(rows.numel(), D, dtype=torch.float64, device="cuda")
+            want.index_add_(0, sums.reshape(-1),
+                            grad[t, :count].double().repeat_interleave(L, 0))
+            if stale:
+                want[flagged[t, rows]] = 0
+            start = before[t][rows].double() if before else 0.0
+            assert torch.equal(weights[t][rows].double(), start - want), (t, count)
+            if before:                     # and no other row was touched
+                after = weights[t].clone()
+                after[rows] = before[t][rows]
+                assert torch.equal(after, before[t]), (t, count)
+            else:
+                assert int((weights[t] != 0).any(1).sum()) <= rows.numel()
+                weights[t].zero_()
