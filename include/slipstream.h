@@ -348,6 +348,13 @@ int32_t ss_select_hot_top(int32_t num_tables, int64_t rows, uint32_t *const *cou
                           void *ws, size_t ws_bytes, void *stream);
 
 /*
+ * Writes n host addresses into a device array of pointers (table, device memory of n pointers), in
+ * order on the stream.  They travel as kernel arguments: the host array may be reused when
+ * the call returns, and neither the host nor the stream waits for anything.
+ */
+int32_t ss_pointer_table(void **table, void *const *pointers, int32_t n, void *stream);
+
+/*
  * Feature normalization of the pooled vectors (section 3.5: a LayerNorm layer
  * brings every sparse vector to zero mean and unit variance; one layer per
  * table).  For each vector v = x[t][j][:], j < n_valid:

@@ -32,7 +32,7 @@ SYMBOLS = (
     "ss_step_plan_for", "ss_step_create", "ss_step_destroy", "ss_step_room",
     "ss_step_submit", "ss_step_forward", "ss_step_backward", "ss_step_flush",
     "ss_step_create_traced", "ss_filter_batch_split", "ss_profile_trace",
-    "ss_step_counters",
+    "ss_step_counters", "ss_pointer_table",
 )
 
 
@@ -44,6 +44,32 @@ class _CTables(C.Structure):
     _fields_ = [("num_tables", C.c_int32), ("dim", C.c_int32),
                 ("rows", C.c_int64), ("weights", C.c_void_p),
                 ("stale_bits", C.c_void_p)]
+
+
+# Argument types of the calls a training or preprocessing loop makes: with them ctypes takes plain
+# numbers and addresses, which costs less than an object of its own per argument.
+# t: ss_tables *, p: address, i / l: int32 / int64, f / d: float / double, z: size
+_ARG = {"t": C.POINTER(_CTables), "p": C.c_void_p, "i": C.c_int32, "l": C.c_int64,
+        "f": C.c_float, "d": C.c_double, "z": C.c_size_t}
+_SIGNATURES = {
+    "ss_filter_batch": "tpiiipppppzp",
+    "ss_embbag_forward": "tpiippp",
+    "ss_embbag_backward_update": "tpiippfpzp",
+    "ss_embbag_backward_update_noalloc": "tpiippfp",
+    "ss_embbag_backward_prepare": "tpiippzp",
+    "ss_embbag_forward_grouped": "tpiipppzp",
+    "ss_embbag_backward_apply": "tiipfpzp",
+    "ss_detect_stale": "tpipfipppp",
+    "ss_sample_drop": "ipippiiipipp",
+    "ss_count_accesses": "ilpiippp",
+    "ss_select_hot_ratio": "ilpdlipppp" "zp",
+    "ss_select_hot_top": "ilpipppzp",
+    "ss_layernorm_forward": "iipippp" "fpppp",
+    "ss_layernorm_backward": "iippippppppppzp",
+    "ss_embbag_forward_ln": "tpiipppfpppp",
+    "ss_embbag_ln_backward": "tpiippppppppp" "zp",
+    "ss_pointer_table": "ppip",
+}
 
 
 def _load():
@@ -73,9 +99,11 @@ def _load():
               "ss_check_indices", "ss_step_plan_for", "ss_step_create", "ss_step_destroy",
               "ss_step_room", "ss_step_submit", "ss_step_forward", "ss_step_backward",
               "ss_step_flush", "ss_step_create_traced", "ss_filter_batch_split",
-              "ss_profile_trace", "ss_step_counters"):
+              "ss_profile_trace", "ss_step_counters", "ss_pointer_table"):
         getattr(lib, n).restype = C.c_int32
     lib.ss_check_enable.restype = None
+    for name, sig in _SIGNATURES.items():
+        getattr(lib, name).argtypes = [_ARG[c] for c in sig]
     return lib
 
 
@@ -155,6 +183,15 @@ def _dev_ptr(t: Optional[torch.Tensor], dtype, name: str) -> C.c_void_p:
     return C.c_void_p(t.data_ptr())
 
 
+def _ptr(t: Optional[torch.Tensor], dtype, name: str):
+    """Address for a call with argument types; the checks of _dev_ptr."""
+    if t is None:
+        return None
+    if t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
+    return _dev_ptr(t, dtype, name).value          # raises
+
+
 def _ptr_table(tensors: Sequence[torch.Tensor], device) -> torch.Tensor:
     return torch.tensor([t.data_ptr() for t in tensors], dtype=torch.int64,
                         device=device)
@@ -164,6 +201,17 @@ def _stream(stream) -> C.c_void_p:
     if stream is None:
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
+
+
+def _stream_ptr(stream):
+    """Handle of `stream`, or of the current stream of the current device.  Asked for without the
+    stream object that torch.cuda.current_stream() builds: 0.2 instead of 2.9 us, in calls whose
+    launches take 3 us each."""
+    if stream is None:
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 class Tables:
@@ -251,14 +299,14 @@ def ss_filter_batch(tables: Tables, idx: torch.Tensor, alpha: int,
             or idx_c.numel() < idx.numel():
         raise SlipstreamError("ss_filter_batch: an output tensor is too small")
     _check(_lib.ss_filter_batch(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(B),
-        C.c_int32(L), C.c_int32(alpha),
-        _dev_ptr(skip_mask, torch.uint8, "skip_mask"),
-        _dev_ptr(kept_ids, torch.int32, "kept_ids"),
-        _dev_ptr(n_kept, torch.int32, "n_kept"),
-        _dev_ptr(idx_c, torch.int32, "idx_c"),
-        _dev_ptr(ws, torch.uint8, "ws"), C.c_size_t(ws.numel()),
-        _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), B,
+        L, alpha,
+        _ptr(skip_mask, torch.uint8, "skip_mask"),
+        _ptr(kept_ids, torch.int32, "kept_ids"),
+        _ptr(n_kept, torch.int32, "n_kept"),
+        _ptr(idx_c, torch.int32, "idx_c"),
+        _ptr(ws, torch.uint8, "ws"), ws.numel(),
+        _stream_ptr(stream)))
 
 
 def ss_filter_batch_split(tables: Tables, hot_bits: Optional[Sequence[torch.Tensor]],
@@ -277,7 +325,7 @@ def ss_filter_batch_split(tables: Tables, hot_bits: Optional[Sequence[torch.Tens
                 b.numel() < Tables.bitmap_words(tables.rows) for b in hot_bits):
             raise SlipstreamError("ss_filter_batch_split: one bitmap of ceil(rows/32) words "
                                   "per table")
-        hp = _opt_ptr_table(hot_bits, torch.int32, "hot_bits", tables.device)
+        hp = _opt_ptr_table(hot_bits, torch.int32, "hot_bits", tables.device, stream)
     _check(_lib.ss_filter_batch_split(
         C.byref(tables.c), C.c_void_p(None if hp is None else hp.data_ptr()),
         _dev_ptr(idx, torch.int32, "idx"), C.c_int32(B), C.c_int32(L), C.c_int32(alpha),
@@ -294,9 +342,9 @@ def ss_embbag_forward(tables: Tables, idx: torch.Tensor,
     if out.numel() < tables.num_tables * Bcap * tables.dim:
         raise SlipstreamError("ss_embbag_forward: out is too small")
     _check(_lib.ss_embbag_forward(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap),
-        C.c_int32(L), _dev_ptr(n_valid, torch.int32, "n_valid"),
-        _dev_ptr(out, torch.float32, "out"), _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap,
+        L, _ptr(n_valid, torch.int32, "n_valid"),
+        _ptr(out, torch.float32, "out"), _stream_ptr(stream)))
 
 
 def ss_embbag_backward_update(tables: Tables, idx: torch.Tensor,
@@ -307,11 +355,11 @@ def ss_embbag_backward_update(tables: Tables, idx: torch.Tensor,
     if grad.numel() < tables.num_tables * Bcap * tables.dim:
         raise SlipstreamError("ss_embbag_backward_update: grad is too small")
     _check(_lib.ss_embbag_backward_update(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap),
-        C.c_int32(L), _dev_ptr(n_valid, torch.int32, "n_valid"),
-        _dev_ptr(grad, torch.float32, "grad"), C.c_float(lr),
-        _dev_ptr(ws, torch.uint8, "ws"), C.c_size_t(ws.numel()),
-        _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap,
+        L, _ptr(n_valid, torch.int32, "n_valid"),
+        _ptr(grad, torch.float32, "grad"), lr,
+        _ptr(ws, torch.uint8, "ws"), ws.numel(),
+        _stream_ptr(stream)))
 
 
 NOALLOC_SCRATCH_BYTES = 16 << 20
@@ -324,9 +372,9 @@ def ss_embbag_backward_update_noalloc(tables: Tables, idx: torch.Tensor,
     if grad.numel() < tables.num_tables * Bcap * tables.dim:
         raise SlipstreamError("ss_embbag_backward_update_noalloc: grad is too small")
     _check(_lib.ss_embbag_backward_update_noalloc(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap),
-        C.c_int32(L), _dev_ptr(n_valid, torch.int32, "n_valid"),
-        _dev_ptr(grad, torch.float32, "grad"), C.c_float(lr), _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap,
+        L, _ptr(n_valid, torch.int32, "n_valid"),
+        _ptr(grad, torch.float32, "grad"), lr, _stream_ptr(stream)))
 
 
 def ss_embbag_backward_prepare(tables: Tables, idx: torch.Tensor,
@@ -334,9 +382,9 @@ def ss_embbag_backward_prepare(tables: Tables, idx: torch.Tensor,
                                stream=None) -> None:
     Bcap, L = _idx_shape(tables, idx)
     _check(_lib.ss_embbag_backward_prepare(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap),
-        C.c_int32(L), _dev_ptr(n_valid, torch.int32, "n_valid"),
-        _dev_ptr(ws, torch.uint8, "ws"), C.c_size_t(ws.numel()), _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap,
+        L, _ptr(n_valid, torch.int32, "n_valid"),
+        _ptr(ws, torch.uint8, "ws"), ws.numel(), _stream_ptr(stream)))
 
 
 def ss_embbag_forward_grouped(tables: Tables, idx: torch.Tensor,
@@ -346,10 +394,10 @@ def ss_embbag_forward_grouped(tables: Tables, idx: torch.Tensor,
     if out.numel() < tables.num_tables * Bcap * tables.dim:
         raise SlipstreamError("ss_embbag_forward_grouped: out is too small")
     _check(_lib.ss_embbag_forward_grouped(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap),
-        C.c_int32(L), _dev_ptr(n_valid, torch.int32, "n_valid"),
-        _dev_ptr(out, torch.float32, "out"), _dev_ptr(bwd_ws, torch.uint8, "bwd_ws"),
-        C.c_size_t(bwd_ws.numel()), _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap,
+        L, _ptr(n_valid, torch.int32, "n_valid"),
+        _ptr(out, torch.float32, "out"), _ptr(bwd_ws, torch.uint8, "bwd_ws"),
+        bwd_ws.numel(), _stream_ptr(stream)))
 
 
 def ss_embbag_backward_apply(tables: Tables, Bcap: int, L: int, grad: torch.Tensor,
@@ -357,9 +405,9 @@ def ss_embbag_backward_apply(tables: Tables, Bcap: int, L: int, grad: torch.Tens
     if grad.numel() < tables.num_tables * Bcap * tables.dim:
         raise SlipstreamError("ss_embbag_backward_apply: grad is too small")
     _check(_lib.ss_embbag_backward_apply(
-        C.byref(tables.c), C.c_int32(Bcap), C.c_int32(L),
-        _dev_ptr(grad, torch.float32, "grad"), C.c_float(lr),
-        _dev_ptr(ws, torch.uint8, "ws"), C.c_size_t(ws.numel()), _stream(stream)))
+        tables.c, Bcap, L,
+        _ptr(grad, torch.float32, "grad"), lr,
+        _ptr(ws, torch.uint8, "ws"), ws.numel(), _stream_ptr(stream)))
 
 
 class HotState:
@@ -400,12 +448,12 @@ class HotState:
 def ss_detect_stale(tables: Tables, hot: HotState, threshold: float,
                     refresh_snapshot: bool = True, stream=None) -> None:
     _check(_lib.ss_detect_stale(
-        C.byref(tables.c), C.c_void_p(hot._hptr.data_ptr()), C.c_int32(hot.H),
-        C.c_void_p(hot._sptr.data_ptr()), C.c_float(threshold),
-        C.c_int32(int(refresh_snapshot)),
-        C.c_void_p(None if hot._shptr is None else hot._shptr.data_ptr()),
-        C.c_void_p(None if hot._dptr is None else hot._dptr.data_ptr()),
-        _dev_ptr(hot.stale_count, torch.int32, "stale_count"), _stream(stream)))
+        tables.c, hot._hptr.data_ptr(), hot.H,
+        hot._sptr.data_ptr(), threshold,
+        int(refresh_snapshot),
+        None if hot._shptr is None else hot._shptr.data_ptr(),
+        None if hot._dptr is None else hot._dptr.data_ptr(),
+        _ptr(hot.stale_count, torch.int32, "stale_count"), _stream_ptr(stream)))
 
 
 MAX_THRESHOLDS = 32
@@ -424,12 +472,12 @@ def ss_sample_drop(hot: HotState, sidx: torch.Tensor, alpha: int,
     if counts.numel() < len(thresholds):
         raise SlipstreamError("ss_sample_drop: counts is shorter than thresholds")
     _check(_lib.ss_sample_drop(
-        C.c_int32(len(hot.hot_ids)), C.c_void_p(hot._hptr.data_ptr()),
-        C.c_int32(hot.H), C.c_void_p(hot._dptr.data_ptr()),
-        _dev_ptr(sidx, torch.int32, "sidx"), C.c_int32(sidx.shape[1]),
-        C.c_int32(sidx.shape[2]), C.c_int32(alpha), thr,
-        C.c_int32(len(thresholds)), _dev_ptr(counts, torch.int32, "counts"),
-        _stream(stream)))
+        len(hot.hot_ids), hot._hptr.data_ptr(),
+        hot.H, hot._dptr.data_ptr(),
+        _ptr(sidx, torch.int32, "sidx"), sidx.shape[1],
+        sidx.shape[2], alpha, thr,
+        len(thresholds), _ptr(counts, torch.int32, "counts"),
+        _stream_ptr(stream)))
 
 
 _STAT_KEYS = ("D", "sd", "half", "lo", "hi", "D_bar", "D_bar_lo", "D_bar_hi")
@@ -464,12 +512,31 @@ class AccessCounters:
         self._cptr = _ptr_table(self.counts, device)
 
 
-def _opt_ptr_table(tensors, dtype, name, device):
+def ss_pointer_table(table: torch.Tensor, pointers: Sequence[int], stream=None) -> None:
+    """table int64 [len(pointers)] or longer, on the device."""
+    n = len(pointers)
+    if table.numel() < n:
+        raise SlipstreamError("ss_pointer_table: table is too short")
+    _check(_lib.ss_pointer_table(_ptr(table, torch.int64, "table"), (C.c_void_p * n)(*pointers), n,
+                                 _stream_ptr(stream)))
+
+
+def _opt_ptr_table(tensors, dtype, name, device, stream=None):
+    """Device array of the tensors' addresses for one call.  On the current stream they travel as
+    kernel arguments: a copy from ordinary host memory makes the host wait for all the stream
+    still has to do (the counting before a selection, say; 17 us a table where it has nothing).  A
+    stream under capture gets that copy, and refuses it: the table does not outlive the call."""
     if tensors is None:
         return None
-    for x in tensors:
-        _dev_ptr(x, dtype, name)
-    return _ptr_table(tensors, device)
+    ptrs = [_ptr(x, dtype, name) for x in tensors]
+    if stream is not None or torch.cuda.is_current_stream_capturing():
+        table = torch.tensor(ptrs, dtype=torch.int64, device=device)
+        if isinstance(stream, torch.cuda.Stream):
+            table.record_stream(stream)
+        return table
+    table = torch.empty(len(ptrs), dtype=torch.int64, device=device)
+    ss_pointer_table(table, ptrs)
+    return table
 
 
 def ss_count_accesses(counters: AccessCounters, idx: torch.Tensor,
@@ -477,10 +544,10 @@ def ss_count_accesses(counters: AccessCounters, idx: torch.Tensor,
     if idx.dim() != 3 or idx.shape[0] != len(counters.counts):
         raise SlipstreamError("ss_count_accesses: idx must be [T, B, L]")
     _check(_lib.ss_count_accesses(
-        C.c_int32(len(counters.counts)), C.c_int64(counters.rows),
-        _dev_ptr(idx, torch.int32, "idx"), C.c_int32(idx.shape[1]),
-        C.c_int32(idx.shape[2]), _dev_ptr(n_valid, torch.int32, "n_valid"),
-        C.c_void_p(counters._cptr.data_ptr()), _stream(stream)))
+        len(counters.counts), counters.rows,
+        _ptr(idx, torch.int32, "idx"), idx.shape[1],
+        idx.shape[2], _ptr(n_valid, torch.int32, "n_valid"),
+        counters._cptr.data_ptr(), _stream_ptr(stream)))
 
 
 def ss_select_hot_workspace_bytes(T: int, rows: int) -> int:
@@ -503,15 +570,15 @@ def ss_select_hot_ratio(counters: AccessCounters, lam: float, total: int,
         raise SlipstreamError("ss_select_hot_ratio: bitmap too short")
     if n_hot is not None and n_hot.numel() < T:
         raise SlipstreamError("ss_select_hot_ratio: n_hot is shorter than T")
-    ip = _opt_ptr_table(hot_ids, torch.int32, "hot_ids", dev)
-    bp = _opt_ptr_table(hot_bits, torch.int32, "hot_bits", dev)
+    ip = _opt_ptr_table(hot_ids, torch.int32, "hot_ids", dev, stream)
+    bp = _opt_ptr_table(hot_bits, torch.int32, "hot_bits", dev, stream)
     _check(_lib.ss_select_hot_ratio(
-        C.c_int32(T), C.c_int64(counters.rows), C.c_void_p(counters._cptr.data_ptr()),
-        C.c_double(lam), C.c_int64(total), C.c_int32(cap),
-        C.c_void_p(None if ip is None else ip.data_ptr()),
-        C.c_void_p(None if bp is None else bp.data_ptr()),
-        _dev_ptr(n_hot, torch.int32, "n_hot"), _dev_ptr(ws, torch.uint8, "ws"),
-        C.c_size_t(ws.numel()), _stream(stream)))
+        T, counters.rows, counters._cptr.data_ptr(),
+        lam, total, cap,
+        None if ip is None else ip.data_ptr(),
+        None if bp is None else bp.data_ptr(),
+        _ptr(n_hot, torch.int32, "n_hot"), _ptr(ws, torch.uint8, "ws"),
+        ws.numel(), _stream_ptr(stream)))
 
 
 def ss_select_hot_top(counters: AccessCounters, H: int,
@@ -525,13 +592,13 @@ def ss_select_hot_top(counters: AccessCounters, H: int,
     if hot_bits is not None and any(b.numel() < Tables.bitmap_words(counters.rows)
                                     for b in hot_bits):
         raise SlipstreamError("ss_select_hot_top: bitmap too short")
-    ip = _opt_ptr_table(hot_ids, torch.int32, "hot_ids", dev)
-    bp = _opt_ptr_table(hot_bits, torch.int32, "hot_bits", dev)
+    ip = _opt_ptr_table(hot_ids, torch.int32, "hot_ids", dev, stream)
+    bp = _opt_ptr_table(hot_bits, torch.int32, "hot_bits", dev, stream)
     _check(_lib.ss_select_hot_top(
-        C.c_int32(T), C.c_int64(counters.rows), C.c_void_p(counters._cptr.data_ptr()),
-        C.c_int32(H), C.c_void_p(None if ip is None else ip.data_ptr()),
-        C.c_void_p(None if bp is None else bp.data_ptr()),
-        _dev_ptr(ws, torch.uint8, "ws"), C.c_size_t(ws.numel()), _stream(stream)))
+        T, counters.rows, counters._cptr.data_ptr(),
+        H, None if ip is None else ip.data_ptr(),
+        None if bp is None else bp.data_ptr(),
+        _ptr(ws, torch.uint8, "ws"), ws.numel(), _stream_ptr(stream)))
 
 
 def _ln_shape(x: torch.Tensor):
@@ -551,11 +618,11 @@ def ss_layernorm_forward(x: torch.Tensor, n_valid: Optional[torch.Tensor],
         if p is not None and tuple(p.shape) != (T, D):
             raise SlipstreamError(f"ss_layernorm_forward: {name} must be [T, D]")
     _check(_lib.ss_layernorm_forward(
-        C.c_int32(T), C.c_int32(D), _dev_ptr(x, torch.float32, "x"), C.c_int32(Bcap),
-        _dev_ptr(n_valid, torch.int32, "n_valid"), _dev_ptr(gamma, torch.float32, "gamma"),
-        _dev_ptr(beta, torch.float32, "beta"), C.c_float(eps),
-        _dev_ptr(y, torch.float32, "y"), _dev_ptr(mean, torch.float32, "mean"),
-        _dev_ptr(rstd, torch.float32, "rstd"), _stream(stream)))
+        T, D, _ptr(x, torch.float32, "x"), Bcap,
+        _ptr(n_valid, torch.int32, "n_valid"), _ptr(gamma, torch.float32, "gamma"),
+        _ptr(beta, torch.float32, "beta"), eps,
+        _ptr(y, torch.float32, "y"), _ptr(mean, torch.float32, "mean"),
+        _ptr(rstd, torch.float32, "rstd"), _stream_ptr(stream)))
 
 
 def ss_layernorm_backward_workspace_bytes(T: int, dim: int, Bcap: int) -> int:
@@ -575,13 +642,13 @@ def ss_layernorm_backward(dy: torch.Tensor, x: torch.Tensor,
         if p is not None and tuple(p.shape) != (T, D):
             raise SlipstreamError(f"ss_layernorm_backward: {name} must be [T, D]")
     _check(_lib.ss_layernorm_backward(
-        C.c_int32(T), C.c_int32(D), _dev_ptr(dy, torch.float32, "dy"),
-        _dev_ptr(x, torch.float32, "x"), C.c_int32(Bcap),
-        _dev_ptr(n_valid, torch.int32, "n_valid"), _dev_ptr(gamma, torch.float32, "gamma"),
-        _dev_ptr(mean, torch.float32, "mean"), _dev_ptr(rstd, torch.float32, "rstd"),
-        _dev_ptr(dx, torch.float32, "dx"), _dev_ptr(dgamma, torch.float32, "dgamma"),
-        _dev_ptr(dbeta, torch.float32, "dbeta"), _dev_ptr(ws, torch.uint8, "ws"),
-        C.c_size_t(0 if ws is None else ws.numel()), _stream(stream)))
+        T, D, _ptr(dy, torch.float32, "dy"),
+        _ptr(x, torch.float32, "x"), Bcap,
+        _ptr(n_valid, torch.int32, "n_valid"), _ptr(gamma, torch.float32, "gamma"),
+        _ptr(mean, torch.float32, "mean"), _ptr(rstd, torch.float32, "rstd"),
+        _ptr(dx, torch.float32, "dx"), _ptr(dgamma, torch.float32, "dgamma"),
+        _ptr(dbeta, torch.float32, "dbeta"), _ptr(ws, torch.uint8, "ws"),
+        0 if ws is None else ws.numel(), _stream_ptr(stream)))
 
 
 def ss_embbag_forward_ln(tables: Tables, idx: torch.Tensor, n_valid: Optional[torch.Tensor],
@@ -596,11 +663,11 @@ def ss_embbag_forward_ln(tables: Tables, idx: torch.Tensor, n_valid: Optional[to
         if p is not None and tuple(p.shape) != (T, D):
             raise SlipstreamError(f"ss_embbag_forward_ln: {name} must be [T, D]")
     _check(_lib.ss_embbag_forward_ln(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap), C.c_int32(L),
-        _dev_ptr(n_valid, torch.int32, "n_valid"), _dev_ptr(gamma, torch.float32, "gamma"),
-        _dev_ptr(beta, torch.float32, "beta"), C.c_float(eps),
-        _dev_ptr(y, torch.float32, "y"), _dev_ptr(mean, torch.float32, "mean"),
-        _dev_ptr(rstd, torch.float32, "rstd"), _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap, L,
+        _ptr(n_valid, torch.int32, "n_valid"), _ptr(gamma, torch.float32, "gamma"),
+        _ptr(beta, torch.float32, "beta"), eps,
+        _ptr(y, torch.float32, "y"), _ptr(mean, torch.float32, "mean"),
+        _ptr(rstd, torch.float32, "rstd"), _stream_ptr(stream)))
 
 
 def ss_embbag_ln_backward(tables: Tables, idx: torch.Tensor, n_valid: Optional[torch.Tensor],
@@ -616,13 +683,13 @@ def ss_embbag_ln_backward(tables: Tables, idx: torch.Tensor, n_valid: Optional[t
         if p is not None and tuple(p.shape) != (T, D):
             raise SlipstreamError(f"ss_embbag_ln_backward: {name} must be [T, D]")
     _check(_lib.ss_embbag_ln_backward(
-        C.byref(tables.c), _dev_ptr(idx, torch.int32, "idx"), C.c_int32(Bcap), C.c_int32(L),
-        _dev_ptr(n_valid, torch.int32, "n_valid"), _dev_ptr(dy, torch.float32, "dy"),
-        _dev_ptr(gamma, torch.float32, "gamma"), _dev_ptr(mean, torch.float32, "mean"),
-        _dev_ptr(rstd, torch.float32, "rstd"), _dev_ptr(dx, torch.float32, "dx"),
-        _dev_ptr(dgamma, torch.float32, "dgamma"), _dev_ptr(dbeta, torch.float32, "dbeta"),
-        _dev_ptr(ws, torch.uint8, "ws"), C.c_size_t(0 if ws is None else ws.numel()),
-        _stream(stream)))
+        tables.c, _ptr(idx, torch.int32, "idx"), Bcap, L,
+        _ptr(n_valid, torch.int32, "n_valid"), _ptr(dy, torch.float32, "dy"),
+        _ptr(gamma, torch.float32, "gamma"), _ptr(mean, torch.float32, "mean"),
+        _ptr(rstd, torch.float32, "rstd"), _ptr(dx, torch.float32, "dx"),
+        _ptr(dgamma, torch.float32, "dgamma"), _ptr(dbeta, torch.float32, "dbeta"),
+        _ptr(ws, torch.uint8, "ws"), 0 if ws is None else ws.numel(),
+        _stream_ptr(stream)))
 
 
 def stream_handle(stream=None) -> C.c_void_p:

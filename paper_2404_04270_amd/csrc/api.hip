@@ -53,6 +53,19 @@ int32_t check_launch(const char *who)
     return SS_OK;
 }
 
+// ---- pointer tables -----------------------------------------------------
+namespace {
+struct PointerPack {
+    static constexpr int kMax = 128;       // 1 KB of kernel arguments
+    void *p[kMax];
+};
+__global__ __launch_bounds__(PointerPack::kMax) void pointer_table_kernel(void **table, int n,
+                                                                          PointerPack pack)
+{
+    if ((int)threadIdx.x < n) table[threadIdx.x] = pack.p[threadIdx.x];
+}
+}  // namespace
+
 // ---- optional per-kernel timing ---------------------------------------
 namespace {
 struct ProfRec {
@@ -307,6 +320,22 @@ int32_t ss_profile_report(char *buf, size_t buf_bytes)
         off += (size_t)w;
     }
     return rc;
+}
+
+int32_t ss_pointer_table(void **table, void *const *pointers, int32_t n, void *stream)
+{
+    const char *who = "ss_pointer_table";
+    if (n < 0) return fail(SS_ERR_INVALID_ARG, "%s: n = %d", who, n);
+    if (n > 0 && (!table || !pointers))
+        return fail(SS_ERR_INVALID_ARG, "%s: table or pointers is NULL", who);
+    for (int32_t k = 0; k < n; k += PointerPack::kMax) {
+        PointerPack pack = {};
+        const int m = n - k < PointerPack::kMax ? n - k : PointerPack::kMax;
+        for (int i = 0; i < m; ++i) pack.p[i] = pointers[k + i];
+        launch(pointer_table_kernel, dim3(1), dim3(PointerPack::kMax),
+               static_cast<hipStream_t>(stream), table + k, m, pack);
+    }
+    return check_launch(who);
 }
 
 size_t ss_filter_batch_workspace_bytes(int32_t T, int32_t B, int32_t L)
