@@ -9,7 +9,9 @@
 // grows with every stale lookup: 21 us at 26 tables once the hot rows are
 // frozen.)  A wavefront ballot plus popcount yields the number of kept samples
 // per workgroup.
-// Kernel 2 runs one workgroup per (tile of 256 samples, table).  It turns the
+// Small batches take one launch that does both for itself per table (filter_small_kernel).
+// Kernel 2 runs one workgroup per (tile of 256 samples, table, or four tables where bags hold
+// one lookup and the batch is large).  It turns the
 // per-tile counts into an offset (summing the counts before it: at most a few
 // hundred values), ranks the tile's kept samples with ballot + popcount prefix
 // sums, writes kept_ids in ascending order and copies the index rows of the kept
@@ -39,6 +41,82 @@ constexpr int flag_wg(int lanes) { return lanes <= 32 ? 256 : 1024; }
 // I = I_hot + I_cold): hot_mask[b] = 1 iff every lookup of the sample hits a row
 // whose hot bit is set.  The indices of a chunk are loaded once for both tests;
 // each test stops probing as soon as its verdict is fixed.
+// Verdicts on sample b (below B) by a group of LANES lanes, of which this is lane c.
+template <int LANES, bool SPLIT>
+__device__ __forceinline__ void classify(const uint32_t *const *__restrict__ bits,
+                                         const uint32_t *const *__restrict__ hot_bits,
+                                         const int32_t *__restrict__ idx, int T, int B, int L,
+                                         int alpha, int b, int c, bool &skip, bool &all_hot)
+{
+    const int total = T * L;
+    skip = false;
+    bool stale_open = true;                      // is the stale verdict still undecided?
+    if (alpha <= 0) {
+        skip = true;
+        stale_open = false;
+    } else if (alpha > total || bits == nullptr) {
+        stale_open = false;
+    }
+    bool hot_open = SPLIT && hot_bits != nullptr;
+    all_hot = hot_open;                          // no hot bitmaps: no input is hot
+    int count = 0;                               // stale lookups so far (all lanes)
+    int per_lane = 1;
+    for (int q0 = 0; q0 < total && (stale_open || hot_open);) {
+        const int chunk = LANES * per_lane;
+        uint32_t row[kFlagProbes];
+        int tab[kFlagProbes];
+        bool in[kFlagProbes];
+#pragma unroll
+        for (int i = 0; i < kFlagProbes; ++i) {
+            const int q = q0 + i * LANES + c;
+            in[i] = i < per_lane && q < total;
+            const int qq = in[i] ? q : 0;
+            const int t = qq / L, l = qq - t * L;
+            tab[i] = t;
+            row[i] = in[i] ? (uint32_t)idx[((int64_t)t * B + b) * L + l] : 0u;
+        }
+        if (stale_open) {
+            gptr<const uint32_t> bt[kFlagProbes];
+            uint32_t word[kFlagProbes];
+#pragma unroll
+            for (int i = 0; i < kFlagProbes; ++i) bt[i] = as_global(bits[tab[i]]);
+#pragma unroll
+            for (int i = 0; i < kFlagProbes; ++i)
+                word[i] = (in[i] && bt[i] != nullptr) ? bt[i][row[i] >> 5] : 0u;
+            int mine = 0;
+#pragma unroll
+            for (int i = 0; i < kFlagProbes; ++i) mine += (word[i] >> (row[i] & 31)) & 1u;
+#pragma unroll
+            for (int off = 1; off < LANES; off <<= 1) mine += __shfl_xor(mine, off, LANES);
+            count += mine;
+        }
+        if (SPLIT && hot_open) {
+            gptr<const uint32_t> ht[kFlagProbes];
+            uint32_t word[kFlagProbes];
+#pragma unroll
+            for (int i = 0; i < kFlagProbes; ++i) ht[i] = as_global(hot_bits[tab[i]]);
+#pragma unroll
+            for (int i = 0; i < kFlagProbes; ++i)
+                word[i] = (in[i] && ht[i] != nullptr) ? ht[i][row[i] >> 5] : 0u;
+            int cold = 0;                        // lookups of this lane that miss the hot set
+#pragma unroll
+            for (int i = 0; i < kFlagProbes; ++i)
+                cold += in[i] && !((word[i] >> (row[i] & 31)) & 1u);
+#pragma unroll
+            for (int off = 1; off < LANES; off <<= 1) cold += __shfl_xor(cold, off, LANES);
+            if (cold) {
+                all_hot = false;
+                hot_open = false;
+            }
+        }
+        q0 += chunk;
+        const int remaining = total > q0 ? total - q0 : 0;
+        if (stale_open && (count >= alpha || count + remaining < alpha)) stale_open = false;
+        per_lane = kFlagProbes;
+    }
+    if (alpha > 0 && alpha <= total && bits != nullptr) skip = count >= alpha;
+}
+
 template <int LANES, bool SPLIT, typename TS>
 __global__ __launch_bounds__(flag_wg(LANES)) void filter_flag_kernel(
     const uint32_t *const *__restrict__ bits, const uint32_t *const *__restrict__ hot_bits,
@@ -53,73 +131,8 @@ __global__ __launch_bounds__(flag_wg(LANES)) void filter_flag_kernel(
     const int b = blockIdx.x * SAMPLES + threadIdx.x / LANES;
     bool keep = false;
     if (b < B) {
-        const int total = T * L;
-        bool skip = false;
-        bool stale_open = true;                  // is the stale verdict still undecided?
-        if (alpha <= 0) {
-            skip = true;
-            stale_open = false;
-        } else if (alpha > total || bits == nullptr) {
-            stale_open = false;
-        }
-        bool hot_open = SPLIT && hot_bits != nullptr;
-        bool all_hot = hot_open;                 // no hot bitmaps: no input is hot
-        int count = 0;                           // stale lookups so far (all lanes)
-        int per_lane = 1;
-        for (int q0 = 0; q0 < total && (stale_open || hot_open);) {
-            const int chunk = LANES * per_lane;
-            uint32_t row[kFlagProbes];
-            int tab[kFlagProbes];
-            bool in[kFlagProbes];
-#pragma unroll
-            for (int i = 0; i < kFlagProbes; ++i) {
-                const int q = q0 + i * LANES + c;
-                in[i] = i < per_lane && q < total;
-                const int qq = in[i] ? q : 0;
-                const int t = qq / L, l = qq - t * L;
-                tab[i] = t;
-                row[i] = in[i] ? (uint32_t)idx[((int64_t)t * B + b) * L + l] : 0u;
-            }
-            if (stale_open) {
-                gptr<const uint32_t> bt[kFlagProbes];
-                uint32_t word[kFlagProbes];
-#pragma unroll
-                for (int i = 0; i < kFlagProbes; ++i) bt[i] = as_global(bits[tab[i]]);
-#pragma unroll
-                for (int i = 0; i < kFlagProbes; ++i)
-                    word[i] = (in[i] && bt[i] != nullptr) ? bt[i][row[i] >> 5] : 0u;
-                int mine = 0;
-#pragma unroll
-                for (int i = 0; i < kFlagProbes; ++i) mine += (word[i] >> (row[i] & 31)) & 1u;
-#pragma unroll
-                for (int off = 1; off < LANES; off <<= 1) mine += __shfl_xor(mine, off, LANES);
-                count += mine;
-            }
-            if (SPLIT && hot_open) {
-                gptr<const uint32_t> ht[kFlagProbes];
-                uint32_t word[kFlagProbes];
-#pragma unroll
-                for (int i = 0; i < kFlagProbes; ++i) ht[i] = as_global(hot_bits[tab[i]]);
-#pragma unroll
-                for (int i = 0; i < kFlagProbes; ++i)
-                    word[i] = (in[i] && ht[i] != nullptr) ? ht[i][row[i] >> 5] : 0u;
-                int cold = 0;                    // lookups of this lane that miss the hot set
-#pragma unroll
-                for (int i = 0; i < kFlagProbes; ++i)
-                    cold += in[i] && !((word[i] >> (row[i] & 31)) & 1u);
-#pragma unroll
-                for (int off = 1; off < LANES; off <<= 1) cold += __shfl_xor(cold, off, LANES);
-                if (cold) {
-                    all_hot = false;
-                    hot_open = false;
-                }
-            }
-            q0 += chunk;
-            const int remaining = total > q0 ? total - q0 : 0;
-            if (stale_open && (count >= alpha || count + remaining < alpha)) stale_open = false;
-            per_lane = kFlagProbes;
-        }
-        if (alpha > 0 && alpha <= total && bits != nullptr) skip = count >= alpha;
+        bool skip, all_hot;
+        classify<LANES, SPLIT>(bits, hot_bits, idx, T, B, L, alpha, b, c, skip, all_hot);
         if (c == 0) skip_mask[b] = skip ? 1 : 0;
         if (SPLIT && c == 0) hot_mask[b] = all_hot ? 1 : 0;
         keep = !skip && c == 0;
@@ -133,6 +146,52 @@ __global__ __launch_bounds__(flag_wg(LANES)) void filter_flag_kernel(
         for (int w = 0; w < kFlagWG / 64; ++w) s += s_cnt[w];
         block_kept[blockIdx.x] = s;
     }
+    trace_end(ts, trace_t0);
+}
+
+// One lookup per bag: TABLES tables per workgroup, whose index words are all requested before the
+// place of the first is known.  Ranking the tile costs a trip to memory and a barrier, and a table's
+// share of it is one word per thread: with a workgroup per tile and table, 4082 of them at 26 tables
+// x 40000 samples, the launch takes 6.7 us alone and 16.5 beside the training kernels; 5.2 alone so.
+template <int TABLES, typename TS>
+__global__ __launch_bounds__(kWG) void filter_compact_onehot_kernel(
+    const int32_t *__restrict__ idx, int T, int B, const uint8_t *__restrict__ skip_mask,
+    const int32_t *__restrict__ block_kept, int per_tile, int32_t *__restrict__ kept_ids,
+    int32_t *__restrict__ n_kept, int32_t *__restrict__ idx_c, TS ts)
+{
+    const unsigned long long trace_t0 = trace_begin<TS>();
+    __shared__ int s_before[kWG / 64], s_kept[kWG / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t0 = blockIdx.y * TABLES, b = blockIdx.x * kWG + tid;
+    const bool keep = b < B && skip_mask[b] == 0;
+    int32_t row[TABLES];
+#pragma unroll
+    for (int k = 0; k < TABLES; ++k)
+        row[k] = b < B && t0 + k < T ? idx[(int64_t)(t0 + k) * B + b] : 0;
+    int part = 0;                        // samples kept by the tiles before this one
+    for (int i = tid; i < (int)blockIdx.x * per_tile; i += kWG) part += block_kept[i];
+    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+    const unsigned long long bal = __ballot(keep);
+    if (lane == 0) {
+        s_before[wave] = part;
+        s_kept[wave] = __popcll(bal);
+    }
+    __syncthreads();
+    int base = 0, at = __popcll(bal & ((1ull << lane) - 1ull)), nk = 0;
+#pragma unroll
+    for (int w = 0; w < kWG / 64; ++w) {
+        base += s_before[w];
+        if (w < wave) at += s_kept[w];
+        nk += s_kept[w];
+    }
+    at += base;
+    if (keep) {
+#pragma unroll
+        for (int k = 0; k < TABLES; ++k)
+            if (t0 + k < T) idx_c[(int64_t)(t0 + k) * B + at] = row[k];
+        if (t0 == 0) kept_ids[at] = b;
+    }
+    if (t0 == 0 && blockIdx.x == gridDim.x - 1 && tid == 0) *n_kept = base + nk;
     trace_end(ts, trace_t0);
 }
 
@@ -184,27 +243,93 @@ __global__ __launch_bounds__(kWG) void filter_compact_kernel(
     // idx_c[t][base + k][:] = idx[t][s_list[k]][:]
     const int32_t *__restrict__ src = idx + (int64_t)t * B * L;
     int32_t *__restrict__ dst = idx_c + ((int64_t)t * B + base) * L;
-    if (L == 1) {
-        if (tid < nk) dst[tid] = src[s_list[tid]];
-    } else {
-        // long bags: gridDim.z workgroups share the rows of a tile (each repeats the
-        // cheap ranking above), 4 * kWG elements at a time
-        const int total = nk * L;
-        for (int e0 = tid + (int)blockIdx.z * 4 * kWG; e0 < total;
-             e0 += (int)gridDim.z * 4 * kWG) {
-            int32_t v[4];
+    // long bags: gridDim.z workgroups share the rows of a tile (each repeats the
+    // cheap ranking above), 4 * kWG elements at a time
+    const int total = nk * L;
+    for (int e0 = tid + (int)blockIdx.z * 4 * kWG; e0 < total;
+         e0 += (int)gridDim.z * 4 * kWG) {
+        int32_t v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = e0 + u * kWG;
-                const int k = e / L, l = e - k * L;
-                v[u] = e < total ? src[(int64_t)s_list[k] * L + l] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (e0 + u * kWG < total) dst[e0 + u * kWG] = v[u];
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kWG;
+            const int k = e / L, l = e - k * L;
+            v[u] = e < total ? src[(int64_t)s_list[k] * L + l] : 0;
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (e0 + u * kWG < total) dst[e0 + u * kWG] = v[u];
     }
     trace_end(ts, trace_t0);
+}
+
+// Small batches, in one launch: a workgroup per table classifies all samples for itself, LANES lanes
+// each, ranks them and copies the index rows of its table.
+constexpr int kSmallThreads = 1024;
+template <int LANES, typename TS>
+__global__ __launch_bounds__(kSmallThreads) void filter_small_kernel(
+    const uint32_t *const *__restrict__ bits, const int32_t *__restrict__ idx, int T, int B, int L,
+    int alpha, uint8_t *__restrict__ skip_mask, int32_t *__restrict__ kept_ids,
+    int32_t *__restrict__ n_kept, int32_t *__restrict__ idx_c, TS ts)
+{
+    const unsigned long long trace_t0 = trace_begin<TS>();
+    constexpr int W = kSmallThreads / 64;
+    __shared__ int s_kept[W];
+    __shared__ int32_t s_list[kSmallThreads / LANES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t = blockIdx.x, b = tid / LANES, c = tid % LANES;
+    bool keep = false;
+    if (b < B) {
+        bool skip, all_hot;
+        classify<LANES, false>(bits, nullptr, idx, T, B, L, alpha, b, c, skip, all_hot);
+        if (t == 0 && c == 0) skip_mask[b] = skip ? 1 : 0;
+        keep = !skip && c == 0;
+    }
+    const unsigned long long bal = __ballot(keep);
+    if (lane == 0) s_kept[wave] = __popcll(bal);
+    __syncthreads();
+    int at = __popcll(bal & ((1ull << lane) - 1ull)), nk = 0;
+    const int waves = blockDim.x / 64;
+    for (int w = 0; w < waves; ++w) {
+        if (w < wave) at += s_kept[w];
+        nk += s_kept[w];
+    }
+    if (keep) {
+        s_list[at] = b;
+        if (t == 0) kept_ids[at] = b;
+    }
+    if (t == 0 && tid == 0) *n_kept = nk;
+    __syncthreads();
+    const int32_t *__restrict__ src = idx + (int64_t)t * B * L;
+    int32_t *__restrict__ dst = idx_c + (int64_t)t * B * L;
+    const int total = nk * L;
+    for (int e0 = tid; e0 < total; e0 += 4 * blockDim.x) {
+        int32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * blockDim.x;
+            const int k = e / L, l = e - k * L;
+            v[u] = e < total ? src[(int64_t)s_list[k] * L + l] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (e0 + u * (int)blockDim.x < total) dst[e0 + u * blockDim.x] = v[u];
+    }
+    trace_end(ts, trace_t0);
+}
+
+// Lanes per sample of the one-launch filter, 0 where the batch is not for it.  Every table's
+// workgroup probes the bitmaps for the whole batch, so what that may cost at worst, with all hot
+// rows stale, is bounded: 16384 lookups in all, and no lane more than two rounds behind its first,
+// one where bags are long (their index words lie apart).  us with two launches, the gap between
+// them not counted, and with one, no row stale and all hot rows stale: 8 tables x 128 lookups
+// 5.3 and 4.1, 4.9 and 4.2; 5 x 777 bags of 3 5.9 and 4.0, 6.2 and 8.8; 16 x 1024 5.6 and 4.2, 6.4
+// and 8.4; a training step call by call 22.3 and 20.2 at 8 x 128, 24.3 and 22.7 at 5 x 777 x 3.
+static int small_lanes(int64_t B, int L, int64_t total)
+{
+    if (B > kSmallThreads || B * total > 16384) return 0;
+    int lanes = 64;
+    while (lanes > 1 && B * lanes > kSmallThreads) lanes >>= 1;
+    return lanes * (1 + (L < 8 ? 2 : 1) * kFlagProbes) >= total ? lanes : 0;
 }
 
 // Lanes per sample in the flag kernel: the fewest of 4 ... 64 with which two
@@ -237,6 +362,26 @@ int32_t launch_filter_split(const ss_tables *tb, uint32_t *const *hot_bits, cons
                             int32_t *kept_ids, int32_t *n_kept, int32_t *idx_c, void *ws,
                             hipStream_t s)
 {
+    const int small = hot_mask ? 0 : small_lanes(B, L, (int64_t)tb->num_tables * L);
+    if (small) {
+        ProfScope prof("filter_small_kernel", s);
+        const int threads = ((B * small + 63) / 64) * 64;
+#define SS_SMALL(LANES_)                                                              \
+    launch(SS_BOTH(filter_small_kernel, LANES_), dim3(tb->num_tables),                 \
+           dim3(threads < 256 ? 256 : threads), s, tb->stale_bits, idx, tb->num_tables, B, L, \
+           alpha, skip_mask, kept_ids, n_kept, idx_c)
+        switch (small) {
+        case 1: SS_SMALL(1); break;
+        case 2: SS_SMALL(2); break;
+        case 4: SS_SMALL(4); break;
+        case 8: SS_SMALL(8); break;
+        case 16: SS_SMALL(16); break;
+        case 32: SS_SMALL(32); break;
+        default: SS_SMALL(64); break;
+        }
+#undef SS_SMALL
+        return check_launch("ss_filter_batch");
+    }
     const int lanes = flag_lanes((int64_t)tb->num_tables * L);
     const int samples = flag_wg(lanes) / lanes;      // per workgroup of the flag kernel
     const int flag_blocks = (B + samples - 1) / samples;
@@ -263,10 +408,21 @@ int32_t launch_filter_split(const ss_tables *tb, uint32_t *const *hot_bits, cons
 #undef SS_FLAG
     }
     ProfScope prof("filter_compact_kernel", s);
+    if (L == 1) {
+#define SS_ONEHOT(N_)                                                                  \
+    launch(SS_BOTH(filter_compact_onehot_kernel, N_),                                  \
+           dim3(tiles, (tb->num_tables + N_ - 1) / N_), dim3(kWG), s, idx, tb->num_tables, B, \
+           skip_mask, (const int32_t *)block_kept, kWG / samples, kept_ids, n_kept, idx_c)
+        // where that leaves workgroups for half of the compute units and more
+        if ((int64_t)tiles * tb->num_tables >= 512) SS_ONEHOT(4);
+        else SS_ONEHOT(1);
+#undef SS_ONEHOT
+        return check_launch("ss_filter_batch");
+    }
     // the last tile may be covered by fewer workgroups of the flag kernel: a tile
     // before it is always covered by exactly kWG / samples of them
     // one workgroup per 1024 index words of a tile's rows, at most eight
-    const int parts = L == 1 ? 1 : (L + 3) / 4 > 8 ? 8 : (L + 3) / 4;
+    const int parts = (L + 3) / 4 > 8 ? 8 : (L + 3) / 4;
     launch(filter_compact_kernel<NoTrace>, filter_compact_kernel<TraceSlot>,
            dim3(tiles, tb->num_tables, parts), dim3(kWG), s, idx, B, L, skip_mask, block_kept,
            kWG / samples, kept_ids, n_kept, idx_c);
