@@ -277,6 +277,23 @@ int32_t ss_sample_drop(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
                        int32_t n_thr, uint32_t *counts, void *stream);
 
 /*
+ * The same in two steps for alpha = T*L, where several ladders of thresholds are to be priced on
+ * one sample: ss_sample_levels finds for every input the threshold from which on it can be dropped
+ * (the largest drift of its lookups, NaN where one of them is never stale), ss_level_counts
+ * counts the levels each threshold reaches.  The counts are those of ss_sample_drop.
+ *   levels       device fp64 [S]
+ *   thresholds   HOST array of n_thr floats (1 <= n_thr <= SS_MAX_LEVEL_THRESHOLDS), read before
+ *                the call returns; any order; NaN is rejected
+ *   counts       device uint32 [n_thr], overwritten
+ */
+#define SS_MAX_LEVEL_THRESHOLDS 64
+int32_t ss_sample_levels(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
+                         double *const *drift, const int32_t *sidx, int32_t S, int32_t L,
+                         double *levels, void *stream);
+int32_t ss_level_counts(const double *levels, int32_t S, const float *thresholds, int32_t n_thr,
+                        uint32_t *counts, void *stream);
+
+/*
  * Estimate of the dropped share from one count of ss_sample_drop, with its
  * confidence interval (Eq. 2-4).  Host arithmetic only, fp64; no GPU work.
  *     D    = count / n_samples                                         (Eq. 2)
@@ -295,6 +312,9 @@ int32_t ss_sample_drop(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
  */
 int32_t ss_drop_stats(uint32_t count, int64_t n_samples, int64_t population,
                       int64_t n_hot_inputs, double t_crit, double *out);
+/* The same for n counts (HOST array): out double[n][8]. */
+int32_t ss_drop_stats_many(const uint32_t *counts, int32_t n, int64_t n_samples,
+                           int64_t population, int64_t n_hot_inputs, double t_crit, double *out);
 
 /*
  * Access counters of the preprocessing phase (section 3.1; first loop of

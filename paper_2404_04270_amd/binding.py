@@ -32,7 +32,8 @@ SYMBOLS = (
     "ss_step_plan_for", "ss_step_create", "ss_step_destroy", "ss_step_room",
     "ss_step_submit", "ss_step_forward", "ss_step_backward", "ss_step_flush",
     "ss_step_create_traced", "ss_filter_batch_split", "ss_profile_trace",
-    "ss_step_counters", "ss_pointer_table",
+    "ss_step_counters", "ss_pointer_table", "ss_sample_levels", "ss_level_counts",
+    "ss_drop_stats_many",
 )
 
 
@@ -69,6 +70,9 @@ _SIGNATURES = {
     "ss_embbag_forward_ln": "tpiipppfpppp",
     "ss_embbag_ln_backward": "tpiippppppppp" "zp",
     "ss_pointer_table": "ppip",
+    "ss_sample_levels": "ipippiipp",
+    "ss_level_counts": "pipipp",
+    "ss_drop_stats_many": "pilll" "dp",
 }
 
 
@@ -99,7 +103,8 @@ def _load():
               "ss_check_indices", "ss_step_plan_for", "ss_step_create", "ss_step_destroy",
               "ss_step_room", "ss_step_submit", "ss_step_forward", "ss_step_backward",
               "ss_step_flush", "ss_step_create_traced", "ss_filter_batch_split",
-              "ss_profile_trace", "ss_step_counters", "ss_pointer_table"):
+              "ss_profile_trace", "ss_step_counters", "ss_pointer_table",
+              "ss_sample_levels", "ss_level_counts", "ss_drop_stats_many"):
         getattr(lib, n).restype = C.c_int32
     lib.ss_check_enable.restype = None
     for name, sig in _SIGNATURES.items():
@@ -490,6 +495,48 @@ def ss_drop_stats(count: int, n_samples: int, population: int, n_hot_inputs: int
                               C.c_int64(population), C.c_int64(n_hot_inputs),
                               C.c_double(t_crit), out))
     return dict(zip(_STAT_KEYS, list(out)))
+
+
+MAX_LEVEL_THRESHOLDS = 64
+
+
+def ss_sample_levels(hot: HotState, sidx: torch.Tensor, levels: torch.Tensor,
+                     stream=None) -> None:
+    """levels fp64 [S]: the threshold from which on each input of sidx (int32 [T, S, L]) can be
+    dropped when all its lookups have to be stale; reads hot.drift."""
+    if hot.drift is None:
+        raise SlipstreamError("ss_sample_levels: HotState was built without diagnostics")
+    if sidx.dim() != 3 or sidx.shape[0] != len(hot.hot_ids):
+        raise SlipstreamError("ss_sample_levels: sidx must be [T, S, L]")
+    if levels.numel() < sidx.shape[1]:
+        raise SlipstreamError("ss_sample_levels: levels is shorter than the sample")
+    _check(_lib.ss_sample_levels(
+        len(hot.hot_ids), hot._hptr.data_ptr(), hot.H, hot._dptr.data_ptr(),
+        _ptr(sidx, torch.int32, "sidx"), sidx.shape[1], sidx.shape[2],
+        _ptr(levels, torch.float64, "levels"), _stream_ptr(stream)))
+
+
+def ss_level_counts(levels: torch.Tensor, thresholds: Sequence[float], counts: torch.Tensor,
+                    stream=None) -> None:
+    """counts int32 [len(thresholds)]: levels that each of up to 64 thresholds reaches."""
+    thr = (C.c_float * len(thresholds))(*thresholds)
+    if counts.numel() < len(thresholds):
+        raise SlipstreamError("ss_level_counts: counts is shorter than thresholds")
+    _check(_lib.ss_level_counts(
+        _ptr(levels, torch.float64, "levels"), levels.numel(), thr, len(thresholds),
+        _ptr(counts, torch.int32, "counts"), _stream_ptr(stream)))
+
+
+def ss_drop_stats_many(counts, n_samples: int, population: int, n_hot_inputs: int,
+                       t_crit: float):
+    """counts: contiguous numpy uint32 [n]; returns numpy float64 [n, 8], the values of
+    ss_drop_stats in its order."""
+    import numpy as np
+    counts = np.ascontiguousarray(counts, dtype=np.uint32)
+    out = np.empty((counts.size, len(_STAT_KEYS)), dtype=np.float64)
+    _check(_lib.ss_drop_stats_many(counts.ctypes.data, counts.size, n_samples, population,
+                                   n_hot_inputs, t_crit, out.ctypes.data))
+    return out
 
 
 class AccessCounters:

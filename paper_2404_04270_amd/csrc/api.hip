@@ -200,6 +200,36 @@ int32_t check_filter(const char *who, const ss_tables *tables, const int32_t *id
     return check_ws(who, ws, ws_bytes, filter_ws_bytes(tables->num_tables, B, L));
 }
 
+static int32_t check_sample(const char *who, int32_t num_tables, int32_t *const *hot_ids, int32_t H,
+                            double *const *drift, const int32_t *sidx, int32_t S, int32_t L)
+{
+    if (num_tables < 1 || num_tables > 65535)
+        return fail(SS_ERR_INVALID_ARG, "%s: num_tables = %d (need 1..65535)", who,
+                    num_tables);
+    if (!hot_ids || !drift)
+        return fail(SS_ERR_INVALID_ARG, "%s: hot_ids or drift is NULL", who);
+    if (H < 0) return fail(SS_ERR_INVALID_ARG, "%s: H = %d", who, H);
+    if (S < 0) return fail(SS_ERR_INVALID_ARG, "%s: S = %d", who, S);
+    if (L < 1) return fail(SS_ERR_INVALID_ARG, "%s: L = %d", who, L);
+    if (S > 0 && !sidx) return fail(SS_ERR_INVALID_ARG, "%s: sidx is NULL", who);
+    if ((int64_t)S * L >= (1LL << 31) || (int64_t)num_tables * L >= (1LL << 31))
+        return fail(SS_ERR_UNSUPPORTED, "%s: S*L or T*L does not fit in int32", who);
+    return SS_OK;
+}
+
+static int32_t check_thresholds(const char *who, const float *thresholds, int32_t n_thr,
+                                int32_t most, const uint32_t *counts)
+{
+    if (n_thr < 1 || n_thr > most)
+        return fail(SS_ERR_INVALID_ARG, "%s: n_thr = %d (need 1..%d)", who, n_thr, most);
+    if (!thresholds || !counts)
+        return fail(SS_ERR_INVALID_ARG, "%s: thresholds or counts is NULL", who);
+    for (int k = 0; k < n_thr; ++k)
+        if (thresholds[k] != thresholds[k])
+            return fail(SS_ERR_INVALID_ARG, "%s: thresholds[%d] is NaN", who, k);
+    return SS_OK;
+}
+
 int32_t check_backward(const char *who, const ss_tables *tables, int32_t Bcap,
                        int32_t L, const void *ws, size_t ws_bytes)
 {
@@ -516,29 +546,38 @@ int32_t ss_sample_drop(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
                        int32_t n_thr, uint32_t *counts, void *stream)
 {
     const char *who = "ss_sample_drop";
-    if (num_tables < 1 || num_tables > 65535)
-        return fail(SS_ERR_INVALID_ARG, "%s: num_tables = %d (need 1..65535)", who,
-                    num_tables);
-    if (!hot_ids || !drift)
-        return fail(SS_ERR_INVALID_ARG, "%s: hot_ids or drift is NULL", who);
-    if (H < 0) return fail(SS_ERR_INVALID_ARG, "%s: H = %d", who, H);
-    if (S < 0) return fail(SS_ERR_INVALID_ARG, "%s: S = %d", who, S);
-    if (L < 1) return fail(SS_ERR_INVALID_ARG, "%s: L = %d", who, L);
-    if (S > 0 && !sidx) return fail(SS_ERR_INVALID_ARG, "%s: sidx is NULL", who);
-    if ((int64_t)S * L >= (1LL << 31) || (int64_t)num_tables * L >= (1LL << 31))
-        return fail(SS_ERR_UNSUPPORTED, "%s: S*L or T*L does not fit in int32", who);
+    int32_t rc = check_sample(who, num_tables, hot_ids, H, drift, sidx, S, L);
+    if (rc) return rc;
     if (alpha < 0) return fail(SS_ERR_INVALID_ARG, "%s: alpha = %d", who, alpha);
-    if (n_thr < 1 || n_thr > SS_MAX_THRESHOLDS)
-        return fail(SS_ERR_INVALID_ARG, "%s: n_thr = %d (need 1..%d)", who, n_thr,
-                    SS_MAX_THRESHOLDS);
-    if (!thresholds || !counts)
-        return fail(SS_ERR_INVALID_ARG, "%s: thresholds or counts is NULL", who);
-    for (int k = 0; k < n_thr; ++k)
-        if (thresholds[k] != thresholds[k])
-            return fail(SS_ERR_INVALID_ARG, "%s: thresholds[%d] is NaN", who, k);
+    rc = check_thresholds(who, thresholds, n_thr, SS_MAX_THRESHOLDS, counts);
+    if (rc) return rc;
     return launch_sample_drop(num_tables, hot_ids, H, drift, sidx, S, L, alpha,
                               thresholds, n_thr, counts,
                               static_cast<hipStream_t>(stream));
+}
+
+int32_t ss_sample_levels(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
+                         double *const *drift, const int32_t *sidx, int32_t S, int32_t L,
+                         double *levels, void *stream)
+{
+    const char *who = "ss_sample_levels";
+    const int32_t rc = check_sample(who, num_tables, hot_ids, H, drift, sidx, S, L);
+    if (rc) return rc;
+    if (S > 0 && !levels) return fail(SS_ERR_INVALID_ARG, "%s: levels is NULL", who);
+    return launch_sample_levels(num_tables, hot_ids, H, drift, sidx, S, L, levels,
+                                static_cast<hipStream_t>(stream));
+}
+
+int32_t ss_level_counts(const double *levels, int32_t S, const float *thresholds, int32_t n_thr,
+                        uint32_t *counts, void *stream)
+{
+    const char *who = "ss_level_counts";
+    if (S < 0) return fail(SS_ERR_INVALID_ARG, "%s: S = %d", who, S);
+    if (S > 0 && !levels) return fail(SS_ERR_INVALID_ARG, "%s: levels is NULL", who);
+    const int32_t rc = check_thresholds(who, thresholds, n_thr, SS_MAX_LEVEL_THRESHOLDS, counts);
+    if (rc) return rc;
+    return launch_level_counts(levels, S, thresholds, n_thr, counts,
+                               static_cast<hipStream_t>(stream));
 }
 
 int32_t ss_drop_stats(uint32_t count, int64_t n_samples, int64_t population,
@@ -569,6 +608,19 @@ int32_t ss_drop_stats(uint32_t count, int64_t n_samples, int64_t population,
     out[5] = share * scale;
     out[6] = (share - half) * scale;
     out[7] = (share + half) * scale;
+    return SS_OK;
+}
+
+int32_t ss_drop_stats_many(const uint32_t *counts, int32_t n, int64_t n_samples,
+                           int64_t population, int64_t n_hot_inputs, double t_crit, double *out)
+{
+    if (n < 0 || (n > 0 && (!counts || !out)))
+        return fail(SS_ERR_INVALID_ARG, "ss_drop_stats_many: n = %d, counts or out is NULL", n);
+    for (int32_t k = 0; k < n; ++k) {
+        const int32_t rc = ss_drop_stats(counts[k], n_samples, population, n_hot_inputs, t_crit,
+                                         out + 8 * (int64_t)k);
+        if (rc) return rc;
+    }
     return SS_OK;
 }
 

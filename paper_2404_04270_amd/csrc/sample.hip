@@ -47,18 +47,14 @@ constexpr int64_t kMaxGroups = 512;
 
 typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
 
-// Classes of N lookups of input s: q0, q0 + step, ... of its TL (those at TL or beyond:
-// none).  The class of a lookup is the first threshold its row's drift does not exceed, K where
-// there is none or the row is not hot.
+// Drifts of N lookups of input s: q0, q0 + step, ... of its TL (a lookup at TL or beyond: that of
+// q0).  found[i]: the row is hot; d[i] means nothing otherwise.
 template <int N>
-__device__ __forceinline__ void lookup_classes(
+__device__ __forceinline__ void lookup_drifts(
     const int32_t *const *__restrict__ hot_ids, int H, const double *const *__restrict__ drift,
     const int32_t *__restrict__ sidx, int S, uint32_t L, uint32_t TL, int s, uint32_t q0,
-    uint32_t step, const double *s_thr, int (&cls)[N])
+    uint32_t step, double (&d)[N], bool (&found)[N])
 {
-    constexpr int K = SS_MAX_THRESHOLDS;
-    static_assert(K == 32, "the class search takes five steps");
-    double d[N];
     int32_t row[N];
     int base[N];
     gptr<const int32_t> ids[N];
@@ -81,7 +77,6 @@ __device__ __forceinline__ void lookup_classes(
             if (ids[i][base[i] + half] <= row[i]) base[i] += half;
         n -= half;
     }
-    bool found[N];
     if (H >= 4) {
         i4 four[N];
 #pragma unroll
@@ -106,6 +101,21 @@ __device__ __forceinline__ void lookup_classes(
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) d[i] = dr[i][base[i]];
+}
+
+// Classes of those lookups (at TL or beyond: none).  The class of a lookup is the first threshold
+// its row's drift does not exceed, K where there is none or the row is not hot.
+template <int N>
+__device__ __forceinline__ void lookup_classes(
+    const int32_t *const *__restrict__ hot_ids, int H, const double *const *__restrict__ drift,
+    const int32_t *__restrict__ sidx, int S, uint32_t L, uint32_t TL, int s, uint32_t q0,
+    uint32_t step, const double *s_thr, int (&cls)[N])
+{
+    constexpr int K = SS_MAX_THRESHOLDS;
+    static_assert(K == 32, "the class search takes five steps");
+    double d[N];
+    bool found[N];
+    lookup_drifts(hot_ids, H, drift, sidx, S, L, TL, s, q0, step, d, found);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         // same verdict as ss_detect_stale; a NaN drift exceeds all thresholds
@@ -214,6 +224,139 @@ __global__ __launch_bounds__(256) void sample_drop_few_kernel(
     add_counts(s_inputs, ladder, n_thr, counts);
 }
 
+// ---- one level per input -------------------------------------------------
+// With alpha = T * L an input can be dropped from the largest drift of its lookups on, whatever the
+// thresholds are: a search over several ladders maps rows to hot slots once and then counts levels.
+// (A threshold search over 65536 inputs of 26 lookups, 5000 hot rows: three passes of the kernel
+// above 75 us; levels 20 us and 10 per count.)  NaN: a lookup that is never stale.
+template <int I>
+__global__ __launch_bounds__(64 * kMaxWaves) void sample_level_kernel(
+    const int32_t *const *__restrict__ hot_ids, int H,
+    const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
+    int L, int TL, double *__restrict__ levels)
+{
+    __shared__ double s_level[64 * kMaxWaves];
+    const int tid = threadIdx.x, in = tid & (I - 1);
+    const uint32_t first_q = I == 64 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid / I;
+    const uint32_t step = blockDim.x / I;
+    const int64_t s0 = (int64_t)blockIdx.x * I;
+    const int s = s0 + in < S ? (int)(s0 + in) : S - 1;
+    double level = H > 0 ? 0.0 : __builtin_nan("");       // (a drift is never below 0)
+    for (uint32_t q0 = first_q; q0 < (uint32_t)TL && H > 0; q0 += step * kBatch) {
+        double d[kBatch];
+        bool found[kBatch];
+        lookup_drifts(hot_ids, H, drift, sidx, S, L, TL, s, q0, step, d, found);
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const double x = found[i] ? d[i] : __builtin_nan("");
+            level = level >= x || level != level ? level : x;
+        }
+    }
+    s_level[tid] = level;
+    __syncthreads();
+    if (tid < I && s0 + tid < S) {
+        for (uint32_t k = 1; k < step; ++k) {
+            const double x = s_level[k * I + tid];
+            level = level >= x || level != level ? level : x;
+        }
+        levels[s0 + tid] = level;
+    }
+}
+
+// Threshold k = blockIdx.x: how many levels it reaches.  A workgroup reads all of its part's
+// levels, sixteen at a time per thread, so that counts need neither clearing nor adding up (65536
+// levels: 10 us, with eight at a time as well: the rate at which one compute unit reads).
+struct LevelLadder {
+    double thr[SS_MAX_LEVEL_THRESHOLDS];
+};
+constexpr int kLevelThreads = 1024;
+constexpr int kLevelPart = 1 << 17;          // levels per workgroup
+__global__ __launch_bounds__(kLevelThreads) void level_count_kernel(
+    const double *__restrict__ levels, int S, LevelLadder ladder, uint32_t *__restrict__ counts)
+{
+    __shared__ uint32_t s_sum[kLevelThreads / 64];
+    const int tid = threadIdx.x;
+    const double thr = ladder.thr[blockIdx.x];
+    const int64_t p0 = (int64_t)blockIdx.y * kLevelPart;
+    const int64_t p1 = p0 + kLevelPart < S ? p0 + kLevelPart : S;
+    uint32_t n = 0;
+    constexpr int U = 16;
+    for (int64_t i0 = p0 + tid; i0 < p1; i0 += U * kLevelThreads) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + u * kLevelThreads;
+            v[u] = levels[i < p1 ? i : i0];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) n += i0 + u * kLevelThreads < p1 && v[u] <= thr ? 1u : 0u;
+    }
+    for (int off = 32; off; off >>= 1) n += __shfl_xor(n, off);
+    if ((tid & 63) == 0) s_sum[tid >> 6] = n;
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t all = 0;
+        for (int w = 0; w < kLevelThreads / 64; ++w) all += s_sum[w];
+        if (gridDim.y == 1) counts[blockIdx.x] = all;
+        else if (all) atomicAdd(&counts[blockIdx.x], all);
+    }
+}
+
+// Inputs per workgroup of the general kernels, 64 / I lanes of each wavefront for one.
+static int inputs_per_group(int S, int TL)
+{
+    // With 64 inputs each there are S / 64 workgroups, and a lane of eight wavefronts has
+    // TL / 32 rounds of searches before it.  Where both leave the chip waiting an input
+    // gets 4 or 16 lanes of every wavefront.  us with 64 / 16 / 4 inputs per workgroup, and
+    // with a group of lanes per input and no regard to tables as it once was, 5000 hot rows
+    // next to each other and Zipf lookups; the same scattered and uniform:
+    //    2000 inputs of 1280   208 / 63 / 32, 42        275 / 89 / 76, 102
+    //    9000 of 1280          227 / 152 / 122, 135     277 / 325 / 306, 408
+    //    4096 of 520           76 / 28 / 31, 41         116 / 58 / 68, 98
+    //    9000 of 520           88 / 64 / 63, 77         125 / 137 / 144, 200
+    //   12000 of 520           94 / 65 / 81, 99         131 / 158 / 190, 261
+    //   16000 of 520           95 / 80 / 102, 125       144 / 207 / 249, 347
+    //    5950 of 104           23 / 14 / 19, 22         32 / 24 / 27, 37
+    int I = 64;
+    if (TL > kMaxWaves * kBatch && S <= 12288) I = 16;
+    if ((TL > kMaxWaves * kBatch * 4 && S <= 4096) || (TL > 1024 && S <= 16384)) I = 4;
+    return I;
+}
+
+int32_t launch_sample_levels(int T, int32_t *const *hot_ids, int H, double *const *drift,
+                             const int32_t *sidx, int S, int L, double *levels, hipStream_t s)
+{
+    if (S > 0) {
+        const int TL = T * L, I = inputs_per_group(S, TL), per_wave = kBatch * (64 / I);
+        int waves = (TL + per_wave - 1) / per_wave;
+        if (waves > kMaxWaves) waves = kMaxWaves;
+        const unsigned grid = (unsigned)(((int64_t)S + I - 1) / I);
+        ProfScope prof("sample_level_kernel", s);
+#define SS_LEVEL(I_)                                                                        \
+    launch(sample_level_kernel<I_>, dim3(grid), dim3(64 * waves), s,                         \
+           (const int32_t *const *)hot_ids, H, (const double *const *)drift, sidx, S, L, TL, levels)
+        if (I == 64) SS_LEVEL(64);
+        else if (I == 16) SS_LEVEL(16);
+        else SS_LEVEL(4);
+#undef SS_LEVEL
+    }
+    return check_launch("ss_sample_levels");
+}
+
+int32_t launch_level_counts(const double *levels, int S, const float *thresholds, int n_thr,
+                            uint32_t *counts, hipStream_t s)
+{
+    LevelLadder ladder = {};
+    for (int k = 0; k < n_thr; ++k)
+        ladder.thr[k] = thresholds[k] > 0.0f ? (double)thresholds[k] : -1.0;
+    const int64_t parts = S > 0 ? ((int64_t)S + kLevelPart - 1) / kLevelPart : 1;
+    if (parts > 1) launch_zero_u32(counts, n_thr, s);
+    ProfScope prof("level_count_kernel", s);
+    launch(level_count_kernel, dim3(n_thr, (unsigned)parts), dim3(kLevelThreads), s, levels, S,
+           ladder, counts);
+    return check_launch("ss_level_counts");
+}
+
 int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const *drift,
                            const int32_t *sidx, int S, int L, int alpha,
                            const float *thresholds, int n_thr, uint32_t *counts,
@@ -251,21 +394,7 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
             if (TL <= kBatch) SS_SAMPLE(sample_drop_few_kernel<kBatch>, grid, 256);
             else SS_SAMPLE(sample_drop_few_kernel<2 * kBatch>, grid, 256);
         } else {
-            // With 64 inputs each there are S / 64 workgroups, and a lane of eight wavefronts has
-            // TL / 32 rounds of searches before it.  Where both leave the chip waiting an input
-            // gets 4 or 16 lanes of every wavefront.  us with 64 / 16 / 4 inputs per workgroup, and
-            // with a group of lanes per input and no regard to tables as it once was, 5000 hot rows
-            // next to each other and Zipf lookups; the same scattered and uniform:
-            //    2000 inputs of 1280   208 / 63 / 32, 42        275 / 89 / 76, 102
-            //    9000 of 1280          227 / 152 / 122, 135     277 / 325 / 306, 408
-            //    4096 of 520           76 / 28 / 31, 41         116 / 58 / 68, 98
-            //    9000 of 520           88 / 64 / 63, 77         125 / 137 / 144, 200
-            //   12000 of 520           94 / 65 / 81, 99         131 / 158 / 190, 261
-            //   16000 of 520           95 / 80 / 102, 125       144 / 207 / 249, 347
-            //    5950 of 104           23 / 14 / 19, 22         32 / 24 / 27, 37
-            int I = 64;
-            if (TL > kMaxWaves * kBatch && S <= 12288) I = 16;
-            if ((TL > kMaxWaves * kBatch * 4 && S <= 4096) || (TL > 1024 && S <= 16384)) I = 4;
+            const int I = inputs_per_group(S, TL);
             const int per_wave = kBatch * (64 / I);
             int waves = (TL + per_wave - 1) / per_wave;
             if (waves > kMaxWaves) waves = kMaxWaves;

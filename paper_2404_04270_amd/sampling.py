@@ -26,8 +26,9 @@ def geometric_ladder(lo: float, hi: float, n: int) -> List[float]:
     """n thresholds strictly inside (lo, hi), evenly spaced in the logarithm."""
     if not (0.0 < lo < hi) or n < 1:
         raise ValueError("need 0 < lo < hi and n >= 1")
-    step = (math.log(hi) - math.log(lo)) / (n + 1)
-    return [math.exp(math.log(lo) + step * (k + 1)) for k in range(n)]
+    first = math.log(lo)
+    step = (math.log(hi) - first) / (n + 1)
+    return [math.exp(first + step * (k + 1)) for k in range(n)]
 
 
 def ladder_search(upper_bounds: Callable[[Sequence[float]], Sequence[float]],
@@ -105,5 +106,29 @@ class SamplingBlock:
 
     def find_threshold(self, budget: float, lo: float, hi: float, passes: int = 2):
         """See ladder_search; call refresh_drift() first."""
-        return ladder_search(lambda ts: [e["hi"] for e in self.estimate(ts)],
-                             lo, hi, budget, passes, self._B.MAX_THRESHOLDS)
+        width = self._B.MAX_THRESHOLDS
+        if self.alpha != int(self.sidx.shape[0] * self.sidx.shape[2]):
+            return ladder_search(lambda ts: [e["hi"] for e in self.estimate(ts)],
+                                 lo, hi, budget, passes, width)
+        # every lookup has to be stale: the inputs' rows are mapped to drifts once, for all ladders
+        import torch
+        B, dev = self._B, self.sidx.device
+        levels = torch.empty(self.sidx.shape[1], dtype=torch.float64, device=dev)
+        counts = torch.empty(B.MAX_LEVEL_THRESHOLDS, dtype=torch.int32, device=dev)
+        B.ss_sample_levels(self.hot, self.sidx, levels)
+        priced = {}
+
+        def upper_bounds(ts):
+            if not all(t in priced for t in ts):
+                ask = list(ts)
+                if not priced and passes > 0 and 0.0 < lo < hi:
+                    # the ends and the ladder between them in one wait for the GPU
+                    ask += geometric_ladder(lo, hi, width)
+                B.ss_level_counts(levels, ask, counts)
+                got = counts[:len(ask)].cpu().numpy().view("uint32")
+                stats = B.ss_drop_stats_many(got, self.n_samples, self.population,
+                                             self.n_hot_inputs, self.t_crit)
+                priced.update(zip(ask, stats[:, B._STAT_KEYS.index("hi")].tolist()))
+            return [priced[t] for t in ts]
+
+        return ladder_search(upper_bounds, lo, hi, budget, passes, width)
