@@ -32,7 +32,9 @@
 #include <algorithm>
 #include <chrono>
 #include <deque>
+#include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -386,6 +388,72 @@ int auto_threads(int T, int B, int L, int n_side)
     return n_side >= 3 ? n_side : 1;
 }
 
+// Index streams, shared by all steps of a device.  The GPU runs a process's streams on a few
+// hardware queues (four by default); with more streams than that, streams that share a queue wait
+// for each other, a step's index work for its own training kernels, say.  A program that keeps
+// several steps (tables of several row lengths, say) trains them in turn, so one set of streams
+// serves all of them.  us per training step with a few steps alive and used in turn, streams of
+// their own and in common: one table of 200 M rows x 65536 lookups (three streams) 31 and 26, 26
+// tables x 8192 (one stream) 44.2 and 41.2, with all hot rows stale 37.1 and 34.7, 26 x 40000 (two)
+// 102.2 and 99.7; with a single step alive 26 for the first either way.  Work of two steps on one stream only gains an order it would not need: every wait on it is for an event
+// recorded before.  The first n streams of a device are handed out; the last step that gives them
+// back destroys them.
+class IndexStreams {
+public:
+    static int32_t acquire(int device, int n, std::vector<hipStream_t> *out)
+    {
+        std::lock_guard<std::mutex> lk(mutex());
+        try {
+            Pool &p = pools()[device];
+            out->reserve(n);
+            p.streams.reserve(n);
+            while ((int)p.streams.size() < n) {
+                hipStream_t s = nullptr;
+                // default priority; non-blocking, so that it never orders itself against the
+                // legacy default stream
+                if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
+                    if (p.users == 0) destroy(device);
+                    return SS_ERR_HIP;
+                }
+                p.streams.push_back(s);
+            }
+            ++p.users;
+            out->assign(p.streams.begin(), p.streams.begin() + n);
+        } catch (const std::bad_alloc &) {
+            return SS_ERR_HIP;
+        }
+        return SS_OK;
+    }
+    static void release(int device)
+    {
+        std::lock_guard<std::mutex> lk(mutex());
+        const auto it = pools().find(device);
+        if (it != pools().end() && --it->second.users == 0) destroy(device);
+    }
+
+private:
+    struct Pool {
+        std::vector<hipStream_t> streams;
+        int users = 0;
+    };
+    static void destroy(int device)
+    {
+        for (hipStream_t s : pools()[device].streams) (void)hipStreamDestroy(s);
+        pools().erase(device);
+    }
+    // never destroyed: a step may be given back while the process ends
+    static std::mutex &mutex()
+    {
+        static std::mutex *m = new std::mutex;
+        return *m;
+    }
+    static std::map<int, Pool> &pools()
+    {
+        static std::map<int, Pool> *p = new std::map<int, Pool>;
+        return *p;
+    }
+};
+
 // ---- the real operations: library kernels, HIP events, issue queues --------
 struct GpuOps final : StepOps {
     ss_tables tables;
@@ -399,7 +467,8 @@ struct GpuOps final : StepOps {
     uint32_t *stale_count;
     float *pooled;
     hipStream_t main;
-    std::vector<hipStream_t> sides;
+    std::vector<hipStream_t> sides;      // of IndexStreams
+    int device = -1;                     // ... which they belong to
     std::vector<ss_issue_queue *> queues;
     std::vector<void *> events;
 
@@ -485,7 +554,7 @@ struct GpuOps final : StepOps {
         for (hipStream_t s : sides) (void)hipStreamSynchronize(s);
         for (void *e : events) (void)ss_event_destroy(e);
         events.clear();
-        for (hipStream_t s : sides) (void)hipStreamDestroy(s);
+        if (!sides.empty()) IndexStreams::release(device);
         sides.clear();
         return rc;
     }
@@ -677,14 +746,10 @@ int32_t ss_step_create(const ss_tables *tables, int32_t B, int32_t L, int32_t al
     ops->stale_count = stale_count;
     ops->pooled = pooled;
     ops->main = static_cast<hipStream_t>(train_stream);
-    for (int j = 0; j < plan->index_streams; ++j) {
-        hipStream_t s = nullptr;
-        // default priority; non-blocking, so that it never orders itself against the
-        // legacy default stream
-        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess)
-            return fail(SS_ERR_HIP, "%s: hipStreamCreateWithFlags failed", who);
-        ops->sides.push_back(s);
-    }
+    if (hipGetDevice(&ops->device) != hipSuccess)
+        return fail(SS_ERR_HIP, "%s: hipGetDevice failed", who);
+    if (IndexStreams::acquire(ops->device, plan->index_streams, &ops->sides) != SS_OK)
+        return fail(SS_ERR_HIP, "%s: no index streams", who);
     for (int q = 0; q < plan->issue_threads; ++q) {
         ss_issue_queue *iq = nullptr;
         rc = ss_issue_queue_create(&iq);
