@@ -281,7 +281,8 @@ int32_t ss_sample_drop(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
  * one sample: ss_sample_levels finds for every input the threshold from which on it can be dropped
  * (the largest drift of its lookups, NaN where one of them is never stale), ss_level_counts
  * counts the levels each threshold reaches.  The counts are those of ss_sample_drop.
- *   levels       device fp64 [S]
+ *   levels       device fp32 [S], rounded up: a threshold is an fp32 number, and reaches the rounded
+ *                level where it reaches the level
  *   thresholds   HOST array of n_thr floats (1 <= n_thr <= SS_MAX_LEVEL_THRESHOLDS), read before
  *                the call returns; any order; NaN is rejected
  *   counts       device uint32 [n_thr], overwritten
@@ -289,8 +290,8 @@ int32_t ss_sample_drop(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
 #define SS_MAX_LEVEL_THRESHOLDS 64
 int32_t ss_sample_levels(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
                          double *const *drift, const int32_t *sidx, int32_t S, int32_t L,
-                         double *levels, void *stream);
-int32_t ss_level_counts(const double *levels, int32_t S, const float *thresholds, int32_t n_thr,
+                         float *levels, void *stream);
+int32_t ss_level_counts(const float *levels, int32_t S, const float *thresholds, int32_t n_thr,
                         uint32_t *counts, void *stream);
 
 /*

@@ -502,7 +502,7 @@ MAX_LEVEL_THRESHOLDS = 64
 
 def ss_sample_levels(hot: HotState, sidx: torch.Tensor, levels: torch.Tensor,
                      stream=None) -> None:
-    """levels fp64 [S]: the threshold from which on each input of sidx (int32 [T, S, L]) can be
+    """levels fp32 [S]: the threshold from which on each input of sidx (int32 [T, S, L]) can be
     dropped when all its lookups have to be stale; reads hot.drift."""
     if hot.drift is None:
         raise SlipstreamError("ss_sample_levels: HotState was built without diagnostics")
@@ -513,7 +513,7 @@ def ss_sample_levels(hot: HotState, sidx: torch.Tensor, levels: torch.Tensor,
     _check(_lib.ss_sample_levels(
         len(hot.hot_ids), hot._hptr.data_ptr(), hot.H, hot._dptr.data_ptr(),
         _ptr(sidx, torch.int32, "sidx"), sidx.shape[1], sidx.shape[2],
-        _ptr(levels, torch.float64, "levels"), _stream_ptr(stream)))
+        _ptr(levels, torch.float32, "levels"), _stream_ptr(stream)))
 
 
 def ss_level_counts(levels: torch.Tensor, thresholds: Sequence[float], counts: torch.Tensor,
@@ -523,7 +523,7 @@ def ss_level_counts(levels: torch.Tensor, thresholds: Sequence[float], counts: t
     if counts.numel() < len(thresholds):
         raise SlipstreamError("ss_level_counts: counts is shorter than thresholds")
     _check(_lib.ss_level_counts(
-        _ptr(levels, torch.float64, "levels"), levels.numel(), thr, len(thresholds),
+        _ptr(levels, torch.float32, "levels"), levels.numel(), thr, len(thresholds),
         _ptr(counts, torch.int32, "counts"), _stream_ptr(stream)))
 
 

@@ -558,7 +558,7 @@ int32_t ss_sample_drop(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
 
 int32_t ss_sample_levels(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
                          double *const *drift, const int32_t *sidx, int32_t S, int32_t L,
-                         double *levels, void *stream)
+                         float *levels, void *stream)
 {
     const char *who = "ss_sample_levels";
     const int32_t rc = check_sample(who, num_tables, hot_ids, H, drift, sidx, S, L);
@@ -568,7 +568,7 @@ int32_t ss_sample_levels(int32_t num_tables, int32_t *const *hot_ids, int32_t H,
                                 static_cast<hipStream_t>(stream));
 }
 
-int32_t ss_level_counts(const double *levels, int32_t S, const float *thresholds, int32_t n_thr,
+int32_t ss_level_counts(const float *levels, int32_t S, const float *thresholds, int32_t n_thr,
                         uint32_t *counts, void *stream)
 {
     const char *who = "ss_level_counts";

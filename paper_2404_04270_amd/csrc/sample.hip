@@ -228,12 +228,22 @@ __global__ __launch_bounds__(256) void sample_drop_few_kernel(
 // With alpha = T * L an input can be dropped from the largest drift of its lookups on, whatever the
 // thresholds are: a search over several ladders maps rows to hot slots once and then counts levels.
 // (A threshold search over 65536 inputs of 26 lookups, 5000 hot rows: three passes of the kernel
-// above 75 us; levels 20 us and 10 per count.)  NaN: a lookup that is never stale.
+// above 75 us; levels 20 us and 7 per count.)  A level is kept as the least float that is not
+// below it: a threshold is a float, and reaches the one where it reaches the other.  NaN: a lookup
+// that is never stale.
+__device__ __forceinline__ float float_not_below(double x)
+{
+    float f = (float)x;
+    if ((double)f < x) {                 // (x >= 0: the next float up has the next bits)
+        f = __uint_as_float(__float_as_uint(f) + 1u);
+    }
+    return f;
+}
 template <int I>
 __global__ __launch_bounds__(64 * kMaxWaves) void sample_level_kernel(
     const int32_t *const *__restrict__ hot_ids, int H,
     const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
-    int L, int TL, double *__restrict__ levels)
+    int L, int TL, float *__restrict__ levels)
 {
     __shared__ double s_level[64 * kMaxWaves];
     const int tid = threadIdx.x, in = tid & (I - 1);
@@ -259,30 +269,30 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_level_kernel(
             const double x = s_level[k * I + tid];
             level = level >= x || level != level ? level : x;
         }
-        levels[s0 + tid] = level;
+        levels[s0 + tid] = float_not_below(level);
     }
 }
 
 // Threshold k = blockIdx.x: how many levels it reaches.  A workgroup reads all of its part's
-// levels, sixteen at a time per thread, so that counts need neither clearing nor adding up (65536
-// levels: 10 us, with eight at a time as well: the rate at which one compute unit reads).
+// levels, 32 at a time per thread, so that counts need neither clearing nor adding up (65536
+// levels: 6.7 us; 9.9 as doubles: what bounds it is the rate at which one compute unit reads).
 struct LevelLadder {
-    double thr[SS_MAX_LEVEL_THRESHOLDS];
+    float thr[SS_MAX_LEVEL_THRESHOLDS];
 };
 constexpr int kLevelThreads = 1024;
 constexpr int kLevelPart = 1 << 17;          // levels per workgroup
 __global__ __launch_bounds__(kLevelThreads) void level_count_kernel(
-    const double *__restrict__ levels, int S, LevelLadder ladder, uint32_t *__restrict__ counts)
+    const float *__restrict__ levels, int S, LevelLadder ladder, uint32_t *__restrict__ counts)
 {
     __shared__ uint32_t s_sum[kLevelThreads / 64];
     const int tid = threadIdx.x;
-    const double thr = ladder.thr[blockIdx.x];
+    const float thr = ladder.thr[blockIdx.x];
     const int64_t p0 = (int64_t)blockIdx.y * kLevelPart;
     const int64_t p1 = p0 + kLevelPart < S ? p0 + kLevelPart : S;
     uint32_t n = 0;
-    constexpr int U = 16;
+    constexpr int U = 32;
     for (int64_t i0 = p0 + tid; i0 < p1; i0 += U * kLevelThreads) {
-        double v[U];
+        float v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = i0 + u * kLevelThreads;
@@ -324,7 +334,7 @@ static int inputs_per_group(int S, int TL)
 }
 
 int32_t launch_sample_levels(int T, int32_t *const *hot_ids, int H, double *const *drift,
-                             const int32_t *sidx, int S, int L, double *levels, hipStream_t s)
+                             const int32_t *sidx, int S, int L, float *levels, hipStream_t s)
 {
     if (S > 0) {
         const int TL = T * L, I = inputs_per_group(S, TL), per_wave = kBatch * (64 / I);
@@ -343,12 +353,12 @@ int32_t launch_sample_levels(int T, int32_t *const *hot_ids, int H, double *cons
     return check_launch("ss_sample_levels");
 }
 
-int32_t launch_level_counts(const double *levels, int S, const float *thresholds, int n_thr,
+int32_t launch_level_counts(const float *levels, int S, const float *thresholds, int n_thr,
                             uint32_t *counts, hipStream_t s)
 {
     LevelLadder ladder = {};
     for (int k = 0; k < n_thr; ++k)
-        ladder.thr[k] = thresholds[k] > 0.0f ? (double)thresholds[k] : -1.0;
+        ladder.thr[k] = thresholds[k] > 0.0f ? thresholds[k] : -1.0f;
     const int64_t parts = S > 0 ? ((int64_t)S + kLevelPart - 1) / kLevelPart : 1;
     if (parts > 1) launch_zero_u32(counts, n_thr, s);
     ProfScope prof("level_count_kernel", s);

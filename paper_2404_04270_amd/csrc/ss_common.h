@@ -300,8 +300,8 @@ int32_t launch_sample_drop(int T, int32_t *const *hot_ids, int H, double *const 
                            const float *thresholds, int n_thr, uint32_t *counts,
                            hipStream_t s);
 int32_t launch_sample_levels(int T, int32_t *const *hot_ids, int H, double *const *drift,
-                             const int32_t *sidx, int S, int L, double *levels, hipStream_t s);
-int32_t launch_level_counts(const double *levels, int S, const float *thresholds, int n_thr,
+                             const int32_t *sidx, int S, int L, float *levels, hipStream_t s);
+int32_t launch_level_counts(const float *levels, int S, const float *thresholds, int n_thr,
                             uint32_t *counts, hipStream_t s);
 int32_t launch_count_accesses(int T, const int32_t *idx, int Bcap, int L,
                               const int32_t *n_valid, uint32_t *const *counts,

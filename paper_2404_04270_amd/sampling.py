@@ -113,7 +113,7 @@ class SamplingBlock:
         # every lookup has to be stale: the inputs' rows are mapped to drifts once, for all ladders
         import torch
         B, dev = self._B, self.sidx.device
-        levels = torch.empty(self.sidx.shape[1], dtype=torch.float64, device=dev)
+        levels = torch.empty(self.sidx.shape[1], dtype=torch.float32, device=dev)
         counts = torch.empty(B.MAX_LEVEL_THRESHOLDS, dtype=torch.int32, device=dev)
         B.ss_sample_levels(self.hot, self.sidx, levels)
         priced = {}

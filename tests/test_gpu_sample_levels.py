@@ -39,7 +39,7 @@ def test_levels_count_what_sample_drop_counts(T, R, H, S, L, cold, odd):
     other = torch.rand(T, S, L, device="cuda", generator=gen) < cold
     sidx[other] = torch.randint(-1, R + 2, (int(other.sum()),), device="cuda", generator=gen,
                                 dtype=torch.int32)
-    levels = torch.full((S,), -7.0, dtype=torch.float64, device="cuda")
+    levels = torch.full((S,), -7.0, device="cuda")
     B.ss_sample_levels(hot, sidx, levels)
     some = float(np.float32(hot.drift[0][-1].item()))
     thr = [1e-2, 0.0, some, 1e-5, math.inf, 3e-4, -1.0, 1e30, 1e-4, 1e-3] + \
@@ -59,7 +59,7 @@ def test_levels_count_what_sample_drop_counts(T, R, H, S, L, cold, odd):
 def test_no_hot_rows():
     from paper_2404_04270_amd import binding as B
     empty = torch.zeros(1, 1, dtype=torch.int64, device="cuda")
-    levels = torch.zeros(5, dtype=torch.float64, device="cuda")
+    levels = torch.zeros(5, device="cuda")
     sidx = torch.zeros(1, 5, 2, dtype=torch.int32, device="cuda")
     B._check(B._lib.ss_sample_levels(1, empty.data_ptr(), 0, empty.data_ptr(), sidx.data_ptr(), 5, 2,
                                      levels.data_ptr(), B._stream_ptr(None)))
