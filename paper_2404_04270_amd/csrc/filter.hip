@@ -319,11 +319,12 @@ __global__ __launch_bounds__(kSmallThreads) void filter_small_kernel(
 
 // Lanes per sample of the one-launch filter, 0 where the batch is not for it.  Every table's
 // workgroup probes the bitmaps for the whole batch, so what that may cost at worst, with all hot
-// rows stale, is bounded: 16384 lookups in all, and no lane more than two rounds behind its first,
-// one where bags are long (their index words lie apart).  us with two launches, the gap between
-// them not counted, and with one, no row stale and all hot rows stale: 8 tables x 128 lookups
-// 5.3 and 4.1, 4.9 and 4.2; 5 x 777 bags of 3 5.9 and 4.0, 6.2 and 8.8; 16 x 1024 5.6 and 4.2, 6.4
-// and 8.4; a training step call by call 22.3 and 20.2 at 8 x 128, 24.3 and 22.7 at 5 x 777 x 3.
+// rows stale, is bounded: 16384 lookups in all, and no lane more than two rounds behind its
+// first, one where bags are long (their index words lie apart).  us of kernels (event pairs,
+// less the 2 us that a pair adds) in two launches and in one, no row stale and all hot rows
+// stale: 8 tables x 128 lookups 5.3 and 4.1, 4.9 and 4.2; 5 x 777 bags of 3 5.9 and 4.0, 6.2 and
+// 8.8; 16 x 1024 5.6 and 4.2, 6.4 and 8.4; a training step call by call 22.3 and 20.2 at 8 x
+// 128, 24.3 and 22.7 at 5 x 777 x 3.
 static int small_lanes(int64_t B, int L, int64_t total)
 {
     if (B > kSmallThreads || B * total > 16384) return 0;
