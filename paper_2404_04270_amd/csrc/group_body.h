@@ -512,15 +512,19 @@ struct ClassSortPlan {
 // classes of a table read all of its lookups (us by the average class of 256 / 512 / 1024 / 2048
 // lookups: 8 tables x 4096 7.7 / 8.4 / 10.2, 8 x 16384 17.9 / 12.5 / 13.8, 26 x 2048 7.7 / 7.7 /
 // 9.1, 26 x 8192 21 / 15 / 11.4 / 16, 64 x 8192 41 / 25 / 18.4 / 16.4).
+// The classes decide the order of the list, and so where runs of equal rows are cut and how their sums
+// round: they depend on the batch alone, not on `threads`, with which a caller asks for a workgroup
+// size of its own.
 inline ClassSortPlan plan_class_sort(int T, int nnz, int key_bits, int threads = 0)
 {
     ClassSortPlan p;
-    p.threads = threads ? threads : nnz > 4096 ? 1024 : 512;
+    const int own = nnz > 4096 ? 1024 : 512;
+    p.threads = threads ? threads : own;
     const int it = (nnz + p.threads - 1) / p.threads;
     p.items = it <= 1 ? 1 : it <= 2 ? 2 : it <= 4 ? 4 : it <= 8 ? 8 : 16;
     p.class_bits = 0;
     while ((256 << p.class_bits) < nnz && p.class_bits < key_bits &&
-           (((int64_t)T << (p.class_bits + 1)) <= 256 || (2 * p.threads) << p.class_bits < nnz))
+           (((int64_t)T << (p.class_bits + 1)) <= 256 || (2 * own) << p.class_bits < nnz))
         ++p.class_bits;
     p.pos_bits = 1;
     while ((1 << p.pos_bits) < nnz) ++p.pos_bits;
