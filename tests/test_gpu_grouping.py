@@ -107,3 +107,40 @@ def test_fused_grouping_leaves_the_bits_of_the_separate_calls(T, B):
         left.append((out, w))
     assert torch.equal(left[0][0], left[1][0])
     assert torch.equal(left[0][1], left[1][1])
+
+
+def _best_us(call):
+    call()
+    best = float("inf")
+    for _ in range(5):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(10):
+            call()
+        end.record()
+        end.synchronize()
+        best = min(best, begin.elapsed_time(end) * 100.0)
+    return best
+
+
+@pytest.mark.parametrize("L", [2, 3, 4, 8])
+def test_periodic_bags_take_no_longer_than_the_same_lookups_in_any_order(L):
+    # L constant ids in every bag: each of them has its share of a class's lookups, at places that
+    # repeat with the bags.  Ids that are not recognized as heavy cost a comparison per pair of
+    # their lookups (64 tables, of which some have ids of one class: 40 times as long and more),
+    # recognized ones the same in any order of the lookups.
+    from paper_2404_04270_amd import binding as Bd
+    T, R, B = 64, 1 << 20, 16384 // L
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    tables = Bd.Tables([torch.empty(1, 4, device="cuda") for _ in range(T)])
+    tables.rows = R                        # (the grouping reads no weights)
+    tables._refresh_struct()
+    ids = torch.randint(0, R, (T, 1, L), device="cuda", generator=gen, dtype=torch.int32)
+    bags = ids.expand(T, B, L).contiguous()
+    mixed = torch.stack([b.reshape(-1)[torch.randperm(B * L, device="cuda", generator=gen)]
+                         for b in bags]).view_as(bags)
+    ws = torch.empty(Bd.ss_backward_workspace_bytes(T, B, L, 4), dtype=torch.uint8, device="cuda")
+    us = [_best_us(lambda: Bd.ss_embbag_backward_prepare(tables, i, None, ws))
+          for i in (bags, mixed)]
+    assert us[0] < 2.0 * us[1], us
