@@ -496,18 +496,19 @@ int32_t ss_stream_wait_event(void *stream, void *event);
  * with their last snapshot; the first period is the warm-up of section 3.1.1 and
  * ends with the capture of the first snapshot), scheduled so that the index work
  * of the coming batches (ss_filter_batch, ss_embbag_backward_prepare: they read
- * indices and stale bitmaps only) runs on index streams of the object's own while
- * the current batch is in its lookup and update kernels on the caller's training
- * stream.  Results are those of the calls issued one after the other on one
+ * indices and stale bitmaps only) runs on index streams while the current batch
+ * is in its lookup and update kernels on the caller's training stream.  Results are those of the calls issued one after the other on one
  * stream, bit for bit: the only reordering is that index work of later batches
  * runs before the update of earlier ones, which it does not read; batches after
  * one that ends with a detect pass are held back until that pass is enqueued.
  *
- * An ss_step is a stateful host object: it owns its index streams (default
- * priority), a fixed pool of events created at ss_step_create, and, if the plan
- * asks for them, issue threads (ss_issue_queue).  It allocates no device memory:
- * the caller hands over a ring of buffer sets and the pooled output.  Use from
- * one host thread.  Per batch, in this order:
+ * An ss_step is a stateful host object: it owns a fixed pool of events created at
+ * ss_step_create, and, if the plan asks for them, issue threads (ss_issue_queue).
+ * Its index streams (default priority) are common to all ss_steps alive on one
+ * device, which are taken to be used in turn: index work of one that has to wait
+ * (for a ready event, or for a batch to be trained on) holds up the index work
+ * that others have submitted later.  No device memory is allocated: the caller hands over a ring of buffer sets and the pooled output.
+ * Use from one host thread.  Per batch, in this order:
  *     ss_step_submit(idx)      as far ahead as ss_step_room() allows (up to two
  *                              thirds of the ring); idx must stay untouched until
  *                              the batch's ss_step_backward has been called.  If
@@ -530,8 +531,9 @@ int32_t ss_stream_wait_event(void *stream, void *event);
  * ss_step_flush returns once everything submitted so far has been handed to its
  * stream (with issue threads; a no-op otherwise), so that a device
  * synchronisation after it covers that work.  ss_step_destroy ends the threads,
- * waits for the index streams and releases streams and events (the one call of
- * this group that waits for the GPU).  Calls out of order return
+ * waits for the index work of this object and releases its events, and the index
+ * streams if no other ss_step has them (the one call of this group that waits for
+ * the GPU).  Calls out of order return
  * SS_ERR_INVALID_ARG and enqueue nothing.
  *
  * The plan: `every` batches between two cross-stream events, `index_streams`,

@@ -469,7 +469,10 @@ struct GpuOps final : StepOps {
     hipStream_t main;
     std::vector<hipStream_t> sides;      // of IndexStreams
     int device = -1;                     // ... which they belong to
+    std::vector<void *> last_work;       // per index stream: event of this step's last work on it
+    bool work_without_event = false;     // a call failed between launches
     std::vector<ss_issue_queue *> queues;
+    std::vector<uint64_t> last_job;      // per queue
     std::vector<void *> events;
 
     hipStream_t stream(int s) const { return s == kMainStream ? main : sides[s]; }
@@ -480,17 +483,26 @@ struct GpuOps final : StepOps {
         const ss_step_set &b = sets[set];
         int32_t rc = launch_filter(&tables, idx, B, L, alpha, b.skip_mask, b.kept_ids, b.n_kept,
                                    b.idx_c, b.ws_filter, stream(s));
-        if (rc) return rc;
-        return launch_backward_prepare(&tables, b.idx_c, B, L, b.n_kept, b.ws_backward, stream(s),
-                                       static_cast<hipEvent_t>(done));
+        if (!rc)
+            rc = launch_backward_prepare(&tables, b.idx_c, B, L, b.n_kept, b.ws_backward, stream(s),
+                                         static_cast<hipEvent_t>(done));
+        if (rc) work_without_event = true;
+        else last_work[s] = done;
+        return rc;
     }
     int32_t q_index(int q, int s, int set, const int32_t *idx, void *done,
                     uint64_t *ticket) override
     {
         const ss_step_set &b = sets[set];
-        return issue_index_batch(queues[q], &tables, idx, B, L, alpha, b.skip_mask, b.kept_ids,
-                                 b.n_kept, b.idx_c, b.ws_filter, b.ws_filter_bytes, b.ws_backward,
-                                 b.ws_backward_bytes, stream(s), done, ticket);
+        const int32_t rc =
+            issue_index_batch(queues[q], &tables, idx, B, L, alpha, b.skip_mask, b.kept_ids,
+                              b.n_kept, b.idx_c, b.ws_filter, b.ws_filter_bytes, b.ws_backward,
+                              b.ws_backward_bytes, stream(s), done, ticket);
+        if (!rc) {
+            last_work[s] = done;
+            last_job[q] = *ticket;
+        }
+        return rc;
     }
     int32_t lookup(int set) override
     {
@@ -534,11 +546,15 @@ struct GpuOps final : StepOps {
     }
     int32_t q_record(int q, void *ev, int s, uint64_t *t) override
     {
-        return ss_issue_record_event(queues[q], ev, stream(s), t);
+        const int32_t rc = ss_issue_record_event(queues[q], ev, stream(s), t);
+        if (!rc) last_job[q] = *t;
+        return rc;
     }
     int32_t q_wait(int q, void *ev, int s, uint64_t *t) override
     {
-        return ss_issue_wait_event(queues[q], ev, stream(s), t);
+        const int32_t rc = ss_issue_wait_event(queues[q], ev, stream(s), t);
+        if (!rc) last_job[q] = *t;
+        return rc;
     }
     int32_t q_wait_issued(int q, uint64_t t) override { return ss_issue_wait(queues[q], t); }
     int32_t shutdown() override
@@ -546,12 +562,18 @@ struct GpuOps final : StepOps {
         int32_t rc = SS_OK;
         // every queued job issued and every thread ended before any event goes: a job
         // of one queue may name an event that another queue's marks own
-        for (ss_issue_queue *q : queues) {
-            const int32_t r = ss_issue_queue_destroy(q);
+        for (size_t q = 0; q < queues.size(); ++q) {
+            if (ss_issue_wait(queues[q], last_job[q])) work_without_event = true;
+            const int32_t r = ss_issue_queue_destroy(queues[q]);
             if (r && !rc) rc = r;
         }
         queues.clear();
-        for (hipStream_t s : sides) (void)hipStreamSynchronize(s);
+        // this step's index work, not what other steps have behind it on the same streams
+        for (size_t j = 0; j < sides.size(); ++j) {
+            if (work_without_event) (void)hipStreamSynchronize(sides[j]);
+            else if (last_work[j])
+                (void)hipEventSynchronize(static_cast<hipEvent_t>(last_work[j]));
+        }
         for (void *e : events) (void)ss_event_destroy(e);
         events.clear();
         if (!sides.empty()) IndexStreams::release(device);
@@ -748,6 +770,8 @@ int32_t ss_step_create(const ss_tables *tables, int32_t B, int32_t L, int32_t al
     ops->main = static_cast<hipStream_t>(train_stream);
     if (hipGetDevice(&ops->device) != hipSuccess)
         return fail(SS_ERR_HIP, "%s: hipGetDevice failed", who);
+    ops->last_work.assign(plan->index_streams, nullptr);
+    ops->last_job.assign(plan->issue_threads, 0);
     if (IndexStreams::acquire(ops->device, plan->index_streams, &ops->sides) != SS_OK)
         return fail(SS_ERR_HIP, "%s: no index streams", who);
     for (int q = 0; q < plan->issue_threads; ++q) {

@@ -143,7 +143,7 @@ class SnapshotRing:
 class PipelinedStep:
     """The same iteration with the index work of the coming batches taken off the
     critical path: a thin front of the library's ss_step (csrc/step.hip), which
-    owns the index streams, the events and the issue threads and decides what is
+    holds the index streams, the events and the issue threads and decides what is
     enqueued where and when.  This class allocates the ring of buffer sets and the
     pooled output, and marshals arguments.
 
@@ -152,8 +152,8 @@ class PipelinedStep:
     the weights: they run on index streams while earlier batches are still in their
     lookup and update kernels.  submit() hands over the indices of a coming batch,
     as far ahead as room() allows; forward() and backward() run on the stream that
-    was current when the object was built.  Results are those of EmbeddingStep bit
-    for bit.
+    was current when the object was built.  All objects alive have their index
+    streams in common.  Results are those of EmbeddingStep bit for bit.
     """
 
     class _Set:
@@ -233,8 +233,9 @@ class PipelinedStep:
         B.ss_step_flush(self._step)
 
     def close(self) -> None:
-        """Ends the issue threads, waits for the index streams and releases the
-        library's streams and events; the object must not be used afterwards."""
+        """Ends the issue threads, waits for this object's index work and releases its
+        events, and its streams if no other object has them; it must not be used
+        afterwards."""
         if self._step is not None:
             B.ss_step_destroy(self._step)
             self._step = None

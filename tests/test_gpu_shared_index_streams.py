@@ -1,5 +1,6 @@
 """Steps that are alive together share their index streams: each has to leave what it leaves alone,
-bit for bit, whatever the others do, also from two threads and when another is closed early."""
+bit for bit, whatever the others do, also from two threads and when another is closed early; closing
+one does not wait for another."""
 import threading
 
 import pytest
@@ -74,13 +75,14 @@ def test_steps_in_turn_and_one_closed_early():
     assert _same(_alone(1), want[1])   # the streams are made again after the last was given back
 
 
-def test_two_threads():
+@pytest.mark.parametrize("one_stream", [False, True])
+def test_two_threads(one_stream):
     want = [_alone(k) for k in range(2)]
     got, errors = [None, None], []
 
     def work(k):
         try:
-            with torch.cuda.stream(torch.cuda.Stream()):
+            with torch.cuda.stream(None if one_stream else torch.cuda.Stream()):
                 step, idx, grad = _make(SHAPES[k], k)
                 for _ in _batches(step, idx, grad):
                     pass
@@ -96,3 +98,40 @@ def test_two_threads():
         t.join()
     assert not errors, errors
     assert all(_same(g, w) for g, w in zip(got, want))
+
+
+def _sleep_cycles(seconds):
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)
+    begin.record()
+    torch.cuda._sleep(1_000_000)
+    end.record()
+    end.synchronize()
+    return int(1_000_000 * seconds * 1e3 / max(begin.elapsed_time(end), 1e-3))
+
+
+def _late_event(cycles):
+    """An event that happens once a stream of its own has slept."""
+    event = torch.cuda.Event()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        torch.cuda._sleep(cycles)
+        event.record()
+    return event
+
+
+def test_closing_a_step_does_not_wait_for_the_data_of_another():
+    cycles = _sleep_cycles(0.4)
+    a, idx_a, grad_a = _make(SHAPES[0], 1)
+    b, idx_b, grad_b = _make(SHAPES[0], 2)
+    for _ in _batches(a, idx_a, grad_a, 3):
+        pass
+    torch.cuda.synchronize()
+    late = _late_event(cycles)
+    b.submit(idx_b[0], ready=late)
+    b.flush()                          # the wait for `late` is on the streams both have
+    a.close()
+    assert not late.query()
+    b.forward()
+    b.backward(grad_b)
+    torch.cuda.synchronize()
+    b.close()
