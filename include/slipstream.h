@@ -505,9 +505,11 @@ int32_t ss_stream_wait_event(void *stream, void *event);
  * An ss_step is a stateful host object: it owns a fixed pool of events created at
  * ss_step_create, and, if the plan asks for them, issue threads (ss_issue_queue).
  * Its index streams (default priority) are common to all ss_steps alive on one
- * device, which are taken to be used in turn: index work of one that has to wait
- * (for a ready event, or for a batch to be trained on) holds up the index work
- * that others have submitted later.  No device memory is allocated: the caller hands over a ring of buffer sets and the pooled output.
+ * device with one training stream, which are taken to be used in turn: index work
+ * of one that has to wait (for a ready event, or for a batch to be trained on)
+ * holds up the index work that others have submitted later.  ss_steps with
+ * different training streams have index streams of their own.  No device memory
+ * is allocated: the caller hands over a ring of buffer sets and the pooled output.
  * Use from one host thread.  Per batch, in this order:
  *     ss_step_submit(idx)      as far ahead as ss_step_room() allows (up to two
  *                              thirds of the ring); idx must stay untouched until

@@ -37,6 +37,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "ss_common.h"
@@ -388,23 +389,28 @@ int auto_threads(int T, int B, int L, int n_side)
     return n_side >= 3 ? n_side : 1;
 }
 
-// Index streams, shared by all steps of a device.  The GPU runs a process's streams on a few
-// hardware queues (four by default); with more streams than that, streams that share a queue wait
-// for each other, a step's index work for its own training kernels, say.  A program that keeps
-// several steps (tables of several row lengths, say) trains them in turn, so one set of streams
-// serves all of them.  us per training step with a few steps alive and used in turn, streams of
-// their own and in common: one table of 200 M rows x 65536 lookups (three streams) 31 and 26, 26
-// tables x 8192 (one stream) 44.2 and 41.2, with all hot rows stale 37.1 and 34.7, 26 x 40000 (two)
-// 102.2 and 99.7; with a single step alive 26 for the first either way.  Work of two steps on one stream only gains an order it would not need: every wait on it is for an event
-// recorded before.  The first n streams of a device are handed out; the last step that gives them
-// back destroys them.
+// Index streams, shared by the steps that have one training stream.  The GPU runs a process's
+// streams on a few hardware queues (four by default); with more streams than that, streams that
+// share a queue wait for each other, a step's index work for its own training kernels, say.  A
+// program that keeps several steps (tables of several row lengths, say) and trains them in turn on
+// one stream gets one set of index streams for all of them.  us per training step with a few steps
+// alive and used in turn, streams of their own and in common: one table of 200 M rows x 65536
+// lookups (three streams) 31 and 26, 26 tables x 8192 (one stream) 44.2 and 41.2, with all hot rows
+// stale 37.1 and 34.7, 26 x 40000 (two) 102.2 and 99.7; with a single step alive 26 for the first
+// either way.
+// Work of two steps on one stream gains an order it would not need: behind one step's wait, for a
+// caller's event say, the other's index work waits too.  Every wait is for an event recorded before,
+// so this ends.  Steps with different training streams are meant to run side by side (in threads of
+// their own, say), and share nothing.
+// The first n streams of a set are handed out; the last step that gives them back destroys them.
 class IndexStreams {
 public:
-    static int32_t acquire(int device, int n, std::vector<hipStream_t> *out)
+    static int32_t acquire(int device, hipStream_t train, int n, std::vector<hipStream_t> *out)
     {
         std::lock_guard<std::mutex> lk(mutex());
+        const Key key(device, train);
         try {
-            Pool &p = pools()[device];
+            Pool &p = pools()[key];
             out->reserve(n);
             p.streams.reserve(n);
             while ((int)p.streams.size() < n) {
@@ -412,7 +418,7 @@ public:
                 // default priority; non-blocking, so that it never orders itself against the
                 // legacy default stream
                 if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
-                    if (p.users == 0) destroy(device);
+                    if (p.users == 0) destroy(key);
                     return SS_ERR_HIP;
                 }
                 p.streams.push_back(s);
@@ -424,22 +430,23 @@ public:
         }
         return SS_OK;
     }
-    static void release(int device)
+    static void release(int device, hipStream_t train)
     {
         std::lock_guard<std::mutex> lk(mutex());
-        const auto it = pools().find(device);
-        if (it != pools().end() && --it->second.users == 0) destroy(device);
+        const auto it = pools().find(Key(device, train));
+        if (it != pools().end() && --it->second.users == 0) destroy(it->first);
     }
 
 private:
+    typedef std::pair<int, hipStream_t> Key;
     struct Pool {
         std::vector<hipStream_t> streams;
         int users = 0;
     };
-    static void destroy(int device)
+    static void destroy(const Key key)
     {
-        for (hipStream_t s : pools()[device].streams) (void)hipStreamDestroy(s);
-        pools().erase(device);
+        for (hipStream_t s : pools()[key].streams) (void)hipStreamDestroy(s);
+        pools().erase(key);
     }
     // never destroyed: a step may be given back while the process ends
     static std::mutex &mutex()
@@ -447,9 +454,9 @@ private:
         static std::mutex *m = new std::mutex;
         return *m;
     }
-    static std::map<int, Pool> &pools()
+    static std::map<Key, Pool> &pools()
     {
-        static std::map<int, Pool> *p = new std::map<int, Pool>;
+        static std::map<Key, Pool> *p = new std::map<Key, Pool>;
         return *p;
     }
 };
@@ -468,7 +475,7 @@ struct GpuOps final : StepOps {
     float *pooled;
     hipStream_t main;
     std::vector<hipStream_t> sides;      // of IndexStreams
-    int device = -1;                     // ... which they belong to
+    int device = -1;                     // ... which they belong to, with `main`
     std::vector<void *> last_work;       // per index stream: event of this step's last work on it
     bool work_without_event = false;     // a call failed between launches
     std::vector<ss_issue_queue *> queues;
@@ -576,7 +583,7 @@ struct GpuOps final : StepOps {
         }
         for (void *e : events) (void)ss_event_destroy(e);
         events.clear();
-        if (!sides.empty()) IndexStreams::release(device);
+        if (!sides.empty()) IndexStreams::release(device, main);
         sides.clear();
         return rc;
     }
@@ -772,7 +779,7 @@ int32_t ss_step_create(const ss_tables *tables, int32_t B, int32_t L, int32_t al
         return fail(SS_ERR_HIP, "%s: hipGetDevice failed", who);
     ops->last_work.assign(plan->index_streams, nullptr);
     ops->last_job.assign(plan->issue_threads, 0);
-    if (IndexStreams::acquire(ops->device, plan->index_streams, &ops->sides) != SS_OK)
+    if (IndexStreams::acquire(ops->device, ops->main, plan->index_streams, &ops->sides) != SS_OK)
         return fail(SS_ERR_HIP, "%s: no index streams", who);
     for (int q = 0; q < plan->issue_threads; ++q) {
         ss_issue_queue *iq = nullptr;

@@ -152,8 +152,9 @@ class PipelinedStep:
     the weights: they run on index streams while earlier batches are still in their
     lookup and update kernels.  submit() hands over the indices of a coming batch,
     as far ahead as room() allows; forward() and backward() run on the stream that
-    was current when the object was built.  All objects alive have their index
-    streams in common.  Results are those of EmbeddingStep bit for bit.
+    was current when the object was built.  Objects built on one stream have their
+    index streams in common and are best used in turn; objects built on different
+    streams have their own.  Results are those of EmbeddingStep bit for bit.
     """
 
     class _Set:

@@ -1,6 +1,7 @@
-"""Steps that are alive together share their index streams: each has to leave what it leaves alone,
-bit for bit, whatever the others do, also from two threads and when another is closed early; closing
-one does not wait for another."""
+"""Steps that are alive together on one training stream share their index streams: each has to leave
+what it leaves alone, bit for bit, whatever the others do, also from two threads and when another is
+closed early; closing one does not wait for another, and steps on different training streams do not
+wait for each other's data."""
 import threading
 
 import pytest
@@ -135,3 +136,36 @@ def test_closing_a_step_does_not_wait_for_the_data_of_another():
     b.backward(grad_b)
     torch.cuda.synchronize()
     b.close()
+
+
+def test_steps_on_two_training_streams_do_not_wait_for_each_others_data():
+    # Streams may share one of the GPU's few hardware queues and wait for each other there, so one
+    # attempt of several, with streams on other queues each time, has to show it.
+    cycles = _sleep_cycles(0.2)
+    passed = []
+    for k in range(8):
+        main_a, main_b = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(main_a):
+            a, idx_a, grad_a = _make(SHAPES[0], 1)
+        with torch.cuda.stream(main_b):
+            b, idx_b, grad_b = _make(SHAPES[0], 2)
+        torch.cuda.synchronize()
+        late = _late_event(cycles)
+        a.submit(idx_a[0], ready=late)
+        a.flush()
+        with torch.cuda.stream(main_b):
+            for _ in _batches(b, idx_b, grad_b, 3):
+                pass
+            trained = torch.cuda.Event()
+            trained.record()
+        trained.synchronize()
+        passed.append(not late.query())
+        with torch.cuda.stream(main_a):
+            a.forward()
+            a.backward(grad_a)
+        torch.cuda.synchronize()
+        a.close()
+        b.close()
+        if passed[-1]:
+            break
+    assert passed[-1], passed
