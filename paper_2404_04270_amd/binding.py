@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from typing import List, Optional, Sequence
 
 import torch
@@ -519,11 +520,11 @@ def ss_sample_levels(hot: HotState, sidx: torch.Tensor, levels: torch.Tensor,
 def ss_level_counts(levels: torch.Tensor, thresholds: Sequence[float], counts: torch.Tensor,
                     stream=None) -> None:
     """counts int32 [len(thresholds)]: levels that each of up to 64 thresholds reaches."""
-    thr = (C.c_float * len(thresholds))(*thresholds)
+    thr = array("f", thresholds)           # (a third of the time of a ctypes array of 34)
     if counts.numel() < len(thresholds):
         raise SlipstreamError("ss_level_counts: counts is shorter than thresholds")
     _check(_lib.ss_level_counts(
-        _ptr(levels, torch.float32, "levels"), levels.numel(), thr, len(thresholds),
+        _ptr(levels, torch.float32, "levels"), levels.numel(), thr.buffer_info()[0], len(thr),
         _ptr(counts, torch.int32, "counts"), _stream_ptr(stream)))
 
 
@@ -533,10 +534,13 @@ def ss_drop_stats_many(counts, n_samples: int, population: int, n_hot_inputs: in
     ss_drop_stats in its order."""
     import numpy as np
     counts = np.ascontiguousarray(counts, dtype=np.uint32)
-    out = np.empty((counts.size, len(_STAT_KEYS)), dtype=np.float64)
-    _check(_lib.ss_drop_stats_many(counts.ctypes.data, counts.size, n_samples, population,
-                                   n_hot_inputs, t_crit, out.ctypes.data))
-    return out
+    n = counts.size
+    if n == 0:
+        return np.empty((0, len(_STAT_KEYS)))
+    out = (C.c_double * (n * len(_STAT_KEYS)))()
+    _check(_lib.ss_drop_stats_many(counts.__array_interface__["data"][0], n, n_samples, population,
+                                   n_hot_inputs, t_crit, out))
+    return np.frombuffer(out).reshape(n, len(_STAT_KEYS))
 
 
 class AccessCounters:

@@ -239,7 +239,8 @@ __device__ __forceinline__ float float_not_below(double x)
     }
     return f;
 }
-template <int I>
+// N searches of a lane side by side: as many as an input has lookups, four at most.
+template <int I, int N>
 __global__ __launch_bounds__(64 * kMaxWaves) void sample_level_kernel(
     const int32_t *const *__restrict__ hot_ids, int H,
     const double *const *__restrict__ drift, const int32_t *__restrict__ sidx, int S,
@@ -252,12 +253,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_level_kernel(
     const int64_t s0 = (int64_t)blockIdx.x * I;
     const int s = s0 + in < S ? (int)(s0 + in) : S - 1;
     double level = H > 0 ? 0.0 : __builtin_nan("");       // (a drift is never below 0)
-    for (uint32_t q0 = first_q; q0 < (uint32_t)TL && H > 0; q0 += step * kBatch) {
-        double d[kBatch];
-        bool found[kBatch];
+    for (uint32_t q0 = first_q; q0 < (uint32_t)TL && H > 0; q0 += step * N) {
+        double d[N];
+        bool found[N];
         lookup_drifts(hot_ids, H, drift, sidx, S, L, TL, s, q0, step, d, found);
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             const double x = found[i] ? d[i] : __builtin_nan("");
             level = level >= x || level != level ? level : x;
         }
@@ -273,22 +274,26 @@ __global__ __launch_bounds__(64 * kMaxWaves) void sample_level_kernel(
     }
 }
 
-// Threshold k = blockIdx.x: how many levels it reaches.  A workgroup reads all of its part's
-// levels, 32 at a time per thread, so that counts need neither clearing nor adding up (65536
-// levels: 6.7 us; 9.9 as doubles: what bounds it is the rate at which one compute unit reads).
+// Threshold k = blockIdx.x: how many of the `part` levels from blockIdx.y * part on it reaches.  What
+// bounds it is the rate at which one compute unit reads: up to 65536 levels a workgroup takes
+// all of them, 32 at a time per thread, and counts need neither clearing nor adding up (65536
+// levels: 6.7 us; 9.9 as doubles).  More are shared out to 512 workgroups, two per compute unit, but
+// no fewer than 16384 to each (a search over 190000 levels 85 us, 96 with 131072 to each; over
+// 400000 98 and 104, over a million 138 and 141; 159 with 16384).
 struct LevelLadder {
     float thr[SS_MAX_LEVEL_THRESHOLDS];
 };
 constexpr int kLevelThreads = 1024;
-constexpr int kLevelPart = 1 << 17;          // levels per workgroup
+constexpr int kLevelsAlone = 1 << 16, kLevelsLeast = 1 << 14, kLevelGroups = 512;
 __global__ __launch_bounds__(kLevelThreads) void level_count_kernel(
-    const float *__restrict__ levels, int S, LevelLadder ladder, uint32_t *__restrict__ counts)
+    const float *__restrict__ levels, int S, int part, LevelLadder ladder,
+    uint32_t *__restrict__ counts)
 {
     __shared__ uint32_t s_sum[kLevelThreads / 64];
     const int tid = threadIdx.x;
     const float thr = ladder.thr[blockIdx.x];
-    const int64_t p0 = (int64_t)blockIdx.y * kLevelPart;
-    const int64_t p1 = p0 + kLevelPart < S ? p0 + kLevelPart : S;
+    const int64_t p0 = (int64_t)blockIdx.y * part;
+    const int64_t p1 = p0 + part < S ? p0 + part : S;
     uint32_t n = 0;
     constexpr int U = 32;
     for (int64_t i0 = p0 + tid; i0 < p1; i0 += U * kLevelThreads) {
@@ -337,17 +342,20 @@ int32_t launch_sample_levels(int T, int32_t *const *hot_ids, int H, double *cons
                              const int32_t *sidx, int S, int L, float *levels, hipStream_t s)
 {
     if (S > 0) {
-        const int TL = T * L, I = inputs_per_group(S, TL), per_wave = kBatch * (64 / I);
+        const int TL = T * L, I = inputs_per_group(S, TL), N = TL < 3 ? TL : kBatch,
+                  per_wave = N * (64 / I);
         int waves = (TL + per_wave - 1) / per_wave;
         if (waves > kMaxWaves) waves = kMaxWaves;
         const unsigned grid = (unsigned)(((int64_t)S + I - 1) / I);
         ProfScope prof("sample_level_kernel", s);
-#define SS_LEVEL(I_)                                                                        \
-    launch(sample_level_kernel<I_>, dim3(grid), dim3(64 * waves), s,                         \
+#define SS_LEVEL(I_, N_)                                                                    \
+    launch(sample_level_kernel<I_, N_>, dim3(grid), dim3(64 * waves), s,                         \
            (const int32_t *const *)hot_ids, H, (const double *const *)drift, sidx, S, L, TL, levels)
-        if (I == 64) SS_LEVEL(64);
-        else if (I == 16) SS_LEVEL(16);
-        else SS_LEVEL(4);
+        if (TL == 1) SS_LEVEL(64, 1);
+        else if (TL == 2) SS_LEVEL(64, 2);
+        else if (I == 64) SS_LEVEL(64, kBatch);
+        else if (I == 16) SS_LEVEL(16, kBatch);
+        else SS_LEVEL(4, kBatch);
 #undef SS_LEVEL
     }
     return check_launch("ss_sample_levels");
@@ -359,11 +367,14 @@ int32_t launch_level_counts(const float *levels, int S, const float *thresholds,
     LevelLadder ladder = {};
     for (int k = 0; k < n_thr; ++k)
         ladder.thr[k] = thresholds[k] > 0.0f ? thresholds[k] : -1.0f;
-    const int64_t parts = S > 0 ? ((int64_t)S + kLevelPart - 1) / kLevelPart : 1;
+    const int64_t share = (int64_t)S * n_thr / kLevelGroups;
+    const int part = S <= kLevelsAlone ? kLevelsAlone
+                                       : (int)(share < kLevelsLeast ? kLevelsLeast : share);
+    const int64_t parts = S > 0 ? ((int64_t)S + part - 1) / part : 1;
     if (parts > 1) launch_zero_u32(counts, n_thr, s);
     ProfScope prof("level_count_kernel", s);
     launch(level_count_kernel, dim3(n_thr, (unsigned)parts), dim3(kLevelThreads), s, levels, S,
-           ladder, counts);
+           part, ladder, counts);
     return check_launch("ss_level_counts");
 }
 

@@ -26,9 +26,9 @@ def geometric_ladder(lo: float, hi: float, n: int) -> List[float]:
     """n thresholds strictly inside (lo, hi), evenly spaced in the logarithm."""
     if not (0.0 < lo < hi) or n < 1:
         raise ValueError("need 0 < lo < hi and n >= 1")
-    first = math.log(lo)
+    exp, first = math.exp, math.log(lo)
     step = (math.log(hi) - first) / (n + 1)
-    return [math.exp(first + step * (k + 1)) for k in range(n)]
+    return [exp(first + step * k) for k in range(1, n + 1)]
 
 
 def ladder_search(upper_bounds: Callable[[Sequence[float]], Sequence[float]],
@@ -83,7 +83,7 @@ class SamplingBlock:
         self.n_hot_inputs = self.population if n_hot_inputs is None else int(n_hot_inputs)
         self.t_crit = float(t_crit)
         self.n_samples = int(sidx.shape[1])
-        self.counts = torch.zeros(B.MAX_THRESHOLDS, dtype=torch.int32, device=sidx.device)
+        self.counts = torch.zeros(B.MAX_LEVEL_THRESHOLDS, dtype=torch.int32, device=sidx.device)
 
     def refresh_drift(self) -> None:
         """Drift of every hot row against the stored snapshot; changes nothing else."""
@@ -112,9 +112,8 @@ class SamplingBlock:
                                  lo, hi, budget, passes, width)
         # every lookup has to be stale: the inputs' rows are mapped to drifts once, for all ladders
         import torch
-        B, dev = self._B, self.sidx.device
-        levels = torch.empty(self.sidx.shape[1], dtype=torch.float32, device=dev)
-        counts = torch.empty(B.MAX_LEVEL_THRESHOLDS, dtype=torch.int32, device=dev)
+        B, counts = self._B, self.counts
+        levels = self.sidx.new_empty(self.sidx.shape[1], dtype=torch.float32)
         B.ss_sample_levels(self.hot, self.sidx, levels)
         priced = {}
 

@@ -27,7 +27,8 @@ def _hot(T, R, H, gen, odd):
     (1, 50, 1, 1, 1, 0.0), (1, 50, 3, 300, 1, 0.1), (2, 60, 4, 1000, 2, 0.0), (3, 70, 5, 64, 3, 0.02),
     (26, 4000, 500, 4097, 1, 0.001), (26, 4000, 300, 65, 5, 0.0), (8, 900, 100, 5000, 16, 0.001),
     (4, 900, 100, 300, 300, 0.0), (1, 400, 40, 131072, 1, 0.2), (1, 400, 40, 131073, 1, 0.2),
-    (2, 400, 40, 300000, 2, 0.1),
+    (2, 400, 40, 300000, 2, 0.1), (1, 400, 40, 65536, 2, 0.2), (2, 400, 40, 65537, 1, 0.2),
+    (1, 400, 40, 3, 2, 0.0),
 ])
 @pytest.mark.parametrize("odd", [False, True])
 def test_levels_count_what_sample_drop_counts(T, R, H, S, L, cold, odd):
