@@ -509,8 +509,9 @@ def ss_sample_levels(hot: HotState, sidx: torch.Tensor, levels: torch.Tensor,
         raise SlipstreamError("ss_sample_levels: HotState was built without diagnostics")
     if sidx.dim() != 3 or sidx.shape[0] != len(hot.hot_ids):
         raise SlipstreamError("ss_sample_levels: sidx must be [T, S, L]")
-    if levels.numel() < sidx.shape[1]:
-        raise SlipstreamError("ss_sample_levels: levels is shorter than the sample")
+    if levels.numel() != sidx.shape[1]:
+        # (ss_level_counts counts all the levels it is given)
+        raise SlipstreamError("ss_sample_levels: levels needs one entry per sampled input")
     _check(_lib.ss_sample_levels(
         len(hot.hot_ids), hot._hptr.data_ptr(), hot.H, hot._dptr.data_ptr(),
         _ptr(sidx, torch.int32, "sidx"), sidx.shape[1], sidx.shape[2],

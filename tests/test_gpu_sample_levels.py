@@ -57,6 +57,23 @@ def test_levels_count_what_sample_drop_counts(T, R, H, S, L, cold, odd):
     assert torch.equal(got, want)
 
 
+def test_levels_of_another_length_are_refused():
+    # ss_level_counts counts all of its levels: a tail that no sample filled would be counted too
+    from paper_2404_04270_amd import binding as B
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    _, hot, ids = _hot(2, 100, 10, gen, False)
+    sidx = torch.stack([i[torch.randint(0, 10, (50, 1), device="cuda", generator=gen)] for i in ids])
+    for n in (49, 51, 64):
+        levels = torch.zeros(n, device="cuda")
+        with pytest.raises(B.SlipstreamError):
+            B.ss_sample_levels(hot, sidx, levels)
+        assert not bool(levels.any())
+    buffer = torch.zeros(64, device="cuda")
+    B.ss_sample_levels(hot, sidx, buffer[:50])
+    assert bool((buffer[:50] > 0).all()) and not bool(buffer[50:].any())
+
+
 def test_no_hot_rows():
     from paper_2404_04270_amd import binding as B
     empty = torch.zeros(1, 1, dtype=torch.int64, device="cuda")
