@@ -393,7 +393,7 @@ int32_t ss_filter_batch(const ss_tables *tables, const int32_t *idx, int32_t B,
                                       B, L, nullptr, static_cast<hipStream_t>(stream)))
         return bad;
     return launch_filter(tables, idx, B, L, alpha, skip_mask, kept_ids, n_kept,
-                         idx_c, ws, static_cast<hipStream_t>(stream));
+                         idx_c, ws, false, static_cast<hipStream_t>(stream));
 }
 
 int32_t ss_filter_batch_split(const ss_tables *tables, uint32_t *const *hot_bits,

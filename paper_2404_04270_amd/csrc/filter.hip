@@ -9,7 +9,8 @@
 // grows with every stale lookup: 21 us at 26 tables once the hot rows are
 // frozen.)  A wavefront ballot plus popcount yields the number of kept samples
 // per workgroup.
-// Small batches take one launch that does both for itself per table (filter_small_kernel).
+// Small batches take one launch whose workgroups, one per table, do both for themselves
+// (filter_small_kernel).
 // Kernel 2 runs one workgroup per (tile of 256 samples, table, or four tables where bags hold
 // one lookup and the batch is large).  It turns the
 // per-tile counts into an offset (summing the counts before it: at most a few
@@ -318,16 +319,26 @@ __global__ __launch_bounds__(kSmallThreads) void filter_small_kernel(
 }
 
 // Lanes per sample of the one-launch filter, 0 where the batch is not for it.  Every table's
-// workgroup probes the bitmaps for the whole batch, so what that may cost at worst, with all hot
-// rows stale, is bounded: 16384 lookups in all, and no lane more than two rounds behind its
-// first, one where bags are long (their index words lie apart).  us of kernels (event pairs,
-// less the 2 us that a pair adds) in two launches and in one, no row stale and all hot rows
-// stale: 8 tables x 128 lookups 5.3 and 4.1, 4.9 and 4.2; 5 x 777 bags of 3 5.9 and 4.0, 6.2 and
-// 8.8; 16 x 1024 5.6 and 4.2, 6.4 and 8.4; a training step call by call 22.3 and 20.2 at 8 x
-// 128, 24.3 and 22.7 at 5 x 777 x 3.
-static int small_lanes(int64_t B, int L, int64_t total)
+// workgroup probes the bitmaps for the whole batch, and what bounds it once rows are stale is the rate
+// at which one compute unit gathers bitmap words: the lookups of the batch are bounded by `most`, and
+// no lane is more than two rounds behind its first, one where bags are long (their index words lie
+// apart).  us of kernels (event pairs, less the 2 us that a pair adds) in two launches and in one, no
+// row stale and all hot rows stale: 8 tables x 128 lookups 5.3 and 4.1, 4.9 and 4.2; 5 x 777 bags of 3
+// 5.9 and 4.0, 6.2 and 8.8; 16 x 1024 5.6 and 4.2, 6.4 and 8.4.
+//   In line, where the launch that is spared counts for more than that: 16384.  us per training step,
+//   no row stale and all hot rows stale: 8 x 128 26.1 and 22.9, 25.5 and 22.6; 16 x 1024 28.3 and
+//   25.2, 28.5 and 25.5; 5 x 777 x 3 28.1 and 25.4, 28.3 and 25.5; 1000 tables x 16 26.1 and 22.4,
+//   25.7 and 22.6.
+//   Index work beside training kernels, where the length of its chain is what counts: 8192.  The
+//   same through the scheduler: 8 x 128 15.8 and 13.8, 15.9 and 13.8; 16 x 512 17.0 and 14.0, 16.7
+//   and 15.4; 2 x 1024 x 4 19.0 and 17.5, 19.1 and 18.5; 5 x 546 x 3 18.7 and 17.8, 18.6 and 18.5;
+//   1000 x 8 18.6 and 17.5, 18.6 and 17.4; but 5 x 777 x 3 18.8 and 18.2, 19.2 and 20.0; 16 x 1024
+//   17.8 and 17.0, 17.6 and 19.0; 3 x 1024 x 5 19.6 and 18.4, 19.7 and 20.9; 1000 x 16 19.1 and 21.0,
+//   18.8 and 21.0.
+constexpr int64_t kSmallInLine = 16384, kSmallBeside = 8192;
+static int small_lanes(int64_t B, int L, int64_t total, int64_t most)
 {
-    if (B > kSmallThreads || B * total > 16384) return 0;
+    if (B > kSmallThreads || B * total > most) return 0;
     int lanes = 64;
     while (lanes > 1 && B * lanes > kSmallThreads) lanes >>= 1;
     return lanes * (1 + (L < 8 ? 2 : 1) * kFlagProbes) >= total ? lanes : 0;
@@ -350,39 +361,11 @@ size_t filter_ws_bytes(int T, int B, int L)
     return align_up(blocks * sizeof(int32_t), 256);
 }
 
-int32_t launch_filter(const ss_tables *tb, const int32_t *idx, int B, int L,
-                      int alpha, uint8_t *skip_mask, int32_t *kept_ids,
-                      int32_t *n_kept, int32_t *idx_c, void *ws, hipStream_t s)
-{
-    return launch_filter_split(tb, nullptr, idx, B, L, alpha, skip_mask, nullptr, kept_ids,
-                               n_kept, idx_c, ws, s);
-}
-
 int32_t launch_filter_split(const ss_tables *tb, uint32_t *const *hot_bits, const int32_t *idx,
                             int B, int L, int alpha, uint8_t *skip_mask, uint8_t *hot_mask,
                             int32_t *kept_ids, int32_t *n_kept, int32_t *idx_c, void *ws,
                             hipStream_t s)
 {
-    const int small = hot_mask ? 0 : small_lanes(B, L, (int64_t)tb->num_tables * L);
-    if (small) {
-        ProfScope prof("filter_small_kernel", s);
-        const int threads = ((B * small + 63) / 64) * 64;
-#define SS_SMALL(LANES_)                                                              \
-    launch(SS_BOTH(filter_small_kernel, LANES_), dim3(tb->num_tables),                 \
-           dim3(threads < 256 ? 256 : threads), s, tb->stale_bits, idx, tb->num_tables, B, L, \
-           alpha, skip_mask, kept_ids, n_kept, idx_c)
-        switch (small) {
-        case 1: SS_SMALL(1); break;
-        case 2: SS_SMALL(2); break;
-        case 4: SS_SMALL(4); break;
-        case 8: SS_SMALL(8); break;
-        case 16: SS_SMALL(16); break;
-        case 32: SS_SMALL(32); break;
-        default: SS_SMALL(64); break;
-        }
-#undef SS_SMALL
-        return check_launch("ss_filter_batch");
-    }
     const int lanes = flag_lanes((int64_t)tb->num_tables * L);
     const int samples = flag_wg(lanes) / lanes;      // per workgroup of the flag kernel
     const int flag_blocks = (B + samples - 1) / samples;
@@ -428,6 +411,35 @@ int32_t launch_filter_split(const ss_tables *tb, uint32_t *const *hot_bits, cons
            dim3(tiles, tb->num_tables, parts), dim3(kWG), s, idx, B, L, skip_mask, block_kept,
            kWG / samples, kept_ids, n_kept, idx_c);
     return check_launch("ss_filter_batch");
+}
+
+int32_t launch_filter(const ss_tables *tb, const int32_t *idx, int B, int L, int alpha,
+                      uint8_t *skip_mask, int32_t *kept_ids, int32_t *n_kept, int32_t *idx_c,
+                      void *ws, bool beside, hipStream_t s)
+{
+    const int small = small_lanes(B, L, (int64_t)tb->num_tables * L,
+                                  beside ? kSmallBeside : kSmallInLine);
+    if (small) {
+        ProfScope prof("filter_small_kernel", s);
+        const int threads = ((B * small + 63) / 64) * 64;
+#define SS_SMALL(LANES_)                                                              \
+    launch(SS_BOTH(filter_small_kernel, LANES_), dim3(tb->num_tables),                 \
+           dim3(threads < 256 ? 256 : threads), s, tb->stale_bits, idx, tb->num_tables, B, L, \
+           alpha, skip_mask, kept_ids, n_kept, idx_c)
+        switch (small) {
+        case 1: SS_SMALL(1); break;
+        case 2: SS_SMALL(2); break;
+        case 4: SS_SMALL(4); break;
+        case 8: SS_SMALL(8); break;
+        case 16: SS_SMALL(16); break;
+        case 32: SS_SMALL(32); break;
+        default: SS_SMALL(64); break;
+        }
+#undef SS_SMALL
+        return check_launch("ss_filter_batch");
+    }
+    return launch_filter_split(tb, nullptr, idx, B, L, alpha, skip_mask, nullptr, kept_ids, n_kept,
+                               idx_c, ws, s);
 }
 
 }  // namespace ss

@@ -84,7 +84,7 @@ void run_job(ss_issue_queue *q, const Job &j)
                              j.stream);
         if (rc != SS_OK) break;
         rc = launch_filter(&j.tables, j.idx, j.B, j.L, j.alpha, j.skip_mask, j.kept_ids,
-                           j.n_kept, j.idx_c, j.ws_filter, j.stream);
+                           j.n_kept, j.idx_c, j.ws_filter, true, j.stream);
         if (rc == SS_OK)
             rc = launch_backward_prepare(&j.tables, j.idx_c, j.B, j.L, j.n_kept,
                                          j.ws_backward, j.stream, j.event);

@@ -256,9 +256,10 @@ __device__ __forceinline__ bool bit_set(gptr<const uint32_t> bits, uint32_t r)
 // Entry points of the kernel families (each in its own .hip file).
 int32_t launch_forward(const ss_tables *tb, const int32_t *idx, int Bcap, int L,
                        const int32_t *n_valid, float *out, hipStream_t s);
-int32_t launch_filter(const ss_tables *tb, const int32_t *idx, int B, int L,
-                      int alpha, uint8_t *skip_mask, int32_t *kept_ids,
-                      int32_t *n_kept, int32_t *idx_c, void *ws, hipStream_t s);
+// beside: as index work next to training kernels (the same results by other launches)
+int32_t launch_filter(const ss_tables *tb, const int32_t *idx, int B, int L, int alpha,
+                      uint8_t *skip_mask, int32_t *kept_ids, int32_t *n_kept, int32_t *idx_c,
+                      void *ws, bool beside, hipStream_t s);
 // The same with a second set of bitmaps (hot rows): hot_mask[b] = every lookup of
 // sample b is a hot row.  hot_mask == nullptr: the plain filter.
 int32_t launch_filter_split(const ss_tables *tb, uint32_t *const *hot_bits, const int32_t *idx,

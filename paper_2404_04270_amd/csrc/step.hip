@@ -489,7 +489,7 @@ struct GpuOps final : StepOps {
     {
         const ss_step_set &b = sets[set];
         int32_t rc = launch_filter(&tables, idx, B, L, alpha, b.skip_mask, b.kept_ids, b.n_kept,
-                                   b.idx_c, b.ws_filter, stream(s));
+                                   b.idx_c, b.ws_filter, true, stream(s));
         if (!rc)
             rc = launch_backward_prepare(&tables, b.idx_c, B, L, b.n_kept, b.ws_backward, stream(s),
                                          static_cast<hipEvent_t>(done));

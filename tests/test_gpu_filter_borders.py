@@ -42,3 +42,38 @@ def test_filter_borders(T, B, L, share):
         assert torch.equal(ids[:kept.numel()].long(), kept), alpha
         assert torch.equal(out[:, :kept.numel()], idx[:, kept]), alpha
         assert bool((ids[kept.numel():] == -1).all()) and bool((out[:, kept.numel():] == -1).all())
+
+
+@pytest.mark.parametrize("T,B,L", [(8, 1024, 1), (9, 911, 1), (16, 1024, 1), (5, 777, 3), (513, 16, 1)])
+def test_scheduler_and_calls_take_other_launches_and_leave_the_same(T, B, L):
+    from paper_2404_04270_amd.step import EmbeddingStep, PipelinedStep
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T * 7 + B)
+    R, D, N = 400, 8, 6
+    start = torch.rand(T, R, D, device="cuda", generator=gen)
+    hot = [torch.arange(0, R, 3, dtype=torch.int32, device="cuda")] * T
+    idx = [torch.randint(0, R, (T, B, L), device="cuda", generator=gen, dtype=torch.int32)
+           for _ in range(N)]
+    grad = torch.randn(T, B, D, device="cuda", generator=gen)
+    left = []
+    for kind in (EmbeddingStep, PipelinedStep):
+        step = kind(list(start.clone().unbind(0)), hot, B, L, 0.01, 0.05, 100,
+                    alpha=T * L // 3)
+        for b in step.bits:                  # a third of the rows stale
+            b.fill_(0x49249249)
+        torch.cuda.synchronize()
+        masks = []
+        for k in range(N):
+            if kind is EmbeddingStep:
+                step.filter_forward(idx[k])
+            else:
+                step.submit(idx[k])
+                step.forward()
+            masks.append(step.skip_mask.clone())
+            step.backward(grad)
+        torch.cuda.synchronize()
+        left.append(masks + [w.clone() for w in step.tables.weights])
+        if kind is PipelinedStep:
+            step.close()
+    assert any(bool(m.any()) and not bool(m.all()) for m in left[0][:N])
+    assert all(torch.equal(a, b) for a, b in zip(*left))
