@@ -169,12 +169,10 @@ static_assert(kMix * kUnmix == 1u, "the product is undone");
 // load(i) gives entry i of the list (called before the
 // second barrier only, so s_bucket, m entries and kBucketPad more, may be where the list lies),
 // keep(entry) whether it is wanted at all; emit(i, entry) is called once for every place i below
-// the number of wanted entries, which is returned.  m <= NT * R.  TIES: entries may be equal (a
-// sample that looks a row up more than once).
+// the number of wanted entries, which is returned.  All entries are different.  kFew < m <= NT * R.
 // ---------------------------------------------------------------------------
 constexpr int kMaxHeavy = 16;          // heavy rows looked for
 constexpr uint32_t kMinVotes = 3;      // of 64
-constexpr uint32_t kVoteFrom = 256;    // shorter lists: no row is worth it
 constexpr uint32_t kVoteMix = 0x85EBCA6Bu;   // odd; its multiples spread over the 32-bit numbers
 constexpr int kBucketPad = 8;
 
@@ -211,7 +209,7 @@ __device__ __forceinline__ uint32_t set_below(uint64_t ballot)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
 }
 
-template <int NT, int R, bool TIES, int NB, typename E, typename Load, typename Keep, typename Emit>
+template <int NT, int R, int NB, typename E, typename Load, typename Keep, typename Emit>
 __device__ __forceinline__ uint32_t group_entries(uint32_t m, int VB, int row_bits, E *s_bucket,
                                                   GroupScratch<NT, NB> &s, Load load, Keep keep,
                                                   Emit emit)
@@ -231,31 +229,28 @@ __device__ __forceinline__ uint32_t group_entries(uint32_t m, int VB, int row_bi
     for (int r = 0; r < R; ++r) in[r] = first + r * 64 < m && keep(ent[r]);
     for (int i = tid; i < N; i += NT) s.cnt[i] = 0;
     if (wave == 0) {
-        uint32_t n = 0;
-        if (m >= kVoteFrom) {
-            // By a hash where in its 64th: at even distances the votes meet only some of the rows of a
-            // list that repeats itself, and the lookups of a row that is not found are compared each
-            // with each (64 tables x 8192 bags of the same two ids: 1245 us, 25 so).
-            const uint32_t from = (uint32_t)(((uint64_t)lane * m) >> 6), width = m >> 6;
-            const uint32_t place = from + __umulhi((uint32_t)(lane + 1) * kVoteMix, width);
-            const uint32_t mine = (uint32_t)(load(place) >> VB);
-            // lanes that agree in ten bits of a hash stand for lanes that agree: a row that
-            // is taken for heavy without being it costs a ballot per round, nothing else
-            const uint32_t h = (mine * 0x9E3779B1u) >> 22;
-            uint64_t same = ~0ull;
+        // By a hash where in its 64th: at even distances the votes meet only some of the rows of a
+        // list that repeats itself, and the lookups of a row that is not found are compared each
+        // with each (64 tables x 8192 bags of the same two ids: 1245 us, 25 so).
+        const uint32_t from = (uint32_t)(((uint64_t)lane * m) >> 6), width = m >> 6;
+        const uint32_t place = from + __umulhi((uint32_t)(lane + 1) * kVoteMix, width);
+        const uint32_t mine = (uint32_t)(load(place) >> VB);
+        // lanes that agree in ten bits of a hash stand for lanes that agree: a row that
+        // is taken for heavy without being it costs a ballot per round, nothing else
+        const uint32_t h = (mine * 0x9E3779B1u) >> 22;
+        uint64_t same = ~0ull;
 #pragma unroll
-            for (int b = 0; b < 10; ++b) {
-                const bool one = (h >> b) & 1u;
-                const uint64_t bal = __ballot(one);
-                same &= one ? bal : ~bal;
-            }
-            const bool heavy = set_below(same) == 0 && __popcll(same) >= (int)kMinVotes;
-            const uint64_t found = __ballot(heavy);
-            const uint32_t at = set_below(found);
-            if (heavy && at < kMaxHeavy) s.heavy[at] = mine;
-            n = __popcll(found);
-            n = n < kMaxHeavy ? n : kMaxHeavy;
+        for (int b = 0; b < 10; ++b) {
+            const bool one = (h >> b) & 1u;
+            const uint64_t bal = __ballot(one);
+            same &= one ? bal : ~bal;
         }
+        const bool heavy = set_below(same) == 0 && __popcll(same) >= (int)kMinVotes;
+        const uint64_t found = __ballot(heavy);
+        const uint32_t at = set_below(found);
+        if (heavy && at < kMaxHeavy) s.heavy[at] = mine;
+        uint32_t n = __popcll(found);
+        n = n < kMaxHeavy ? n : kMaxHeavy;
         if (lane == 0) s.n_heavy = n;
     }
     __syncthreads();
@@ -339,7 +334,7 @@ __device__ __forceinline__ uint32_t group_entries(uint32_t m, int VB, int row_bi
             for (uint32_t u = 0; u < U; ++u)
 #pragma unroll
                 for (uint32_t q = 0; q < PC; ++q)
-                    place += TIES ? v[u][q] < e + ((p + u) * PC + q < i ? 1u : 0u) : v[u][q] < e;
+                    place += v[u][q] < e;
         }
         emit(place, e);
     }
@@ -351,7 +346,7 @@ __device__ __forceinline__ uint32_t group_entries(uint32_t m, int VB, int row_bi
 // One barrier, and a chain a quarter as long as that of the buckets (8 tables x 128 lookups: 8.2 us
 // with the radix sort, 5.3 with the buckets, 4 so).
 constexpr uint32_t kFew = 256;
-template <int NT, bool TIES, int NB, typename E, typename Keep, typename Emit>
+template <int NT, int NB, typename E, typename Keep, typename Emit>
 __device__ __forceinline__ uint32_t group_few(uint32_t m, E *s_list, GroupScratch<NT, NB> &s,
                                               Keep keep, Emit emit)
 {
@@ -386,8 +381,7 @@ __device__ __forceinline__ uint32_t group_few(uint32_t m, E *s_list, GroupScratc
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u)
 #pragma unroll
-            for (uint32_t q = 0; q < PC; ++q)
-                place += TIES ? v[u][q] < e + ((p0 + u * PARTS) * PC + q < i ? 1u : 0u) : v[u][q] < e;
+            for (uint32_t q = 0; q < PC; ++q) place += v[u][q] < e;
     }
 #pragma unroll
     for (uint32_t off = 1; off < PARTS; off <<= 1) place += __shfl_xor(place, off);
@@ -486,9 +480,9 @@ __device__ __forceinline__ void class_sort_body(
         oe[n_below + i] = make_uint2(row_of(e), L == 1 ? pos : pos / (uint32_t)L);
     };
 #define SS_GROUP(R_) \
-    real = group_entries<NT, R_, false, NB>(m, VB, rem_bits, s_list, s_group, load, keep, emit)
+    real = group_entries<NT, R_, NB>(m, VB, rem_bits, s_list, s_group, load, keep, emit)
     uint32_t real = 0;
-    if (m <= kFew) real = group_few<NT, false, NB>(m, s_list, s_group, keep, emit);
+    if (m <= kFew) real = group_few<NT, NB>(m, s_list, s_group, keep, emit);
     else if (ITEMS == 1 || m <= NT) SS_GROUP(1);
     else if (ITEMS <= 2 || m <= 2 * NT) SS_GROUP(2);
     else if (ITEMS > 2 && m <= 3 * NT) SS_GROUP(3);
