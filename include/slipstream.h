@@ -198,9 +198,10 @@ int32_t ss_embbag_backward_apply(const ss_tables *tables, int32_t Bcap, int32_t 
  * one call: out receives the pooled vectors, bwd_ws is left ready for
  * ss_embbag_backward_apply.  Both halves read the same indices, and the grouping
  * is bound by latency while the gather is bound by HBM, so for one-hot batches
- * of at most 16384 lookups per table (and row ids + sample numbers that fit 31
- * bits together) a single launch runs the grouping in the shadow of the gather;
- * other shapes get the two launches back to back.  Results are identical to the
+ * of at most 16384 lookups per table (and 2 M rows, 16 M where tables or lookups
+ * are few: row bits and lookup numbers have to fit a word) a single launch runs
+ * the grouping in the shadow of the gather; other shapes get the two launches back
+ * to back.  Results are identical to the
  * separate calls.
  */
 int32_t ss_embbag_forward_grouped(const ss_tables *tables, const int32_t *idx,

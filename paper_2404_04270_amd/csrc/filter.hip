@@ -21,28 +21,17 @@
 
 namespace ss {
 
-// LANES lanes per sample, flag_wg(LANES) / LANES samples per workgroup.  A chunk
+// Verdicts on sample b (below B) by a group of LANES lanes, of which this is lane c.  A chunk
 // of lookups costs two round trips to memory (indices, then bitmap words) however many of
 // them are stale.  The first chunk is one lookup per lane: while few rows are
-// stale that settles almost every sample, and the kernel reads no more than
-// that.  Later chunks take eight per lane.  The host picks LANES so that two
-// chunks cover all T * L lookups of a sample where it can: the kernel lasts as
-// long as its unluckiest sample, and with most hot rows frozen there is always
-// a sample that needs nearly all of them (160 lookups per sample: 16 us with
-// four lanes and six chunks, 7 us with 32 lanes and two).
-constexpr int kFlagProbes = 8;                   // lookups per lane and chunk
-// Threads per workgroup: 256 (1024 with 64 lanes per sample).  Beside the training
-// kernels a 1024-thread workgroup waits for a compute unit with sixteen free
-// wavefront slots: at 32 lanes per sample the kernel then took 13-15 us instead of
-// the 4 us it takes alone.
-constexpr int flag_wg(int lanes) { return lanes <= 32 ? 256 : 1024; }
-
+// stale that settles almost every sample, and no more than that is read.  Later
+// chunks take eight per lane.
 // SPLIT: the same pass also classifies the sample against a second set of bitmaps
 // (the hot rows, section 3.1: an input that reads only hot entries is a hot input,
 // I = I_hot + I_cold): hot_mask[b] = 1 iff every lookup of the sample hits a row
 // whose hot bit is set.  The indices of a chunk are loaded once for both tests;
 // each test stops probing as soon as its verdict is fixed.
-// Verdicts on sample b (below B) by a group of LANES lanes, of which this is lane c.
+constexpr int kFlagProbes = 8;                   // lookups per lane and chunk
 template <int LANES, bool SPLIT>
 __device__ __forceinline__ void classify(const uint32_t *const *__restrict__ bits,
                                          const uint32_t *const *__restrict__ hot_bits,
@@ -117,6 +106,17 @@ __device__ __forceinline__ void classify(const uint32_t *const *__restrict__ bit
     }
     if (alpha > 0 && alpha <= total && bits != nullptr) skip = count >= alpha;
 }
+
+// LANES lanes per sample, flag_wg(LANES) / LANES samples per workgroup.  The host picks LANES so
+// that two chunks cover all T * L lookups of a sample where it can: the kernel lasts as
+// long as its unluckiest sample, and with most hot rows frozen there is always
+// a sample that needs nearly all of them (160 lookups per sample: 16 us with
+// four lanes and six chunks, 7 us with 32 lanes and two).
+// Threads per workgroup: 256 (1024 with 64 lanes per sample).  Beside the training
+// kernels a 1024-thread workgroup waits for a compute unit with sixteen free
+// wavefront slots: at 32 lanes per sample the kernel then took 13-15 us instead of
+// the 4 us it takes alone.
+constexpr int flag_wg(int lanes) { return lanes <= 32 ? 256 : 1024; }
 
 template <int LANES, bool SPLIT, typename TS>
 __global__ __launch_bounds__(flag_wg(LANES)) void filter_flag_kernel(

@@ -6,9 +6,9 @@
 // hundred workgroups while the gather is bound by HBM.  Launched one after the
 // other they cost their sum; as two roles of one grid the grouping workgroups
 // (lowest block ids, dispatched first) run in the shadow of the gather.  The
-// grouping role sorts 31-bit words (row bits above the class bits + sample
-// number), which keeps its LDS small enough for two 1024-thread workgroups per
-// CU, so the gather role keeps its occupancy.
+// grouping role works on 32-bit words (row bits below the class + position of
+// the lookup), which keeps its LDS small enough for two 1024-thread workgroups
+// per CU, so the gather role keeps its occupancy.
 #include "forward_body.h"
 #include "group_body.h"
 #include "ss_common.h"

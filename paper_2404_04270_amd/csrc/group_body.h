@@ -2,7 +2,8 @@
 // (stage 1 of the backward pass), as a device function so that it can run as a
 // kernel of its own or as one role of the fused forward + grouping launch; and the
 // pieces it shares with the grouping of larger tables: ranking inside a wavefront,
-// the sentinel for stale rows, grouping inside one workgroup.
+// the sentinel for stale rows.  (An LSD radix sort in LDS, which only the larger
+// tables take, is here too.)
 #pragma once
 #include "ss_common.h"
 
@@ -148,8 +149,8 @@ static_assert(kMix * kUnmix == 1u, "the product is undone");
 // ---------------------------------------------------------------------------
 // Grouping of one workgroup's list: equal rows become neighbours, in sample order inside a
 // row.  Nothing else is asked of the order, which is what spares a digit pass per six row
-// bits: an entry is a word of its own, (row bits << VB) | sample, so its place among the
-// entries of its bucket is the number of smaller ones, whatever order they arrived in.
+// bits: an entry is a word of its own, (row bits << VB) | position of the lookup, so its place
+// among the entries of its bucket is the number of smaller ones, whatever order they arrived in.
 //
 //   1. 64 entries vote for heavy rows (three or more votes), one from each 64th of the list.
 //   2. A heavy row's entries are counted per wavefront with a ballot per row, in list order;
@@ -166,10 +167,10 @@ static_assert(kMix * kUnmix == 1u, "the product is undone");
 // with this: 15.1 and 9.0 us for 26 tables x 8192 lookups of a million rows, popular rows next to
 // each other, 20 and 11 scattered; 42 and 14, 46 and 17 for 26 x 16384; 11 and 7 for 26 x 2048.
 //
-// load(i) gives entry i of the list (called before the
-// second barrier only, so s_bucket, m entries and kBucketPad more, may be where the list lies),
-// keep(entry) whether it is wanted at all; emit(i, entry) is called once for every place i below
-// the number of wanted entries, which is returned.  All entries are different.  kFew < m <= NT * R.
+// load(i) gives entry i of the list (called before the second barrier only, so s_bucket, m entries
+// and kBucketPad more, may be where the list lies), keep(entry) whether it is wanted at all;
+// emit(i, entry) is called once for every place i below the number of wanted entries, which is
+// returned.  All entries are different.  kFew < m <= NT * R.
 // ---------------------------------------------------------------------------
 constexpr int kMaxHeavy = 16;          // heavy rows looked for
 constexpr uint32_t kMinVotes = 3;      // of 64
