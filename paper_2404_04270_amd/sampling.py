@@ -83,7 +83,7 @@ class SamplingBlock:
         self.n_hot_inputs = self.population if n_hot_inputs is None else int(n_hot_inputs)
         self.t_crit = float(t_crit)
         self.n_samples = int(sidx.shape[1])
-        self.counts = torch.zeros(B.MAX_LEVEL_THRESHOLDS, dtype=torch.int32, device=sidx.device)
+        self.counts = torch.zeros(B.MAX_THRESHOLDS, dtype=torch.int32, device=sidx.device)
 
     def refresh_drift(self) -> None:
         """Drift of every hot row against the stored snapshot; changes nothing else."""
@@ -112,8 +112,9 @@ class SamplingBlock:
                                  lo, hi, budget, passes, width)
         # every lookup has to be stale: the inputs' rows are mapped to drifts once, for all ladders
         import torch
-        B, counts = self._B, self.counts
+        B = self._B
         levels = self.sidx.new_empty(self.sidx.shape[1], dtype=torch.float32)
+        counts = self.sidx.new_empty(B.MAX_LEVEL_THRESHOLDS)
         B.ss_sample_levels(self.hot, self.sidx, levels)
         priced = {}
 

@@ -99,3 +99,33 @@ def test_search_is_the_same(budget, passes):
     want = ladder_search(lambda ts: [e["hi"] for e in block.estimate(ts)], 1e-6, 1e-1, budget,
                          passes, B.MAX_THRESHOLDS)
     assert got == want
+
+
+def test_searches_of_one_block_from_two_threads():
+    import threading
+    from paper_2404_04270_amd.sampling import SamplingBlock
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    tables, hot, ids = _hot(4, 3000, 200, gen, False)
+    sidx = torch.stack([i[torch.randint(0, 200, (3000, 1), device="cuda", generator=gen)]
+                        for i in ids])
+    block = SamplingBlock(tables, hot, sidx, alpha=4, population=100000)
+    ranges = [(0.2, 1e-6, 1e-1), (0.5, 1e-5, 1e-2)]
+    want = [block.find_threshold(*r) for r in ranges]
+    torch.cuda.synchronize()
+    wrong, errors = [0, 0], []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(40):
+                    wrong[k] += block.find_threshold(*ranges[k]) != want[k]
+        except Exception as e:         # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors and wrong == [0, 0], (errors, wrong)
