@@ -498,10 +498,11 @@ int32_t ss_stream_wait_event(void *stream, void *event);
  * ends with the capture of the first snapshot), scheduled so that the index work
  * of the coming batches (ss_filter_batch, ss_embbag_backward_prepare: they read
  * indices and stale bitmaps only) runs on index streams while the current batch
- * is in its lookup and update kernels on the caller's training stream.  Results are those of the calls issued one after the other on one
- * stream, bit for bit: the only reordering is that index work of later batches
- * runs before the update of earlier ones, which it does not read; batches after
- * one that ends with a detect pass are held back until that pass is enqueued.
+ * is in its lookup and update kernels on the caller's training stream.  Results
+ * are those of the calls issued one after the other on one stream, bit for bit:
+ * the only reordering is that index work of later batches runs before the update
+ * of earlier ones, which it does not read; batches after one that ends with a
+ * detect pass are held back until that pass is enqueued.
  *
  * An ss_step is a stateful host object: it owns a fixed pool of events created at
  * ss_step_create, and, if the plan asks for them, issue threads (ss_issue_queue).

@@ -401,7 +401,9 @@ __device__ __forceinline__ uint32_t group_few(uint32_t m, E *s_list, GroupScratc
 // The class is the high bits of the mixed row id (kMix), the next bits choose the bucket.
 //
 // PACKED: the remaining row bits and the position of the lookup fit 32 bits, which is then
-// all that is grouped: half the LDS and half the registers.
+// all that is grouped: half the LDS and half the registers.  (64-bit entries, 26 tables of 4 M rows x
+// 1024 bags of 16, whole launch: 16.4 us; 13.9 packed, at 1 M rows; with the radix sort 39 and 38.
+// Per step through the scheduler, rows of 16 floats: 32.0, 30.3; 76 and 67.)
 // ---------------------------------------------------------------------------
 template <int NT, int ITEMS, bool PACKED>
 __device__ __forceinline__ void class_sort_body(
