@@ -236,8 +236,7 @@ __device__ __forceinline__ uint32_t group_entries(uint32_t m, int VB, int row_bi
         const uint32_t from = (uint32_t)(((uint64_t)lane * m) >> 6), width = m >> 6;
         const uint32_t place = from + __umulhi((uint32_t)(lane + 1) * kVoteMix, width);
         const uint32_t mine = (uint32_t)(load(place) >> VB);
-        // lanes that agree in ten bits of a hash stand for lanes that agree: a row that
-        // is taken for heavy without being it costs a ballot per round, nothing else
+        // the lanes that have a lane's row, by ten bits of a hash ...
         const uint32_t h = (mine * 0x9E3779B1u) >> 22;
         uint64_t same = ~0ull;
 #pragma unroll
@@ -245,6 +244,16 @@ __device__ __forceinline__ uint32_t group_entries(uint32_t m, int VB, int row_bi
             const bool one = (h >> b) & 1u;
             const uint64_t bal = __ballot(one);
             same &= one ? bal : ~bal;
+        }
+        // ... and, where these agree for several rows, by the row: each time round a group of lanes
+        // loses those that differ from its first.  (Of two heavy rows the second was not found, and
+        // its lookups compared each with each: 64 tables x 16384 lookups of two such rows 2469 us,
+        // 35 so.)
+        for (;;) {
+            const uint32_t row = (uint32_t)__shfl((int)mine, (int)__builtin_ctzll(same));
+            const uint64_t differ = __ballot(mine != row);
+            if (!differ) break;
+            same &= mine != row ? differ : ~differ;
         }
         const bool heavy = set_below(same) == 0 && __popcll(same) >= (int)kMinVotes;
         const uint64_t found = __ballot(heavy);

@@ -144,3 +144,36 @@ def test_periodic_bags_take_no_longer_than_the_same_lookups_in_any_order(L):
     us = [_best_us(lambda: Bd.ss_embbag_backward_prepare(tables, i, None, ws))
           for i in (bags, mixed)]
     assert us[0] < 2.0 * us[1], us
+
+
+def test_heavy_rows_whose_hashes_agree_take_no_longer_than_others():
+    # Two rows of one class that have all of its lookups between them.  The votes compare ten bits of a
+    # hash of the row: where these agree, the rows still have to be told apart, as a row that is not
+    # recognized costs a comparison per pair of its lookups.  64 tables x 16384 lookups of 2^20 rows:
+    # eight classes, by the highest three bits of the mixed row id.
+    from paper_2404_04270_amd import binding as Bd
+    T, key_bits, class_bits, B = 64, 20, 3, 8192
+    R, mix = 1 << key_bits, 0x9E3779B1
+    rem = key_bits - class_bits
+    mixed = (torch.arange(R) * mix) & (R - 1)
+    cls, above = mixed >> rem, mixed & ((1 << rem) - 1)
+    hashed = ((above * mix) & 0xFFFFFFFF) >> 22
+    first = 12345
+    same_class = cls == cls[first]
+    agree = (same_class & (hashed == hashed[first])).nonzero().flatten()
+    other = (same_class & (hashed != hashed[first])).nonzero().flatten()
+    agree = agree[agree != first]
+    assert agree.numel() > T
+    tables = Bd.Tables([torch.empty(1, 4, device="cuda") for _ in range(T)])
+    tables.rows = R                        # (the grouping reads no weights)
+    tables._refresh_struct()
+    ws = torch.empty(Bd.ss_backward_workspace_bytes(T, B, 2, 4), dtype=torch.uint8, device="cuda")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    which = torch.randint(0, 2, (T, 2 * B), device="cuda", generator=gen)
+    us = []
+    for second in (agree, other):
+        ids = torch.stack([torch.full((T,), first), second[:T]], dim=1).int().cuda()
+        idx = ids.gather(1, which).view(T, B, 2)
+        us.append(_best_us(lambda: Bd.ss_embbag_backward_prepare(tables, idx, None, ws)))
+    assert us[0] < 2.0 * us[1], us
