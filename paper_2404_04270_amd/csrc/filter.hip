@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kSmallThreads) void filter_small_kernel(
 
 // Lanes per sample of the one-launch filter, 0 where the batch is not for it.  Every table's
 // workgroup probes the bitmaps for the whole batch, and what bounds it once rows are stale is the rate
-// at which one compute unit gathers bitmap words: the lookups of the batch are bounded by `most`, and
+// at which one compute unit gathers bitmap words: the lookups of the batch are bounded, and
 // no lane is more than two rounds behind its first, one where bags are long (their index words lie
 // apart).  us of kernels (event pairs, less the 2 us that a pair adds) in two launches and in one, no
 // row stale and all hot rows stale: 8 tables x 128 lookups 5.3 and 4.1, 4.9 and 4.2; 5 x 777 bags of 3
@@ -335,10 +335,23 @@ __global__ __launch_bounds__(kSmallThreads) void filter_small_kernel(
 //   1000 x 8 18.6 and 17.5, 18.6 and 17.4; but 5 x 777 x 3 18.8 and 18.2, 19.2 and 20.0; 16 x 1024
 //   17.8 and 17.0, 17.6 and 19.0; 3 x 1024 x 5 19.6 and 18.4, 19.7 and 20.9; 1000 x 16 19.1 and 21.0,
 //   18.8 and 21.0.
-constexpr int64_t kSmallInLine = 16384, kSmallBeside = 8192;
-static int small_lanes(int64_t B, int L, int64_t total, int64_t most)
+//   Where fewer than all lookups suffice a verdict is seldom settled by the first few, and the probes of
+//   all tables' workgroups together count: at most 2 M of them in line, half a million beside training
+//   kernels.  us of kernels (20 calls of a graph) in two launches and in one, with half of the lookups
+//   sufficing and every other hot row stale: 16 x 1024 5.6 and 8.4, 128 x 128 6.4 and 11.7, 500 x 8 8.4
+//   and 11.0 (per training step in line 22.6 and 20.0, 25.2 and 22.2, 26.1 and 23.0); but 300 x 27 7.9
+//   and 15.5, 500 x 32 11.9 and 32.1, 1000 x 4 7.8 and 17.4 (26.3 and 29.3 per step), 1000 x 16 17.9 and
+//   78.9.  Per step through the scheduler 64 x 64 13.3 and 14.2, 64 x 128 13.2 and 14.1, 16 x 512 13.8
+//   and 13.0; but 128 x 64 14.1 and 16.7, 200 x 40 13.4 and 17.1, 1000 x 4 21.5 and 30.1.
+struct SmallMost {
+    int64_t lookups, probes;
+};
+constexpr SmallMost kSmallInLine = {16384, 1 << 21}, kSmallBeside = {8192, 1 << 19};
+static int small_lanes(int64_t B, int L, int64_t T, int alpha, const SmallMost &most)
 {
-    if (B > kSmallThreads || B * total > most) return 0;
+    const int64_t total = T * L;
+    if (B > kSmallThreads || B * total > most.lookups) return 0;
+    if (alpha > 0 && alpha < total && T * B * total > most.probes) return 0;
     int lanes = 64;
     while (lanes > 1 && B * lanes > kSmallThreads) lanes >>= 1;
     return lanes * (1 + (L < 8 ? 2 : 1) * kFlagProbes) >= total ? lanes : 0;
@@ -417,8 +430,8 @@ int32_t launch_filter(const ss_tables *tb, const int32_t *idx, int B, int L, int
                       uint8_t *skip_mask, int32_t *kept_ids, int32_t *n_kept, int32_t *idx_c,
                       void *ws, bool beside, hipStream_t s)
 {
-    const int small = small_lanes(B, L, (int64_t)tb->num_tables * L,
-                                  beside ? kSmallBeside : kSmallInLine);
+    const int small =
+        small_lanes(B, L, tb->num_tables, alpha, beside ? kSmallBeside : kSmallInLine);
     if (small) {
         ProfScope prof("filter_small_kernel", s);
         const int threads = ((B * small + 63) / 64) * 64;
